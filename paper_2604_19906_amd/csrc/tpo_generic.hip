@@ -1,6 +1,7 @@
 // Kernel of the inverse-Helmholtz operator for anisotropic elements: nx, ny, nz points along
 // axes 0, 1, 2, all runtime values in 1 .. 16.  It stands behind tpo_ihelm_apply_aniso for the
-// shapes that are not cubic (cubic shapes go to the tuned families).
+// shapes that are not cubic (cubic shapes go to the tuned families), except the fp32 calls for which
+// slice_kernel_pays() chooses the slice kernel (tpo_slice_f32.hip).
 //
 // Same scheme as the pencil kernels: a workgroup takes g whole elements, the cube lives in LDS,
 // every lane owns one pencil per mode product, the matrix entries arrive in SGPRs.  What makes
@@ -210,6 +211,8 @@ hipError_t launch_bound(const AnisoArgs &a)
     int g, nt;
     size_t lds;
     aniso_shape<T>(a, g, nt, lds);
+    if (sizeof(T) == 4 && slice_kernel_pays(a.nx, a.ny, a.nz, a.num_elems, g, nt / 64))
+        return launch_ihelm_slice(a);
     const long long groups = (a.num_elems + g - 1) / g;
     drop_stale_error();
     hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, ANISO_HINT, ANISO_XCD>),

@@ -73,6 +73,10 @@ struct AnisoArgs {
     hipStream_t stream;
 };
 hipError_t launch_ihelm_generic(const AnisoArgs &a, int dtype);
+// fp32: whether the slice kernel is the faster one for this call, given the pencil kernel's
+// elements and wavefronts per workgroup; its launcher (only for calls for which it is).
+bool slice_kernel_pays(int nx, int ny, int nz, long long num_elems, int elems_per_wg, int waves_per_wg);
+hipError_t launch_ihelm_slice(const AnisoArgs &a);
 
 // dtype index: 0 = f64, 1 = f32.  n in 1..TPO_MAX_N.  Returns nullptr when the family has
 // no kernel for that shape.
