@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include "tpo_pencil.hpp"
+#include "tpo_pencil_mm.hpp"
 
 namespace tpo {
 
@@ -72,18 +73,122 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     }
 }
 
+// fp32 form with the mode products issued as 4x4x1 matrix-core outer products (tpo_pencil_mm.hpp):
+// same data movement, same order of the sums, bit-identical results.  The table of axis 2 goes
+// straight into registers, those of axes 1 and 0 are built once per workgroup and parked in LDS
+// until the barrier before their use.  Idle lanes shadow pencil 0 of the batch's first element and
+// never store (the matrix instructions read their coefficients from active lanes).
+// What bounds it: the vector-FMA form issues 3 n^2 FMAs of 4 cycles per pencil, half as many cycles
+// here; what is left is the memory system (a plain copy in the same pieces runs at 5.75 TB/s).  On
+// 3 GB, us per call against the vector-FMA form: n = 12 539 / 551, 13 538 / 555, 15 593 / 627, 16
+// 519 / 569.  Where n is smaller or wastes a row group (n = 4 .. 11, 14) the two are equal or the
+// vector form leads (n = 10 548 against 568, 11 535 / 539, 14 622 / 623), so those keep it.
+template <int N, int G, int HINT, bool XCD, bool FWD>
+__global__ void __launch_bounds__((PencilShape<float, N, G>::NT))
+__attribute__((amdgpu_waves_per_eu(mm_waves_per_simd<N>())))
+transform_mm_kernel(const float *u, const float *__restrict__ Sx, const float *__restrict__ Sy,
+                    const float *__restrict__ Sz, float *t, long long num_elems)
+{
+    using Sh = PencilShape<float, N, G>;
+    using M = MmShape<N>;
+    constexpr int P = Sh::P, PA = Sh::PA, PB = Sh::PB, CUBE = Sh::CUBE, N3 = N * N * N;
+    constexpr int NWAVES = Sh::NT / 64, ROWS = 2 * M::NTAB, PER_WAVE = (ROWS + NWAVES - 1) / NWAVES;
+    extern __shared__ __align__(16) unsigned char tpo_lds[];
+    float *cube_all = reinterpret_cast<float *>(tpo_lds);
+    float *tabs = cube_all + G * CUBE;                  // [axis 1, axis 0][register][lane]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const long long nbatch = (num_elems + G - 1) / G;
+    const long long batch = pencil_batch<XCD>(nbatch);
+    if (XCD && batch >= nbatch) return;                 // whole workgroup: no barrier is skipped
+    const int g_ = tid / P;
+    const bool on = (tid < G * P) && (batch * G + g_ < num_elems);
+    const int g = on ? g_ : 0;
+    const int p = on ? tid - g_ * P : 0;
+    const int hi = p / N, lo = p - hi * N;
+    float *cube = cube_all + g * CUBE;
+    const size_t wg_base = (size_t)(batch * G) * (size_t)N3;
+
+    float x[N], y[M::NY], tab[M::NTAB];
+
+    // axis 2: lane (a,b) = (hi,lo) owns u[a][b][0..n-1], contiguous in memory
+#pragma unroll
+    for (int r = 0; r < M::NTAB; ++r) tab[r] = mm_coef<N>(Sz, FWD, r, lane);
+    load_words<(HINT & 1) != 0>(u + wg_base + (unsigned)(g * N3 + p * N), x);
+    {
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        float val[PER_WAVE];
+#pragma unroll
+        for (int k = 0; k < PER_WAVE; ++k) {
+            const int r = wave + k * NWAVES < ROWS ? wave + k * NWAVES : ROWS - 1;
+            val[k] = r < M::NTAB ? mm_coef<N>(Sy, FWD, r, lane) : mm_coef<N>(Sx, FWD, r - M::NTAB, lane);
+        }
+#pragma unroll
+        for (int k = 0; k < PER_WAVE; ++k) {
+            const int r = wave + k * NWAVES < ROWS ? wave + k * NWAVES : ROWS - 1;
+            tabs[r * 64 + lane] = val[k];
+        }
+    }
+    mode_product_mm<N, FWD>(tab, (const TPO_CONSTANT float *)Sz, x, y);
+    if (on) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) cube[hi * PA + lo * PB + k] = y[k];
+    }
+    __syncthreads();
+
+    // axis 1: lane (a,c) = (hi,lo)
+    mm_fetch_table<N>(tabs, 1, lane, tab);
+#pragma unroll
+    for (int m = 0; m < N; ++m) x[m] = cube[hi * PA + m * PB + lo];
+    mode_product_mm<N, FWD>(tab, (const TPO_CONSTANT float *)Sy, x, y);
+    if (on) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) cube[hi * PA + j * PB + lo] = y[j];
+    }
+    __syncthreads();
+
+    // axis 0: lane (b,c) = (hi,lo); stores are consecutive over lanes
+    mm_fetch_table<N>(tabs, 2, lane, tab);
+#pragma unroll
+    for (int l = 0; l < N; ++l) x[l] = cube[l * PA + hi * PB + lo];
+    mode_product_mm<N, FWD>(tab, (const TPO_CONSTANT float *)Sx, x, y);
+    if (on) {
+        float *tb = t + wg_base + (unsigned)(g * N3 + p);
+#pragma unroll
+        for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(tb + i * P, y[i]);
+    }
+}
+
 // Elements per workgroup and die renumbering as for the separable-diagonal operator kernels
 // (same traffic: one field in, one out); cached loads, since each lane's n-word run shares its
-// cache lines with its neighbours' runs.
+// cache lines with its neighbours' runs.  The matrix-core form has its own rows: the best of 1 .. 3
+// elements per workgroup x non-temporal stores x renumbering.
+template <typename T, int N> struct TransformTune {
+    using Tune = PencilSepTune<T, N>;
+    static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
+    static constexpr bool XCD = Tune::XCD, MM = false;
+};
+template <int GG, int H, bool X> struct TransformMmRow {
+    static constexpr int G = GG, HINT = H;
+    static constexpr bool XCD = X, MM = true;
+};
+template <> struct TransformTune<float, 12> : TransformMmRow<3, 0, true> {};
+template <> struct TransformTune<float, 13> : TransformMmRow<3, 0, true> {};
+template <> struct TransformTune<float, 15> : TransformMmRow<2, 0, true> {};
+template <> struct TransformTune<float, 16> : TransformMmRow<1, 2, false> {};
+
 template <typename T, int N, bool FWD>
 struct TransformLauncher {
-    using Tune = PencilSepTune<T, N>;
+    using Tune = TransformTune<T, N>;
     static constexpr int G = Tune::G;
     using Sh = PencilShape<T, N, G>;
-    static constexpr size_t LDS = Sh::LDS_BYTES / 2;
-    static constexpr int HINT = Tune::HINT & 2;
+    static constexpr size_t LDS = Sh::LDS_BYTES / 2 + (Tune::MM ? 2 * MmShape<N>::NTAB * 256 : 0);
 
-    static constexpr auto kernel() { return &transform_pencil_kernel<T, N, G, HINT, Tune::XCD, FWD>; }
+    static constexpr auto kernel()
+    {
+        if constexpr (Tune::MM) return &transform_mm_kernel<N, G, Tune::HINT, Tune::XCD, FWD>;
+        else return &transform_pencil_kernel<T, N, G, Tune::HINT, Tune::XCD, FWD>;
+    }
 
     static hipError_t launch(const TransformArgs &a)
     {
