@@ -80,9 +80,11 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
 // never store (the matrix instructions read their coefficients from active lanes).
 // What bounds it: the vector-FMA form issues 3 n^2 FMAs of 4 cycles per pencil, half as many cycles
 // here; what is left is the memory system (a plain copy in the same pieces runs at 5.75 TB/s).  On
-// 3 GB, us per call against the vector-FMA form: n = 12 539 / 551, 13 538 / 555, 15 593 / 627, 16
-// 519 / 569.  Where n is smaller or wastes a row group (n = 4 .. 11, 14) the two are equal or the
-// vector form leads (n = 10 548 against 568, 11 535 / 539, 14 622 / 623), so those keep it.
+// 3 GB, us per call against the vector-FMA form: n = 12 539 / 551, 13 538 / 555, 14 623 / 622, 15
+// 593 / 627, 16 519 / 569; n = 8 485 / 483, 9 520 / 524, 10 568 / 548, 11 539 / 535.  While both
+// fields stay in the last-level cache (256 MB) the cycles count for more, and n = 8 .. 11 gain
+// too (150 MB: 22.1 / 23.7, 24.4 / 25.3, 26.8 / 28.2, 26.3 / 27.5; 40 MB: 5.2 / 6.2, 8.3 / 8.6, 9.3 /
+// 10.1, 9.2 / 10.2; 600 MB: 96 / 89, 105 / 105, 116 / 110, 111 / 107); n = 4 .. 7 do not.
 template <int N, int G, int HINT, bool XCD, bool FWD>
 __global__ void __launch_bounds__((PencilShape<float, N, G>::NT))
 __attribute__((amdgpu_waves_per_eu(mm_waves_per_simd<N>())))
@@ -174,12 +176,20 @@ template <int GG, int H, bool X> struct TransformMmRow {
 };
 template <> struct TransformTune<float, 12> : TransformMmRow<3, 0, true> {};
 template <> struct TransformTune<float, 13> : TransformMmRow<3, 0, true> {};
+template <> struct TransformTune<float, 14> : TransformMmRow<2, 0, false> {};
 template <> struct TransformTune<float, 15> : TransformMmRow<2, 0, true> {};
 template <> struct TransformTune<float, 16> : TransformMmRow<1, 2, false> {};
 
-template <typename T, int N, bool FWD>
-struct TransformLauncher {
-    using Tune = TransformTune<T, N>;
+// Settings while both fields stay in the last-level cache: the matrix-core form from n = 8 on.
+template <typename T, int N> struct TransformCachedTune : TransformTune<T, N> {};
+template <> struct TransformCachedTune<float, 8> : TransformMmRow<2, 2, false> {};
+template <> struct TransformCachedTune<float, 9> : TransformMmRow<3, 0, false> {};
+template <> struct TransformCachedTune<float, 10> : TransformMmRow<2, 0, false> {};
+template <> struct TransformCachedTune<float, 11> : TransformMmRow<2, 0, false> {};
+constexpr long long kTransformCachedBytes = 256LL << 20;
+
+template <typename T, int N, bool FWD, typename Tune>
+struct TransformLauncherT {
     static constexpr int G = Tune::G;
     using Sh = PencilShape<T, N, G>;
     static constexpr size_t LDS = Sh::LDS_BYTES / 2 + (Tune::MM ? 2 * MmShape<N>::NTAB * 256 : 0);
@@ -206,6 +216,22 @@ struct TransformLauncher {
         if (LDS <= 48 * 1024) return hipSuccess;
         return hipFuncSetAttribute((const void *)kernel(),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    }
+};
+
+template <typename T, int N, bool FWD>
+struct TransformLauncher {
+    using Plain = TransformLauncherT<T, N, FWD, TransformTune<T, N>>;
+    using Cached = TransformLauncherT<T, N, FWD, TransformCachedTune<T, N>>;
+    static hipError_t launch(const TransformArgs &a)
+    {
+        constexpr long long most = kTransformCachedBytes / (2LL * N * N * N * (long long)sizeof(T));
+        return a.num_elems <= most ? Cached::launch(a) : Plain::launch(a);
+    }
+    static hipError_t prepare()
+    {
+        const hipError_t rc = Plain::prepare();
+        return rc != hipSuccess ? rc : Cached::prepare();
     }
 };
 
