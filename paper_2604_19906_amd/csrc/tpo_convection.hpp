@@ -21,6 +21,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "tpo_pencil.hpp"
 #include "tpo_pencil_mm.hpp"
 
@@ -446,6 +448,127 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     }
 }
 
+// The same phases for batches that pass the last-level cache.  Every phase works out its unit and
+// addresses where it uses them instead of once for all lanes and phases: fp64 (8,12) with compact
+// lanes then takes 84 instead of 97 registers (five wavefronts per SIMD instead of four), and the
+// loads leave earlier (fp64 (8,10), one unit, same occupancy: 441 against 488 us on 2.5 GB).  On
+// batches that stay in the cache the form above is up to 8 % ahead (fp64 (9,11), fp32 (11,12)).
+// COMPACT: the lanes of the axis-m and axis-n phases are numbered through over the workgroup's units
+// with that phase's own pencil count, so that these phases (fewer pencils) leave whole wavefronts
+// idle; otherwise a unit keeps its NQ*NQ lanes throughout and part of every wavefront idles, which
+// spreads the stores over more wavefronts.
+template <typename T, int NV, int NQ, int G, int HINT, bool XCD, bool COMPACT>
+__global__ void __launch_bounds__((ConvRectShape<T, NV, NQ, G>::NT))
+convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const T *Dm_,
+                             const T *Im_, T *__restrict__ F, long long num_elems)
+{
+    using Sh = ConvRectShape<T, NV, NQ, G>;
+    constexpr int PA = Sh::PA, PB = Sh::PB, CUBE = Sh::CUBE;
+    extern __shared__ __align__(16) unsigned char tpo_lds[];
+    T *lds = reinterpret_cast<T *>(tpo_lds);
+
+    const TPO_CONSTANT T *Dm = (const TPO_CONSTANT T *)Dm_;
+    const TPO_CONSTANT T *Im = (const TPO_CONSTANT T *)Im_;
+
+    const int tid = threadIdx.x;
+    const long long units = 3 * num_elems;
+    const long long nbatch = (units + G - 1) / G;
+    const long long batch = convection_batch<XCD>();
+    if (XCD && batch >= nbatch) return;                 // whole workgroup: no barrier is skipped
+    const long long left = units - batch * G;
+    const int here = left < G ? (int)left : G;          // units of this workgroup
+    constexpr size_t QC = (size_t)NQ * NQ * NQ, VC = (size_t)NV * NV * NV;
+
+    const int gl = tid / (NQ * NQ), pl = tid - gl * (NQ * NQ);      // pencils along l: lane (n,m)
+    constexpr int PM = NQ * NV, PN = NV * NV, LM = COMPACT ? PM : NQ * NQ, LN = COMPACT ? PN : NQ * NQ;
+    const int gm = tid / LM, pm = tid - gm * LM;                    // pencils along m: lane (n,i)
+    const int gn = tid / LN, pn = tid - gn * LN;                    // pencils along n: lane (j,i)
+    const bool on_l = gl < here, on_m = gm < here && pm < PM, on_n = gn < here && pn < PN;
+
+    T xq[NQ], x2[NQ], yv[NV], zv[NV];
+
+    // axis l: lane (n,m) owns the NQ consecutive words [e][n][m][0..NQ-1] of M and P
+    if (on_l) {
+        const long long unit = batch * G + gl;
+        const long long e = unit / 3;
+        const int c = (int)(unit - 3 * e);
+        T mq[NQ];
+        load_words<(HINT & 1) != 0>(Mq + (size_t)e * QC + (size_t)(pl * NQ), mq);
+#pragma unroll
+        for (int dir = 0; dir < 3; ++dir) {
+            const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
+            load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(pl * NQ), xq);
+#pragma unroll
+            for (int l = 0; l < NQ; ++l) xq[l] *= mq[l];
+            if (dir == 2) {
+#pragma unroll
+                for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
+            } else {
+                mode_product_rect<T, NV, NQ>(dir == 0 ? Dm : Im, xq, yv);
+                T *dst = lds + (2 * gl + dir) * CUBE;
+                const int nn = pl / NQ, mm = pl - nn * NQ;
+#pragma unroll
+                for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
+            }
+        }
+    }
+    __syncthreads();
+
+    // axis m, first two terms merged: lane (n,i)
+    T *c0 = lds + 2 * gm * CUBE, *c1 = c0 + CUBE;
+    const int bn = pm / NV, bi = pm - bn * NV;
+    if (on_m) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) xq[m] = c0[bn * PA + m * PB + bi];
+        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
+        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+    }
+    __syncthreads();                                    // every pencil of cubes 0 and 1 has been read
+    if (on_m) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) c0[bn * PA + j * PB + bi] = yv[j] + zv[j];
+    }
+    // axis l of the third term, into the freed cube 1: lane (n,m)
+    if (on_l) {
+        T *dst = lds + (2 * gl + 1) * CUBE;
+        const int nn = pl / NQ, mm = pl - nn * NQ;
+        mode_product_rect<T, NV, NQ>(Im, x2, yv);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
+    }
+    __syncthreads();
+    // axis m of the third term: lane (n,i)
+    if (on_m) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
+        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) c1[bn * PA + j * PB + bi] = yv[j];   // the lane's own pencil
+    }
+    __syncthreads();
+
+    // axis n: lane (j,i); stores are consecutive over lanes
+    if (on_n) {
+        const T *d0 = lds + 2 * gn * CUBE, *d1 = d0 + CUBE;
+        const int jj = pn / NV, ii = pn - jj * NV;
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) xq[n] = d0[n * PA + jj * PB + ii];
+        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) xq[n] = d1[n * PA + jj * PB + ii];
+        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+        const long long unit = batch * G + gn;
+        const long long e = unit / 3;
+        const size_t out = ((size_t)(unit - 3 * e) * (size_t)num_elems + (size_t)e) * VC;
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            gstore<(HINT & 2) != 0>(F + out + (size_t)(k * NV * NV + pn), yv[k] + zv[k]);
+    }
+}
+
+// Units per workgroup by lane utilisation: with at most 512 threads and 56 KB of LDS.
 template <typename T, int NV, int NQ>
 constexpr int convection_rect_group()
 {
@@ -465,15 +588,63 @@ constexpr int convection_rect_group()
     return best;
 }
 
+// Batches whose fields stay in the last-level cache (256 MB) take the utilisation rule's group and the
+// first form, larger ones the second form where a row below pays (1 % or more): the best of a sweep on MI355X over {1, 2,
+// 3, 4, 6, 8, 12} units, the rule's group and both lane numberings, 2 GB per call.  us per call on 2.5
+// GB, before / now: fp64 (5,8) 536 / 493, (6,9) 517 / 479, (8,10) 523 / 441, (8,12) 515 / 486, (10,12)
+// 529 / 472, (11,12) 648 / 479; fp32 (3,4) 492 / 454, (10,12) 527 / 498, (11,13) 546 / 510, (9,14) 517 /
+// 473.
+// `always`: the row also wins (or ties) on small batches, mostly because it takes the smaller
+// workgroups of the two (150 MB: fp64 (8,10) 31.3 / 25.9, (11,12) 45.9 / 33.6); larger groups lose
+// there, where a launch is a few rounds of workgroups (2 MB: fp64 (6,8) 3.8 / 5.9, (7,11) 5.6 / 7.2).
+struct ConvRectRow { int nv, nq, g, compact, always; };
+template <typename T> struct ConvRectTable;
+template <> struct ConvRectTable<double> {
+    static constexpr ConvRectRow row[] = {
+        {2, 4, 6, 1, 0},   {3, 4, 6, 0, 0},   {4, 5, 12, 1, 0},  {5, 7, 8, 1, 0},   {5, 8, 4, 0, 0},
+        {6, 7, 9, 0, 0},   {6, 8, 8, 1, 0},   {6, 9, 6, 0, 0},   {7, 8, 8, 0, 0},   {7, 9, 6, 0, 0},
+        {7, 11, 4, 1, 0},  {8, 9, 3, 0, 0},   {8, 10, 1, 0, 1},  {8, 12, 3, 1, 0},  {9, 10, 1, 0, 1},
+        {9, 11, 2, 0, 0},  {9, 14, 2, 1, 1},  {10, 12, 1, 0, 1}, {11, 12, 1, 0, 1}, {12, 13, 1, 0, 0},
+        {12, 14, 1, 0, 0},
+    };
+};
+template <> struct ConvRectTable<float> {
+    static constexpr ConvRectRow row[] = {
+        {2, 3, 12, 1, 0},  {2, 4, 12, 0, 0},  {3, 4, 8, 1, 0},   {3, 5, 8, 1, 0},   {4, 5, 8, 1, 0},
+        {4, 6, 4, 0, 0},   {5, 7, 8, 0, 0},   {5, 8, 6, 0, 0},   {6, 9, 4, 1, 1},   {7, 8, 1, 0, 0},
+        {8, 10, 3, 1, 1},  {8, 12, 2, 1, 1},  {9, 11, 2, 1, 0},  {9, 14, 2, 1, 1},  {10, 11, 2, 1, 0},
+        {10, 12, 2, 1, 0}, {11, 13, 3, 1, 0}, {12, 14, 2, 1, 0},
+    };
+};
+template <typename T>
+constexpr ConvRectRow convection_rect_row(int nv, int nq)
+{
+    for (const ConvRectRow &r : ConvRectTable<T>::row)
+        if (r.nv == nv && r.nq == nq) return r;
+    return {nv, nq, 0, 0, 0};           // no row: the first form at every batch size
+}
+
+constexpr long long kConvectionCachedBytes = 256LL << 20;
+// Elements whose ten input and three output cubes fill the last-level cache.
 template <typename T, int NV, int NQ>
-struct ConvectionRectLauncher {
-    static constexpr int G = convection_rect_group<T, NV, NQ>();
+constexpr long long convection_cached_elems()
+{
+    return kConvectionCachedBytes
+           / ((10LL * NQ * NQ * NQ + 3LL * NV * NV * NV) * (long long)sizeof(T));
+}
+
+template <typename T, int NV, int NQ, int G, bool LARGE, bool COMPACT>
+struct ConvectionRectLauncherT {
     using Sh = ConvRectShape<T, NV, NQ, G>;
     static constexpr size_t LDS = Sh::LDS_BYTES;
     static constexpr int HINT = 2;
     static constexpr bool XCD = G % 3 != 0;
 
-    static constexpr auto kernel() { return &convection_rect_kernel<T, NV, NQ, G, HINT, XCD>; }
+    static constexpr auto kernel()
+    {
+        if constexpr (LARGE) return &convection_rect_large_kernel<T, NV, NQ, G, HINT, XCD, COMPACT>;
+        else return &convection_rect_kernel<T, NV, NQ, G, HINT, XCD>;
+    }
 
     static hipError_t launch(const ConvectionArgs &a)
     {
@@ -491,6 +662,25 @@ struct ConvectionRectLauncher {
         if (LDS <= 48 * 1024) return hipSuccess;
         return hipFuncSetAttribute((const void *)kernel(),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    }
+};
+
+template <typename T, int NV, int NQ>
+struct ConvectionRectLauncher {
+    static constexpr ConvRectRow R = convection_rect_row<T>(NV, NQ);
+    using Rule = ConvectionRectLauncherT<T, NV, NQ, convection_rect_group<T, NV, NQ>(), false, false>;
+    using Row = ConvectionRectLauncherT<T, NV, NQ, R.g != 0 ? R.g : 1, true, R.compact != 0>;
+    using Large = std::conditional_t<R.g != 0, Row, Rule>;
+    using Cached = std::conditional_t<R.always != 0, Row, Rule>;
+
+    static hipError_t launch(const ConvectionArgs &a)
+    {
+        return a.num_elems <= convection_cached_elems<T, NV, NQ>() ? Cached::launch(a) : Large::launch(a);
+    }
+    static hipError_t prepare()
+    {
+        const hipError_t rc = Large::prepare();
+        return rc != hipSuccess ? rc : Cached::prepare();
     }
 };
 
@@ -502,26 +692,46 @@ struct ConvectionRectEntry {
     ConvectionRectEntry { NV, NQ, ConvectionEntry { &ConvectionRectLauncher<T, NV, NQ>::launch, \
                                                     &ConvectionRectLauncher<T, NV, NQ>::prepare } }
 
-template <typename T, int N>
-struct ConvectionLauncher {
+// Square shapes: units per workgroup by lane utilisation, SPLIT by size, and in fp32 from n = 9 on
+// the 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there, as for the
+// inverse-Helmholtz operator).  A sweep over 1 .. 16 units x SPLIT x form on MI355X found more for
+// some n (us per call on 2.5 GB, rule / setting): fp64 n = 7 454 / 430, n = 10 484 / 432, which also
+// hold on small batches (150 MB: 31.1 / 25.9, 31.8 / 30.3; 2 MB: 4.9 / 4.1, 7.2 / 6.1), as does
+// fp32 n = 7 (462 / 446, 27.5 / 26.1, 4.4 / 4.0); fp64 n = 3 525 / 499, 9 460 / 444 and fp32 n = 3 567 / 516,
+// 5 486 / 468, 11 502 / 466, which only pay once the fields pass the last-level cache.
+template <typename T, int N> struct ConvectionTune {
     static constexpr int G = convection_group<T, N>();
-    using Sh = PencilShape<T, N, G>;
     static constexpr bool SPLIT = convection_split<T, N>();
-    static constexpr size_t LDS = (size_t)(SPLIT ? 2 : 3) * G * Sh::CUBE * sizeof(T);
-    // Sweep on MI355X (units per workgroup 1..6 x hints x renumbering; fp64 n = 8, 11, fp32
-    // n = 13): non-temporal stores are worth 3 to 8 %, non-temporal loads halve the rate (the
-    // per-lane runs share cache lines), more units per workgroup do not pay.
+    static constexpr bool MM = sizeof(T) == 4 && N >= 9;
+};
+template <int GG, bool S, bool M> struct ConvectionSet {
+    static constexpr int G = GG;
+    static constexpr bool SPLIT = S, MM = M;
+};
+template <> struct ConvectionTune<double, 7> : ConvectionSet<1, false, false> {};
+template <> struct ConvectionTune<double, 10> : ConvectionSet<1, true, false> {};
+template <> struct ConvectionTune<float, 7> : ConvectionSet<1, true, true> {};
+template <typename T, int N> struct ConvectionLargeTune : ConvectionTune<T, N> {};
+template <> struct ConvectionLargeTune<double, 3> : ConvectionSet<16, false, false> {};
+template <> struct ConvectionLargeTune<double, 9> : ConvectionSet<3, true, false> {};
+template <> struct ConvectionLargeTune<float, 3> : ConvectionSet<16, false, false> {};
+template <> struct ConvectionLargeTune<float, 5> : ConvectionSet<8, false, false> {};
+template <> struct ConvectionLargeTune<float, 11> : ConvectionSet<2, true, true> {};
+
+template <typename T, int N, typename Tune>
+struct ConvectionLauncherT {
+    static constexpr int G = Tune::G;
+    using Sh = PencilShape<T, N, G>;
+    static constexpr size_t LDS = (size_t)(Tune::SPLIT ? 2 : 3) * G * Sh::CUBE * sizeof(T);
+    // Non-temporal stores are worth 3 to 8 %, non-temporal loads halve the rate (the per-lane runs
+    // share cache lines).
     static constexpr int HINT = 2;
     static constexpr bool XCD = G % 3 != 0;    // with G a multiple of 3 an element stays in one workgroup
 
-    // fp32, n >= 9: the 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there,
-    // as for the inverse-Helmholtz operator).
-    static constexpr bool MM = sizeof(T) == 4 && N >= 9;
-
     static constexpr auto kernel()
     {
-        if constexpr (MM) return &convection_mm_kernel<N, G, HINT, XCD, SPLIT>;
-        else return &convection_pencil_kernel<T, N, G, HINT, XCD, SPLIT>;
+        if constexpr (Tune::MM) return &convection_mm_kernel<N, G, HINT, XCD, Tune::SPLIT>;
+        else return &convection_pencil_kernel<T, N, G, HINT, XCD, Tune::SPLIT>;
     }
 
     static hipError_t launch(const ConvectionArgs &a)
@@ -540,6 +750,21 @@ struct ConvectionLauncher {
         if (LDS <= 48 * 1024) return hipSuccess;
         return hipFuncSetAttribute((const void *)kernel(),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    }
+};
+
+template <typename T, int N>
+struct ConvectionLauncher {
+    using Cached = ConvectionLauncherT<T, N, ConvectionTune<T, N>>;
+    using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>>;
+    static hipError_t launch(const ConvectionArgs &a)
+    {
+        return a.num_elems <= convection_cached_elems<T, N, N>() ? Cached::launch(a) : Large::launch(a);
+    }
+    static hipError_t prepare()
+    {
+        const hipError_t rc = Cached::prepare();
+        return rc != hipSuccess ? rc : Large::prepare();
     }
 };
 
