@@ -419,6 +419,30 @@ template <> struct PencilSepTune<double, 9> : PencilTune<double, 9> {
     static constexpr int G = 2, HINT = 0;       // (the D form's retuning at n = 9 was not repeated here)
 };
 
+// Settings of a pencil kernel spelled out.
+template <int GG, int H, bool X> struct PencilSet {
+    static constexpr int G = GG, HINT = H;
+    static constexpr bool DDIRECT = true, XCD = X;
+    static constexpr size_t LDS_MIN = 0;
+};
+// Separable form on batches whose two fields pass the last-level cache, where a sweep over 1 .. 32
+// elements per workgroup x hints x renumbering on 2 GB per call found 4 % or more against the D form's
+// settings (us per call on 2.5 GB, before / now): fp64 n = 3 578 / 544, 5 530 / 464,
+// 6 566 / 483, 9 550 / 522; fp32 n = 3 691 / 620, 4 456 / 443, 5 580 / 563, 6 580 / 551.  On smaller batches
+// the gains are larger (600 MB: fp64 n = 6 136 / 115, fp32 n = 6 144 / 123); while the fields stay in the
+// cache there are none to be had.
+constexpr long long kPencilCachedBytes = 256LL << 20;
+template <typename T, int N>
+struct PencilSepLargeTune : PencilSepTune<T, N> {};
+template <> struct PencilSepLargeTune<double, 3> : PencilSet<24, 0, false> {};
+template <> struct PencilSepLargeTune<double, 5> : PencilSet<2, 2, false> {};
+template <> struct PencilSepLargeTune<double, 6> : PencilSet<3, 0, true> {};
+template <> struct PencilSepLargeTune<double, 9> : PencilSet<3, 0, false> {};
+template <> struct PencilSepLargeTune<float, 3> : PencilSet<24, 2, false> {};
+template <> struct PencilSepLargeTune<float, 4> : PencilSet<4, 2, false> {};
+template <> struct PencilSepLargeTune<float, 5> : PencilSet<2, 0, true> {};
+template <> struct PencilSepLargeTune<float, 6> : PencilSet<6, 2, false> {};
+
 // SEP: 0 = D read from memory, 1 / 2 = separable diagonal (IEEE division / fast reciprocal).
 template <typename T, int N, typename Tune, int SEP>
 struct PencilLauncherT {
@@ -458,18 +482,24 @@ struct PencilLauncher {
     using Plain = PencilLauncherT<T, N, PencilTune<T, N>, 0>;
     using Small = PencilLauncherT<T, N, PencilSmallTune<T, N>, 0>;
     using Sep = PencilLauncherT<T, N, PencilSepTune<T, N>, 2>;   // fast reciprocal
+    using SepLarge = PencilLauncherT<T, N, PencilSepLargeTune<T, N>, 2>;
     static hipError_t launch(const ApplyArgs &a)
     {
         using St = PencilSmallTune<T, N>;
         if (a.num_elems > St::LO && a.num_elems <= St::HI) return Small::launch(a);
         return Plain::launch(a);
     }
-    static hipError_t launch_sep(const ApplyArgs &a) { return Sep::launch(a); }
+    static hipError_t launch_sep(const ApplyArgs &a)
+    {
+        constexpr long long cached = kPencilCachedBytes / (2LL * N * N * N * (long long)sizeof(T));
+        return a.num_elems <= cached ? Sep::launch(a) : SepLarge::launch(a);
+    }
     static hipError_t prepare()
     {
         hipError_t rc = Plain::prepare();
         if (rc == hipSuccess) rc = Small::prepare();
-        return rc != hipSuccess ? rc : Sep::prepare();
+        if (rc == hipSuccess) rc = Sep::prepare();
+        return rc != hipSuccess ? rc : SepLarge::prepare();
     }
 };
 

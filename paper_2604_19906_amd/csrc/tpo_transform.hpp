@@ -169,24 +169,48 @@ template <typename T, int N> struct TransformTune {
     using Tune = PencilSepTune<T, N>;
     static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
     static constexpr bool XCD = Tune::XCD, MM = false;
+    static constexpr long long FROM = kPencilCachedBytes;       // of the settings for large batches
 };
-template <int GG, int H, bool X> struct TransformMmRow {
+template <int GG, int H, bool X, bool M, long long MB = 256> struct TransformSet {
     static constexpr int G = GG, HINT = H;
-    static constexpr bool XCD = X, MM = true;
+    static constexpr bool XCD = X, MM = M;
+    static constexpr long long FROM = MB << 20;
 };
-template <> struct TransformTune<float, 12> : TransformMmRow<3, 0, true> {};
-template <> struct TransformTune<float, 13> : TransformMmRow<3, 0, true> {};
-template <> struct TransformTune<float, 14> : TransformMmRow<2, 0, false> {};
-template <> struct TransformTune<float, 15> : TransformMmRow<2, 0, true> {};
-template <> struct TransformTune<float, 16> : TransformMmRow<1, 2, false> {};
-
-// Settings while both fields stay in the last-level cache: the matrix-core form from n = 8 on.
-template <typename T, int N> struct TransformCachedTune : TransformTune<T, N> {};
-template <> struct TransformCachedTune<float, 8> : TransformMmRow<2, 2, false> {};
-template <> struct TransformCachedTune<float, 9> : TransformMmRow<3, 0, false> {};
-template <> struct TransformCachedTune<float, 10> : TransformMmRow<2, 0, false> {};
-template <> struct TransformCachedTune<float, 11> : TransformMmRow<2, 0, false> {};
-constexpr long long kTransformCachedBytes = 256LL << 20;
+template <> struct TransformTune<float, 12> : TransformSet<3, 0, true, true> {};
+template <> struct TransformTune<float, 13> : TransformSet<3, 0, true, true> {};
+template <> struct TransformTune<float, 14> : TransformSet<2, 0, false, true> {};
+template <> struct TransformTune<float, 15> : TransformSet<2, 0, true, true> {};
+template <> struct TransformTune<float, 16> : TransformSet<1, 2, false, true> {};
+// While both fields stay in the last-level cache: the matrix-core form from n = 8 on.
+template <> struct TransformTune<float, 8> : TransformSet<2, 2, false, true> {};
+template <> struct TransformTune<float, 9> : TransformSet<3, 0, false, true> {};
+template <> struct TransformTune<float, 10> : TransformSet<2, 0, false, true> {};
+template <> struct TransformTune<float, 11> : TransformSet<2, 0, false, true> {};
+// Beyond: the vector-FMA form for those, and settings from a sweep over 1 .. 32 elements per workgroup
+// x stores x renumbering on 2 GB per call where it found 4 % or more (us per call on 2.5
+// GB, before / now): fp64 n = 3 460 / 434, 4 427 / 384, 7 452 / 427, 9 450 / 433, 10 476 / 439, 12 454 /
+// 435, 13 480 / 450; fp32 n = 3 569 / 531, 5 491 / 450.  (n = 7, 10: only past 1 GB, at 600 MB 101 / 108,
+// 110 / 114.)
+template <typename T, int N> struct TransformLargeTune : TransformTune<T, N> {};
+template <int N> struct TransformVectorTune {
+    using Tune = PencilSepTune<float, N>;
+    static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
+    static constexpr bool XCD = Tune::XCD, MM = false;
+    static constexpr long long FROM = kPencilCachedBytes;
+};
+template <> struct TransformLargeTune<float, 8> : TransformVectorTune<8> {};
+template <> struct TransformLargeTune<float, 9> : TransformVectorTune<9> {};
+template <> struct TransformLargeTune<float, 10> : TransformVectorTune<10> {};
+template <> struct TransformLargeTune<float, 11> : TransformVectorTune<11> {};
+template <> struct TransformLargeTune<float, 3> : TransformSet<24, 2, false, false> {};
+template <> struct TransformLargeTune<float, 5> : TransformSet<2, 0, true, false> {};
+template <> struct TransformLargeTune<double, 3> : TransformSet<24, 0, true, false> {};
+template <> struct TransformLargeTune<double, 4> : TransformSet<2, 2, false, false> {};
+template <> struct TransformLargeTune<double, 7> : TransformSet<6, 0, true, false, 1024> {};
+template <> struct TransformLargeTune<double, 9> : TransformSet<4, 0, true, false> {};
+template <> struct TransformLargeTune<double, 10> : TransformSet<3, 0, true, false, 1024> {};
+template <> struct TransformLargeTune<double, 12> : TransformSet<2, 2, true, false> {};
+template <> struct TransformLargeTune<double, 13> : TransformSet<2, 0, true, false> {};
 
 template <typename T, int N, bool FWD, typename Tune>
 struct TransformLauncherT {
@@ -221,17 +245,17 @@ struct TransformLauncherT {
 
 template <typename T, int N, bool FWD>
 struct TransformLauncher {
-    using Plain = TransformLauncherT<T, N, FWD, TransformTune<T, N>>;
-    using Cached = TransformLauncherT<T, N, FWD, TransformCachedTune<T, N>>;
+    using Cached = TransformLauncherT<T, N, FWD, TransformTune<T, N>>;
+    using Large = TransformLauncherT<T, N, FWD, TransformLargeTune<T, N>>;
     static hipError_t launch(const TransformArgs &a)
     {
-        constexpr long long most = kTransformCachedBytes / (2LL * N * N * N * (long long)sizeof(T));
-        return a.num_elems <= most ? Cached::launch(a) : Plain::launch(a);
+        constexpr long long most = TransformLargeTune<T, N>::FROM / (2LL * N * N * N * (long long)sizeof(T));
+        return a.num_elems <= most ? Cached::launch(a) : Large::launch(a);
     }
     static hipError_t prepare()
     {
-        const hipError_t rc = Plain::prepare();
-        return rc != hipSuccess ? rc : Cached::prepare();
+        const hipError_t rc = Cached::prepare();
+        return rc != hipSuccess ? rc : Large::prepare();
     }
 };
 

@@ -1,0 +1,65 @@
+"""The separable form and the transform halves on both sides of the batch size where their launch
+settings change: a batch's results are the same bits as those of its parts (every setting adds in the
+same order), and its last elements agree with the CPU oracle (ragged last workgroups)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TOL, dev
+from paper_2604_19906_amd import tpo
+from paper_2604_19906_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    yield
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
+
+
+def field(dtype, n, mb, seed):
+    word, dt = (8, torch.float64) if dtype == "f64" else (4, torch.float32)
+    most = (mb << 20) // (2 * n ** 3 * word)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.empty((most + 3, n, n, n), dtype=dt, device="cuda").uniform_(-1, 1, generator=g)
+    w = wl.custom(n, most + 3, dtype, key=1800 + n)
+    return most, u, w, [dev(m) for m in wl.direction_matrices(w)]
+
+
+h = lambda t: t.cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype,n", [("f64", 3), ("f64", 5), ("f64", 6), ("f64", 9), ("f32", 3),
+                                     ("f32", 4), ("f32", 5), ("f32", 6)])
+def test_sep(dtype, n):
+    most, u, w, s = field(dtype, n, 256, n)
+    lam = [dev(x.astype(w.np_dtype)) for x in wl.eigenvalues(w)]
+    mu = torch.rand(most + 3, dtype=u.dtype, device="cuda")
+    print(f"case sep {dtype} n={n} E={most + 3}", flush=True)
+    large = tpo.apply_sep_tensors(u, *s, *lam, mu, v=torch.full_like(u, float("nan")))
+    for e in (most, 1, 26, 401):
+        part = tpo.apply_sep_tensors(u[:e], *s, *lam, mu[:e])
+        torch.cuda.synchronize()
+        assert torch.equal(part, large[:e])
+    ref = oracle.ihelm_apply_sep(h(u[-50:]), *map(h, s), *map(h, lam), h(mu[-50:]))
+    assert oracle.max_rel_err_per_element(h(large[-50:]), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,n,mb", [("f64", 3, 256), ("f64", 4, 256), ("f64", 7, 1024), ("f64", 9, 256),
+                                        ("f64", 10, 1024), ("f64", 12, 256), ("f64", 13, 256),
+                                        ("f32", 3, 256), ("f32", 5, 256)])
+def test_transform(dtype, n, mb):
+    most, u, w, s = field(dtype, n, mb, 50 + n)
+    print(f"case transform {dtype} n={n} E={most + 3}", flush=True)
+    for direction, fn in ((tpo.TPO_FORWARD, oracle.forward), (tpo.TPO_BACKWARD, oracle.backward)):
+        large = tpo.transform_tensors(u, *s, direction, t=torch.full_like(u, float("nan")))
+        for e in (most, 1, 26, 401):
+            part = tpo.transform_tensors(u[:e], *s, direction)
+            torch.cuda.synchronize()
+            assert torch.equal(part, large[:e])
+        ref = fn(h(u[-50:]), *map(h, s))
+        assert oracle.max_rel_err_per_element(h(large[-50:]), ref) <= TOL[dtype]
