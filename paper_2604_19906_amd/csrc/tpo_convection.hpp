@@ -83,7 +83,8 @@ constexpr int convection_group()
 // SPLIT: the third term's axis-l and axis-m products run after the first two terms have been
 // merged, in the LDS cube that merge frees: two cubes per unit instead of three (more
 // workgroups per CU) for two more barriers.
-template <typename T, int N, int G, int HINT, bool XCD, bool SPLIT = false>
+// LOADS_FIRST: see the loads.
+template <typename T, int N, int G, int HINT, bool XCD, bool SPLIT, bool LOADS_FIRST>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
 convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const T *Dm_,
                          const T *Im_, T *__restrict__ F, long long num_elems)
@@ -116,23 +117,30 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     T *c2 = SPLIT ? c1 : c1 + CUBE;
 
     T x[N], y[N], z[N];
-    T x2[N];                     // SPLIT: M.P2 of the lane's (n,m) pencil, kept for later
+    T xd[3][N];                  // M.P of the lane's (n,m) pencil; SPLIT keeps the third for later
+    // LOADS_FIRST: all four long loads go out before anything waits for one of them (the fence keeps the
+    // third one, whose use is far below, from sinking).  It takes 14 .. 28 registers more per lane.
 
     // axis l: lane (n,m) = (hi,lo) owns the n consecutive words [e][n][m][0..N-1] of M and P
     if (on) {
         T mq[N];
         load_words<(HINT & 1) != 0>(Mq + (size_t)e * QC + (size_t)(p * N), mq);
+        auto load_p = [&](int dir) {
+            const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
+            load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), xd[dir]);
+        };
+        if constexpr (LOADS_FIRST) {
+#pragma unroll
+            for (int dir = 0; dir < 3; ++dir) load_p(dir);
+        }
 #pragma unroll
         for (int dir = 0; dir < 3; ++dir) {
-            const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
-            load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), x);
+            if constexpr (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+            else load_p(dir);
 #pragma unroll
-            for (int l = 0; l < N; ++l) x[l] *= mq[l];
-            if (SPLIT && dir == 2) {
-#pragma unroll
-                for (int l = 0; l < N; ++l) x2[l] = x[l];
-            } else {
-                mode_product<T, N, false>(dir == 0 ? Dm : Im, x, y);
+            for (int l = 0; l < N; ++l) xd[dir][l] *= mq[l];
+            if (!(SPLIT && dir == 2)) {
+                mode_product<T, N, false>(dir == 0 ? Dm : Im, xd[dir], y);
                 T *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
 #pragma unroll
                 for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
@@ -155,7 +163,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     if constexpr (SPLIT) {
         __syncthreads();                      // every lane has read its pencils of cube 1
         if (on) {                             // axis l of the third term: lane (n,m)
-            mode_product<T, N, false>(Im, x2, y);
+            mode_product<T, N, false>(Im, xd[2], y);
 #pragma unroll
             for (int i = 0; i < N; ++i) c2[hi * PA + lo * PB + i] = y[i];
         }
@@ -188,7 +196,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 // (tpo_pencil_mm.hpp): same data movement; the coefficient tables of D and I (both used
 // untransposed) stay in registers for the whole kernel.  The matrix instructions run on whole
 // wavefronts, outside the `on` branches (their broadcast coefficients come from active lanes
-// only); idle lanes carry zeros or stale LDS words and never store.
+// only).
 template <int N, int G, int HINT, bool XCD, bool SPLIT = false>
 __global__ void __launch_bounds__((PencilShape<float, N, G>::NT))
 convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
@@ -206,59 +214,69 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int g = tid / P;
-    const int p = tid - g * P;
-    const int hi = p / N;
-    const int lo = p - hi * N;
     const long long units = 3 * num_elems;
     const long long nbatch = (units + G - 1) / G;
     const long long batch = convection_batch<XCD>();
     if (XCD && batch >= nbatch) return;
+    constexpr bool LOADS_FIRST = N >= 13;         // see below
+    // Lanes without a pencil never write; with LOADS_FIRST they read pencil 0 of the workgroup's first
+    // unit (there is one), else the global loads leave them out.
+    const int g_ = tid / P;
+    const bool on = (tid < G * P) && (batch * G + g_ < units);
+    const int g = on || !LOADS_FIRST ? g_ : 0;
+    const int p = on || !LOADS_FIRST ? tid - g_ * P : 0;
+    const int hi = p / N;
+    const int lo = p - hi * N;
     const long long unit = batch * G + g;
-    const bool on = (tid < G * P) && (unit < units);
-    const long long e = on ? unit / 3 : 0;
-    const int c = on ? (int)(unit - 3 * e) : 0;
+    const long long e = on || LOADS_FIRST ? unit / 3 : 0;
+    const int c = on || LOADS_FIRST ? (int)(unit - 3 * e) : 0;
     constexpr size_t QC = (size_t)N * N * N;
 
-    // Lanes past the last pencil read (never write) slot 0; p < P keeps them inside the cube.
-    float *c0 = lds + (size_t)(g < G ? g : 0) * (SPLIT ? 2 : 3) * CUBE;
+    float *c0 = lds + (size_t)(g < G ? g : 0) * (SPLIT ? 2 : 3) * CUBE;   // p < P: inside the cube
     float *c1 = c0 + CUBE;
     float *c2 = SPLIT ? c1 : c1 + CUBE;
 
     float tab_d[MS::NTAB], tab_i[MS::NTAB];
-#pragma unroll
-    for (int t = 0; t < MS::NTAB; ++t) {
-        tab_d[t] = mm_coef<N>(Dm, false, t, lane);
-        tab_i[t] = mm_coef<N>(Im, false, t, lane);
-    }
-
     float x[N], y[NY], z[NY], mq[N];
-    float x2[N];                 // SPLIT: M.P2 of the lane's (n,m) pencil, kept for later
+    float xd[3][N];              // M.P of the lane's (n,m) pencil; SPLIT keeps the third for later
+    auto load_tables = [&]() {
+#pragma unroll
+        for (int t = 0; t < MS::NTAB; ++t) {
+            tab_d[t] = mm_coef<N>(Dm, false, t, lane);
+            tab_i[t] = mm_coef<N>(Im, false, t, lane);
+        }
+    };
+    // From n = 13 on all four long loads go out before the tables and before anything waits for one of
+    // them; below, the registers they hold cost more than the wait.  At 3 GB, first against last:
+    // n = 13 617 / 651 us, 14 726 / 768, 16 606 / 633; n = 12 614 / 588, 11 636 / 565, 9 605 / 542.
+    // The branch on `on` is what keeps the compiler from moving the loads of the others up.
+    auto load_field = [&](const float *f, float (&w)[N]) {
+        if (LOADS_FIRST || on) {
+            load_words<(HINT & 1) != 0>(f + (size_t)e * QC + (size_t)(p * N), w);
+        } else {
+#pragma unroll
+            for (int l = 0; l < N; ++l) w[l] = 0.0f;
+        }
+    };
+    auto load_p = [&](int dir) { load_field(Pq + (size_t)(c * 3 + dir) * (size_t)num_elems * QC, xd[dir]); };
 
     // axis l: lane (n,m) = (hi,lo)
-    if (on) {
-        load_words<(HINT & 1) != 0>(Mq + (size_t)e * QC + (size_t)(p * N), mq);
-    } else {
+    if constexpr (!LOADS_FIRST) load_tables();
+    load_field(Mq, mq);
+    if constexpr (LOADS_FIRST) {
 #pragma unroll
-        for (int l = 0; l < N; ++l) mq[l] = 0.0f;
+        for (int dir = 0; dir < 3; ++dir) load_p(dir);
+        __builtin_amdgcn_sched_barrier(0);
+        load_tables();
     }
 #pragma unroll
     for (int dir = 0; dir < 3; ++dir) {
-        if (on) {
-            const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
-            load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), x);
-        } else {
+        if constexpr (!LOADS_FIRST) load_p(dir);
 #pragma unroll
-            for (int l = 0; l < N; ++l) x[l] = 0.0f;
-        }
-#pragma unroll
-        for (int l = 0; l < N; ++l) x[l] *= mq[l];
-        if (SPLIT && dir == 2) {
-#pragma unroll
-            for (int l = 0; l < N; ++l) x2[l] = x[l];
-        } else {
-            if (dir == 0) mode_product_mm<N, false>(tab_d, Dc, x, y);
-            else mode_product_mm<N, false>(tab_i, Ic, x, y);
+        for (int l = 0; l < N; ++l) xd[dir][l] *= mq[l];
+        if (!(SPLIT && dir == 2)) {
+            if (dir == 0) mode_product_mm<N, false>(tab_d, Dc, xd[dir], y);
+            else mode_product_mm<N, false>(tab_i, Ic, xd[dir], y);
             float *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
             if (on) {
 #pragma unroll
@@ -281,7 +299,7 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
     }
     if constexpr (SPLIT) {
         __syncthreads();                      // every lane has read its pencils of cube 1
-        mode_product_mm<N, false>(tab_i, Ic, x2, y);       // axis l of the third term: lane (n,m)
+        mode_product_mm<N, false>(tab_i, Ic, xd[2], y);       // axis l of the third term: lane (n,m)
         if (on) {
 #pragma unroll
             for (int i = 0; i < N; ++i) c2[hi * PA + lo * PB + i] = y[i];
@@ -718,7 +736,7 @@ template <> struct ConvectionLargeTune<float, 3> : ConvectionSet<16, false, fals
 template <> struct ConvectionLargeTune<float, 5> : ConvectionSet<8, false, false> {};
 template <> struct ConvectionLargeTune<float, 11> : ConvectionSet<2, true, true> {};
 
-template <typename T, int N, typename Tune>
+template <typename T, int N, typename Tune, bool LARGE>
 struct ConvectionLauncherT {
     static constexpr int G = Tune::G;
     using Sh = PencilShape<T, N, G>;
@@ -727,11 +745,16 @@ struct ConvectionLauncherT {
     // share cache lines).
     static constexpr int HINT = 2;
     static constexpr bool XCD = G % 3 != 0;    // with G a multiple of 3 an element stays in one workgroup
+    // fp64 on batches past the last-level cache (3 GB, with / without: n = 11 527 / 551 us, 12 569 / 582,
+    // 13 584 / 622, 14 632 / 672, 15 716 / 772, 16 703 / 750; n = 10 524 / 521, 9 544 / 534, 8 529 / 527,
+    // 6 527 / 519), where the wait for memory outweighs the registers; cached ones lose 2 to 9 %
+    // (n = 11, 150 MB: 38.4 / 35.2).
+    static constexpr bool LOADS_FIRST = LARGE && sizeof(T) == 8 && N >= 11;
 
     static constexpr auto kernel()
     {
         if constexpr (Tune::MM) return &convection_mm_kernel<N, G, HINT, XCD, Tune::SPLIT>;
-        else return &convection_pencil_kernel<T, N, G, HINT, XCD, Tune::SPLIT>;
+        else return &convection_pencil_kernel<T, N, G, HINT, XCD, Tune::SPLIT, LOADS_FIRST>;
     }
 
     static hipError_t launch(const ConvectionArgs &a)
@@ -755,8 +778,8 @@ struct ConvectionLauncherT {
 
 template <typename T, int N>
 struct ConvectionLauncher {
-    using Cached = ConvectionLauncherT<T, N, ConvectionTune<T, N>>;
-    using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>>;
+    using Cached = ConvectionLauncherT<T, N, ConvectionTune<T, N>, false>;
+    using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>, true>;
     static hipError_t launch(const ConvectionArgs &a)
     {
         return a.num_elems <= convection_cached_elems<T, N, N>() ? Cached::launch(a) : Large::launch(a);

@@ -12,10 +12,10 @@
 //     acc[r] += Areg[lane 4k + r] * b        r = 0..3
 //
 // which is exactly four FMAs of a pencil product y[4*rg + r] += M[4*rg + r][l] * x[l] with
-// wavefront-uniform coefficients.  One A register holds 16 such coefficient quadruples; the
-// n * ceil(n/4) quadruples of one matrix in one direction fill ceil(n * ceil(n/4) / 16)
-// registers (4 for n = 13), built once per workgroup from the matrix in global memory.
-// Rows n .. 4*ceil(n/4)-1 have zero coefficients; the padding costs 16/13 at n = 13.
+// wavefront-uniform coefficients.  One A register holds 16 such coefficient quadruples, the row
+// groups of an input index (their number rounded up to a power of two) next to each other: n = 13
+// takes four registers per matrix and direction, built once per workgroup from the matrix in global
+// memory.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -34,26 +34,29 @@ struct MmShape {
     static constexpr bool REM_VALU = (N % 4 == 1) && (N > 1);
     static constexpr int RG = REM_VALU ? N / 4 : (N + 3) / 4;   // row groups of 4 output rows
     static constexpr int NY = REM_VALU ? N : 4 * RG;            // outputs per pencil (>= N)
-    static constexpr int SLOTS = N * RG;              // coefficient quadruples per table
-    static constexpr int NTAB = (SLOTS + 15) / 16;    // A registers per table
+    static constexpr int SLOTS = N * RG;              // coefficient quadruples in use per table
+    static constexpr int RGP = RG > 2 ? 4 : RG;       // quadruples an input index takes up
+    static constexpr int NTAB = (N * RGP + 15) / 16;  // A registers per table
     static constexpr size_t TAB_LDS_BYTES = (size_t)5 * NTAB * 64 * sizeof(float);
 };
 
-// Coefficient tables.  Slot s = l*RG + rg of a table sits in register s/16, lanes 4*(s%16) .. +3;
-// lane r of the quadruple holds the coefficient of output row 4*rg + r and input index l:
-// S[l][row] forward (transpose applied), S[row][l] backward.  mm_coef is the value of register t
-// in lane `lane`.
+// Coefficient tables.  Register t, lane L of a table holds the coefficient of output row L % (4 RGP)
+// and input index l = (16 / RGP) t + L / (4 RGP): S[l][row] forward (transpose applied), S[row][l]
+// backward; the quadruple of row group rg and input l is number RGP l + rg.  Rows past the matrix repeat
+// its last row (their results are never used) and input indices past it some entry (never multiplied),
+// so the only index arithmetic is one lane offset per direction; the registers are constant distances
+// apart.  Dense packing (RG instead of RGP) needs a division and masks per register: 109 instead of 60
+// vector instructions in the prologue of the n = 13 kernel below, of 590 in all.  Us
+// per call, dense / this, with the load orders of the kernels: inverse Helmholtz at 3 GB n = 11 598 / 561, 12
+// 588 / 583, 13 592 / 584, at 150 MB 31.4 / 27.2, 30.7 / 29.6, 32.4 / 30.2; separable form n = 13 823 / 802.
 template <int N>
 __device__ __forceinline__ float mm_coef(const float *__restrict__ S, bool fwd, int t, int lane)
 {
-    using M = MmShape<N>;
-    const int s = 16 * t + (lane >> 2);
-    const int l = s / M::RG;
-    const int row = 4 * (s - l * M::RG) + (lane & 3);
-    const bool ok = (l < N) && (row < N);
-    const int idx = ok ? (fwd ? l * N + row : row * N + l) : 0;
-    const float c = S[idx];
-    return ok ? c : 0.0f;
+    constexpr int ROWS = 4 * MmShape<N>::RGP, LPT = 64 / ROWS;      // rows, input indices per register
+    const int row = (lane % ROWS) < N ? lane % ROWS : N - 1, q = lane / ROWS;
+    int idx = fwd ? q * N + row + LPT * t * N : row * N + q + LPT * t;
+    if (N % LPT != 0) idx = idx < N * N - 1 ? idx : N * N - 1;
+    return S[idx];
 }
 // The six tables in the order the kernel uses them: x, y, z forward, then z, y, x backward.
 // Table 0 is loaded straight into registers by every wavefront; tables 1..5 are built once per
@@ -102,13 +105,13 @@ template <int N, int I>
 __device__ __forceinline__ void mm_step(const float (&tab)[MmShape<N>::NTAB], const float (&x)[N],
                                         mm_f4 (&acc)[MmShape<N>::RG])
 {
-    constexpr int RG = MmShape<N>::RG;
-    constexpr int L = I / RG, R = I % RG;
+    constexpr int RG = MmShape<N>::RG, RGP = MmShape<N>::RGP;
+    constexpr int L = I / RG, R = I % RG, Q = RGP * L + R;
     if constexpr (L == 0) {
         const mm_f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-        acc[R] = __builtin_amdgcn_mfma_f32_4x4x1f32(tab[I / 16], x[L], zero, 4, I % 16, 0);
+        acc[R] = __builtin_amdgcn_mfma_f32_4x4x1f32(tab[Q / 16], x[L], zero, 4, Q % 16, 0);
     } else {
-        acc[R] = __builtin_amdgcn_mfma_f32_4x4x1f32(tab[I / 16], x[L], acc[R], 4, I % 16, 0);
+        acc[R] = __builtin_amdgcn_mfma_f32_4x4x1f32(tab[Q / 16], x[L], acc[R], 4, Q % 16, 0);
     }
 }
 template <int N, int... I>
@@ -119,7 +122,7 @@ __device__ __forceinline__ void mm_steps(const float (&tab)[MmShape<N>::NTAB], c
     (mm_step<N, I>(tab, x, acc), ...);
 }
 
-// y[row] = sum_l coef(row, l) * x[l] for the lane's pencil; rows >= N of y (if any) are 0.
+// y[row] = sum_l coef(row, l) * x[l] for the lane's pencil; rows >= N of y (if any) repeat row N-1.
 // S is the matrix itself, read through the constant address space for the left-over row.
 template <int N, bool FWD>
 __device__ __forceinline__ void mode_product_mm(const float (&tab)[MmShape<N>::NTAB],
@@ -207,11 +210,21 @@ ihelm_pencil_mm_kernel(const float *u, const float *__restrict__ Sx, const float
     float sep_ab = 1.0f, sep_mu = 0.0f;   // lam_x[a] + lam_y[b] of the lane's axis-2 pencil, mu[e]
 
     // forward, axis 0: lane (b,c) = (hi,lo)
+    // From n = 12 on u_e is asked for before the first table: the table's few loads used to come first
+    // and held the long ones up (n = 13, 4 GB: 765 against 783 us per call; n = 8 .. 11 no difference).
+    constexpr bool U_FIRST = N >= 12;
+    auto load_table = [&]() {
 #pragma unroll
-    for (int t = 0; t < M::NTAB; ++t) tab[t] = mm_coef<N>(Sx, true, t, lane);
+        for (int t = 0; t < M::NTAB; ++t) tab[t] = mm_coef<N>(Sx, true, t, lane);
+    };
+    if constexpr (!U_FIRST) load_table();
 #pragma unroll
     for (int l = 0; l < N; ++l)
         x[l] = gload<(HINT & 1) != 0>(reinterpret_cast<const float *>(ub + off_bc + (l - MID) * P * 4));
+    if constexpr (U_FIRST) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_table();
+    }
     if constexpr (SEP != 0) {
         sep_ab = lam_x[hi] + lam_y[lo];
         sep_mu = mu[e];

@@ -2,7 +2,7 @@
 fit the last-level cache or not): every element against plain fp64 products on the device, the last
 elements against the CPU oracle, ragged last workgroups.  Both settings add in the same order, so a
 batch's results are the same bits as those of its parts.  One shape per kind of setting: other units
-per workgroup, lanes numbered per phase, SPLIT, the 4x4x1 form."""
+per workgroup, lanes numbered per phase, SPLIT, the 4x4x1 form, all loads first."""
 import numpy as np
 import pytest
 import torch
@@ -24,8 +24,8 @@ def library():
 
 
 SHAPES = [("f64", 3, 3), ("f64", 9, 9), ("f64", 7, 7), ("f64", 10, 10), ("f64", 2, 4), ("f64", 4, 5),
-          ("f64", 7, 11), ("f64", 8, 12), ("f64", 9, 14), ("f64", 11, 12), ("f32", 3, 3), ("f32", 5, 5),
-          ("f32", 7, 7), ("f32", 11, 11), ("f32", 2, 3), ("f32", 6, 9), ("f32", 8, 12), ("f32", 10, 12),
+          ("f64", 7, 11), ("f64", 8, 12), ("f64", 9, 14), ("f64", 11, 12), ("f64", 11, 11), ("f64", 16, 16), ("f32", 3, 3), ("f32", 5, 5),
+          ("f32", 7, 7), ("f32", 11, 11), ("f32", 13, 13), ("f32", 2, 3), ("f32", 6, 9), ("f32", 8, 12), ("f32", 10, 12),
           ("f32", 11, 13), ("f32", 12, 14)]
 
 
