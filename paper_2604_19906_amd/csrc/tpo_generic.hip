@@ -242,3 +242,16 @@ hipError_t launch_ihelm_generic(const AnisoArgs &a, int dtype)
 }
 
 }  // namespace tpo
+
+extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype, long long num_elems)
+{
+    if (dtype != TPO_F32) return 0;
+    tpo::AnisoArgs a = {};
+    a.nx = nx;
+    a.ny = ny;
+    a.nz = nz;
+    int g, nt;
+    size_t lds;
+    tpo::aniso_shape<float>(a, g, nt, lds);
+    return tpo::slice_kernel_pays(nx, ny, nz, num_elems, g, nt / 64);
+}

@@ -77,6 +77,7 @@ hipError_t launch_ihelm_generic(const AnisoArgs &a, int dtype);
 // elements and wavefronts per workgroup; its launcher (only for calls for which it is).
 bool slice_kernel_pays(int nx, int ny, int nz, long long num_elems, int elems_per_wg, int waves_per_wg);
 hipError_t launch_ihelm_slice(const AnisoArgs &a);
+bool slice_class_built(int nx, int ksb, int ksc);
 
 // dtype index: 0 = f64, 1 = f32.  n in 1..TPO_MAX_N.  Returns nullptr when the family has
 // no kernel for that shape.
@@ -101,3 +102,8 @@ int validate_apply_sep(const void *u, const void *sx, const void *sy, const void
                        const void *v, int n, long long num_elems, int dtype, int variant);
 
 }  // namespace tpo
+
+// For the tests (no GPU needed): whether tpo_ihelm_apply_aniso takes the slice kernel for this call, and
+// whether the slice kernel is built for a class of shapes.
+extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype, long long num_elems);
+extern "C" int tpo_internal_slice_class_built(int nx, int ksb, int ksc);
