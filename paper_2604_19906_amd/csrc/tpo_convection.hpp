@@ -117,33 +117,54 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     T *c2 = SPLIT ? c1 : c1 + CUBE;
 
     T x[N], y[N], z[N];
-    T xd[3][N];                  // M.P of the lane's (n,m) pencil; SPLIT keeps the third for later
-    // LOADS_FIRST: all four long loads go out before anything waits for one of them (the fence keeps the
-    // third one, whose use is far below, from sinking).  It takes 14 .. 28 registers more per lane.
+    T x2[N];                     // SPLIT: M.P2 of the lane's (n,m) pencil, kept for later
+    static_assert(SPLIT || !LOADS_FIRST, "the third load waits where SPLIT keeps the third term");
 
     // axis l: lane (n,m) = (hi,lo) owns the n consecutive words [e][n][m][0..N-1] of M and P
     if (on) {
         T mq[N];
         load_words<(HINT & 1) != 0>(Mq + (size_t)e * QC + (size_t)(p * N), mq);
-        auto load_p = [&](int dir) {
-            const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
-            load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), xd[dir]);
-        };
         if constexpr (LOADS_FIRST) {
+            // All four long loads go out before anything waits for one of them (the fences keep the third
+            // one, whose use is far below, from sinking).  It takes 17 .. 30 registers more per lane.
+            T x1[N];
+            auto load_p = [&](int dir, T (&w)[N]) {
+                const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
+                load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), w);
+            };
+            auto product = [&](const TPO_CONSTANT T *S, T (&w)[N], T *dst) {
 #pragma unroll
-            for (int dir = 0; dir < 3; ++dir) load_p(dir);
-        }
-#pragma unroll
-        for (int dir = 0; dir < 3; ++dir) {
-            if constexpr (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
-            else load_p(dir);
-#pragma unroll
-            for (int l = 0; l < N; ++l) xd[dir][l] *= mq[l];
-            if (!(SPLIT && dir == 2)) {
-                mode_product<T, N, false>(dir == 0 ? Dm : Im, xd[dir], y);
-                T *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
+                for (int l = 0; l < N; ++l) w[l] *= mq[l];
+                mode_product<T, N, false>(S, w, y);
 #pragma unroll
                 for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
+            };
+            load_p(0, x);
+            load_p(1, x1);
+            load_p(2, x2);
+            __builtin_amdgcn_sched_barrier(0);
+            product(Dm, x, c0);
+            __builtin_amdgcn_sched_barrier(0);
+            product(Im, x1, c1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int l = 0; l < N; ++l) x2[l] *= mq[l];
+        } else {
+#pragma unroll
+            for (int dir = 0; dir < 3; ++dir) {
+                const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
+                load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), x);
+#pragma unroll
+                for (int l = 0; l < N; ++l) x[l] *= mq[l];
+                if (SPLIT && dir == 2) {
+#pragma unroll
+                    for (int l = 0; l < N; ++l) x2[l] = x[l];
+                } else {
+                    mode_product<T, N, false>(dir == 0 ? Dm : Im, x, y);
+                    T *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
+#pragma unroll
+                    for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
+                }
             }
         }
     }
@@ -163,7 +184,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     if constexpr (SPLIT) {
         __syncthreads();                      // every lane has read its pencils of cube 1
         if (on) {                             // axis l of the third term: lane (n,m)
-            mode_product<T, N, false>(Im, xd[2], y);
+            mode_product<T, N, false>(Im, x2, y);
 #pragma unroll
             for (int i = 0; i < N; ++i) c2[hi * PA + lo * PB + i] = y[i];
         }
