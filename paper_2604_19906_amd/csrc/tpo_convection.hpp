@@ -664,12 +664,11 @@ constexpr ConvRectRow convection_rect_row(int nv, int nq)
 }
 
 constexpr long long kConvectionCachedBytes = 256LL << 20;
-// Elements whose ten input and three output cubes fill the last-level cache.
+// Elements whose ten input and three output cubes take up `bytes`.
 template <typename T, int NV, int NQ>
-constexpr long long convection_cached_elems()
+constexpr long long convection_elems(long long bytes)
 {
-    return kConvectionCachedBytes
-           / ((10LL * NQ * NQ * NQ + 3LL * NV * NV * NV) * (long long)sizeof(T));
+    return bytes / ((10LL * NQ * NQ * NQ + 3LL * NV * NV * NV) * (long long)sizeof(T));
 }
 
 template <typename T, int NV, int NQ, int G, bool LARGE, bool COMPACT>
@@ -714,7 +713,11 @@ struct ConvectionRectLauncher {
 
     static hipError_t launch(const ConvectionArgs &a)
     {
-        return a.num_elems <= convection_cached_elems<T, NV, NQ>() ? Cached::launch(a) : Large::launch(a);
+        return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
+    }
+    static bool takes_large(long long num_elems)
+    {
+        return num_elems > convection_elems<T, NV, NQ>(kConvectionCachedBytes);
     }
     static hipError_t prepare()
     {
@@ -729,7 +732,8 @@ struct ConvectionRectEntry {
 };
 #define TPO_CONVECTION_RECT_ENTRY(T, NV, NQ)                                              \
     ConvectionRectEntry { NV, NQ, ConvectionEntry { &ConvectionRectLauncher<T, NV, NQ>::launch, \
-                                                    &ConvectionRectLauncher<T, NV, NQ>::prepare } }
+                                                    &ConvectionRectLauncher<T, NV, NQ>::prepare, \
+                                                    &ConvectionRectLauncher<T, NV, NQ>::takes_large } }
 
 // Square shapes: units per workgroup by lane utilisation, SPLIT by size, and in fp32 from n = 9 on
 // the 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there, as for the
@@ -766,7 +770,7 @@ struct ConvectionLauncherT {
     // share cache lines).
     static constexpr int HINT = 2;
     static constexpr bool XCD = G % 3 != 0;    // with G a multiple of 3 an element stays in one workgroup
-    // fp64 on batches past the last-level cache (3 GB, with / without: n = 11 527 / 551 us, 12 569 / 582,
+    // fp64 on large batches (3 GB, with / without: n = 11 527 / 551 us, 12 569 / 582,
     // 13 584 / 622, 14 632 / 672, 15 716 / 772, 16 703 / 750; n = 10 524 / 521, 9 544 / 534, 8 529 / 527,
     // 6 527 / 519), where the wait for memory outweighs the registers; cached ones lose 2 to 9 %
     // (n = 11, 150 MB: 38.4 / 35.2).
@@ -803,7 +807,14 @@ struct ConvectionLauncher {
     using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>, true>;
     static hipError_t launch(const ConvectionArgs &a)
     {
-        return a.num_elems <= convection_cached_elems<T, N, N>() ? Cached::launch(a) : Large::launch(a);
+        return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
+    }
+    // All loads first at n = 11, 12 costs until the fields are some times the cache (275 .. 430 MB: n = 11 1.02
+    // .. 1.09 of the time, n = 12 0.99 .. 1.02; 600 MB 1.00, 0.99; 1.2 GB 0.96, 0.97).
+    static bool takes_large(long long num_elems)
+    {
+        constexpr bool late = sizeof(T) == 8 && (N == 11 || N == 12);
+        return num_elems > convection_elems<T, N, N>(late ? 1LL << 30 : kConvectionCachedBytes);
     }
     static hipError_t prepare()
     {
@@ -813,6 +824,7 @@ struct ConvectionLauncher {
 };
 
 #define TPO_CONVECTION_ENTRY(T, N) \
-    ConvectionEntry { &ConvectionLauncher<T, N>::launch, &ConvectionLauncher<T, N>::prepare }
+    ConvectionEntry { &ConvectionLauncher<T, N>::launch, &ConvectionLauncher<T, N>::prepare, \
+                      &ConvectionLauncher<T, N>::takes_large }
 
 }  // namespace tpo

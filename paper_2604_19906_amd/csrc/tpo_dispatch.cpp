@@ -58,3 +58,9 @@ const TransformEntry *transform_entry(int n, int dtype)
 }
 
 }  // namespace tpo
+
+extern "C" int tpo_internal_convection_setting(int n_v, int n_q, int dtype, long long num_elems)
+{
+    const tpo::ConvectionEntry *k = tpo::convection_entry(n_v, n_q, dtype);
+    return k ? k->takes_large(num_elems) : -1;
+}

@@ -58,6 +58,7 @@ struct ConvectionArgs {
 struct ConvectionEntry {
     hipError_t (*launch)(const ConvectionArgs &);
     hipError_t (*prepare)();
+    bool (*takes_large)(long long num_elems);      // which of the two settings a batch gets
 };
 // n_v == n_q: every n in 1..TPO_MAX_N; n_v != n_q: the instantiated over-integration shapes.
 const ConvectionEntry *convection_entry(int n_v, int n_q, int dtype);
@@ -103,7 +104,9 @@ int validate_apply_sep(const void *u, const void *sx, const void *sy, const void
 
 }  // namespace tpo
 
-// For the tests (no GPU needed): whether tpo_ihelm_apply_aniso takes the slice kernel for this call, and
-// whether the slice kernel is built for a class of shapes.
+// For the tests (no GPU needed): whether tpo_ihelm_apply_aniso takes the slice kernel for this call, whether
+// the slice kernel is built for a class of shapes, and which of its settings tpo_convection_apply takes for
+// this batch (0 / 1; -1: no such shape).
 extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype, long long num_elems);
 extern "C" int tpo_internal_slice_class_built(int nx, int ksb, int ksc);
+extern "C" int tpo_internal_convection_setting(int n_v, int n_q, int dtype, long long num_elems);
