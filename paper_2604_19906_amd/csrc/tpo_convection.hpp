@@ -627,32 +627,34 @@ constexpr int convection_rect_group()
     return best;
 }
 
-// Batches whose fields stay in the last-level cache (256 MB) take the utilisation rule's group and the
-// first form, larger ones the second form where a row below pays (1 % or more): the best of a sweep on MI355X over {1, 2,
-// 3, 4, 6, 8, 12} units, the rule's group and both lane numberings, 2 GB per call.  us per call on 2.5
-// GB, before / now: fp64 (5,8) 536 / 493, (6,9) 517 / 479, (8,10) 523 / 441, (8,12) 515 / 486, (10,12)
-// 529 / 472, (11,12) 648 / 479; fp32 (3,4) 492 / 454, (10,12) 527 / 498, (11,13) 546 / 510, (9,14) 517 /
-// 473.
-// `always`: the row also wins (or ties) on small batches, mostly because it takes the smaller
-// workgroups of the two (150 MB: fp64 (8,10) 31.3 / 25.9, (11,12) 45.9 / 33.6); larger groups lose
-// there, where a launch is a few rounds of workgroups (2 MB: fp64 (6,8) 3.8 / 5.9, (7,11) 5.6 / 7.2).
-struct ConvRectRow { int nv, nq, g, compact, always; };
+// The utilisation rule's group and the first form, or the second form with a row's settings: the best of a
+// sweep on MI355X over {1, 2, 3, 4, 6, 8, 12} units, the rule's group and both lane numberings, 2 GB per
+// call, kept where it gains 2 % or more.  us per call on 2.5 GB, rule / row: fp64 (5,8) 536 / 493, (6,9)
+// 517 / 479, (8,10) 523 / 441, (8,12) 515 / 486, (10,12) 529 / 472, (11,12) 648 / 479; fp32 (3,4) 492 / 454,
+// (10,12) 527 / 498, (11,13) 546 / 510, (9,14) 517 / 473.
+// `from`: MiB of fields from which the row is the faster one.
+//   0: on small batches too, mostly because it takes the smaller workgroups of the two (150 MB: fp64 (8,10) 31.3 /
+//   25.9, (11,12) 45.9 / 33.6).  Larger groups lose there, where a launch is a few rounds of workgroups (2 MB:
+//   fp64 (6,8) 3.8 / 5.9, (7,11) 5.6 / 7.2).
+//   256: once the fields pass the last-level cache.
+//   320: up to there the fields are cached in part and the smaller workgroups lead (row over rule at 275 .. 310 MB:
+//   fp64 (6,8) 1.05, (7,8) 1.05, (7,9) 1.06, (9,11) 1.06; fp32 (2,3) 1.02 .. 1.10, (3,4) 1.02 .. 1.05).
+//   26: fp32 (6,9) 0.95 .. 0.98 up to 300 MB; below 1.05 .. 1.12 at 11 .. 16 and 22 .. 24 MB, 0.84 .. 0.98 between.
+struct ConvRectRow { int nv, nq, g, compact, from; };
 template <typename T> struct ConvRectTable;
 template <> struct ConvRectTable<double> {
     static constexpr ConvRectRow row[] = {
-        {2, 4, 6, 1, 0},   {3, 4, 6, 0, 0},   {4, 5, 12, 1, 0},  {5, 7, 8, 1, 0},   {5, 8, 4, 0, 0},
-        {6, 7, 9, 0, 0},   {6, 8, 8, 1, 0},   {6, 9, 6, 0, 0},   {7, 8, 8, 0, 0},   {7, 9, 6, 0, 0},
-        {7, 11, 4, 1, 0},  {8, 9, 3, 0, 0},   {8, 10, 1, 0, 1},  {8, 12, 3, 1, 0},  {9, 10, 1, 0, 1},
-        {9, 11, 2, 0, 0},  {9, 14, 2, 1, 1},  {10, 12, 1, 0, 1}, {11, 12, 1, 0, 1}, {12, 13, 1, 0, 0},
-        {12, 14, 1, 0, 0},
+        {2, 4, 6, 1, 256},   {3, 4, 6, 0, 256}, {5, 8, 4, 0, 256},  {6, 7, 9, 0, 256},  {6, 8, 8, 1, 320},
+        {6, 9, 6, 0, 256},   {7, 8, 8, 0, 320}, {7, 9, 6, 0, 320},  {7, 11, 4, 1, 256}, {8, 9, 3, 0, 256},
+        {8, 10, 1, 0, 0},    {8, 12, 3, 1, 256}, {9, 10, 1, 0, 0},  {9, 11, 2, 0, 320}, {9, 14, 2, 1, 0},
+        {10, 12, 1, 0, 0},   {11, 12, 1, 0, 0},
     };
 };
 template <> struct ConvRectTable<float> {
     static constexpr ConvRectRow row[] = {
-        {2, 3, 12, 1, 0},  {2, 4, 12, 0, 0},  {3, 4, 8, 1, 0},   {3, 5, 8, 1, 0},   {4, 5, 8, 1, 0},
-        {4, 6, 4, 0, 0},   {5, 7, 8, 0, 0},   {5, 8, 6, 0, 0},   {6, 9, 4, 1, 1},   {7, 8, 1, 0, 0},
-        {8, 10, 3, 1, 1},  {8, 12, 2, 1, 1},  {9, 11, 2, 1, 0},  {9, 14, 2, 1, 1},  {10, 11, 2, 1, 0},
-        {10, 12, 2, 1, 0}, {11, 13, 3, 1, 0}, {12, 14, 2, 1, 0},
+        {2, 3, 12, 1, 320},  {2, 4, 12, 0, 256},  {3, 4, 8, 1, 320},   {3, 5, 8, 1, 256}, {4, 5, 8, 1, 256},
+        {5, 8, 6, 0, 256},   {6, 9, 4, 1, 26},    {8, 10, 3, 1, 0},    {8, 12, 2, 1, 0},  {9, 11, 2, 1, 256},
+        {9, 14, 2, 1, 0},    {10, 12, 2, 1, 256}, {11, 13, 3, 1, 256}, {12, 14, 2, 1, 256},
     };
 };
 template <typename T>
@@ -706,23 +708,32 @@ struct ConvectionRectLauncherT {
 template <typename T, int NV, int NQ>
 struct ConvectionRectLauncher {
     static constexpr ConvRectRow R = convection_rect_row<T>(NV, NQ);
-    using Rule = ConvectionRectLauncherT<T, NV, NQ, convection_rect_group<T, NV, NQ>(), false, false>;
+    static constexpr int RULE_G = convection_rect_group<T, NV, NQ>();
+    // No batch leaves the row: see takes_large().
+    static constexpr bool ROW_ONLY = R.g != 0 && R.from == 0 && (R.g == 1 || R.g >= RULE_G);
+    using Rule = ConvectionRectLauncherT<T, NV, NQ, RULE_G, false, false>;
     using Row = ConvectionRectLauncherT<T, NV, NQ, R.g != 0 ? R.g : 1, true, R.compact != 0>;
+    using Small = std::conditional_t<ROW_ONLY, Row, Rule>;
     using Large = std::conditional_t<R.g != 0, Row, Rule>;
-    using Cached = std::conditional_t<R.always != 0, Row, Rule>;
 
     static hipError_t launch(const ConvectionArgs &a)
     {
-        return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
+        return takes_large(a.num_elems) ? Large::launch(a) : Small::launch(a);
     }
     static bool takes_large(long long num_elems)
     {
-        return num_elems > convection_elems<T, NV, NQ>(kConvectionCachedBytes);
+        if (ROW_ONLY) return true;
+        if (R.g == 0 || num_elems <= convection_elems<T, NV, NQ>((long long)R.from << 20)) return false;
+        // While the rule's larger workgroups still are one per CU and the row's are not, the rule's lead (row
+        // over rule: fp32 (8,10) 1.03 .. 1.07 at 12 .. 18 MB, (8,12) 1.08 .. 1.10 at 13 .. 19 MB; 0.75 .. 0.90 on both
+        // sides of that).  One unit per workgroup is ahead all the same (fp64 (8,10) 0.92 .. 0.96).
+        constexpr int CUS = 256;
+        return num_elems * 3 <= CUS * R.g || num_elems * 3 > CUS * RULE_G;
     }
     static hipError_t prepare()
     {
         const hipError_t rc = Large::prepare();
-        return rc != hipSuccess ? rc : Cached::prepare();
+        return rc != hipSuccess ? rc : Small::prepare();
     }
 };
 

@@ -26,3 +26,21 @@ def convection_setting():
 def test_convection_f64_loads_first(convection_setting, n, keeps, takes):
     assert convection_setting("f64", n, n, keeps) == 0
     assert convection_setting("f64", n, n, takes) == 1
+
+
+# (dtype, nv, nq), MB of fields on which the utilisation rule's setting leads, on which the table's does
+@pytest.mark.parametrize("dtype,nv,nq,rule,row", [
+    ("f64", 6, 8, (100, 275, 310), (600, 2500)), ("f64", 7, 8, (100, 275, 310), (380, 2500)),
+    ("f64", 7, 9, (100, 275, 310), (380, 2500)), ("f64", 9, 11, (100, 275, 310), (340, 2500)),
+    ("f64", 8, 12, (100, 240), (340, 2500)), ("f64", 12, 14, (1, 300, 2500), ()),
+    ("f64", 8, 10, (), (1, 16, 200, 2500)), ("f64", 11, 12, (), (1, 16, 200, 2500)),
+    ("f32", 2, 3, (100, 275, 310), (430, 2500)), ("f32", 3, 4, (100, 275, 310), (340, 2500)),
+    ("f32", 6, 9, (13, 16, 23), (30, 60, 240)),
+    ("f32", 8, 10, (13, 15, 18), (4, 11, 20, 30, 240, 2500)),
+    ("f32", 8, 12, (14, 16, 18.5), (4, 11, 21, 30, 240, 2500)),
+    ("f32", 9, 14, (), (4, 11, 16, 30, 240, 2500)), ("f32", 7, 8, (1, 300, 2500), ())])
+def test_convection_over_integrated(convection_setting, dtype, nv, nq, rule, row):
+    for mb in rule:
+        assert convection_setting(dtype, nv, nq, mb) == 0, mb
+    for mb in row:
+        assert convection_setting(dtype, nv, nq, mb) == 1, mb
