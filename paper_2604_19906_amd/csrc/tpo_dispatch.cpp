@@ -64,3 +64,9 @@ extern "C" int tpo_internal_convection_setting(int n_v, int n_q, int dtype, long
     const tpo::ConvectionEntry *k = tpo::convection_entry(n_v, n_q, dtype);
     return k ? k->takes_large(num_elems) : -1;
 }
+
+extern "C" int tpo_internal_transform_setting(int n, int dtype, long long num_elems)
+{
+    const tpo::TransformEntry *k = tpo::transform_entry(n, dtype);
+    return k ? k->takes_large(num_elems) : -1;
+}

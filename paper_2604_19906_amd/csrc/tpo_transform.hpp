@@ -184,7 +184,7 @@ template <int GG, int H, bool X, bool M, long long MB = 256> struct TransformSet
     static constexpr bool XCD = X, MM = M;
     static constexpr long long FROM = MB << 20;
 };
-template <> struct TransformTune<float, 12> : TransformSet<3, 0, true, true> {};
+template <> struct TransformTune<float, 12> : TransformSet<3, 2, true, true> {};
 template <> struct TransformTune<float, 13> : TransformSet<3, 0, true, true> {};
 template <> struct TransformTune<float, 14> : TransformSet<2, 0, false, true> {};
 template <> struct TransformTune<float, 15> : TransformSet<2, 0, true, true> {};
@@ -197,8 +197,12 @@ template <> struct TransformTune<float, 11> : TransformSet<2, 0, false, true> {}
 // Beyond: the vector-FMA form for those, and settings from a sweep over 1 .. 32 elements per workgroup
 // x stores x renumbering on 2 GB per call where it found 4 % or more (us per call on 2.5
 // GB, before / now): fp64 n = 3 460 / 434, 4 427 / 384, 7 452 / 427, 9 450 / 433, 10 476 / 439, 12 454 /
-// 435, 13 480 / 450; fp32 n = 3 569 / 531, 5 491 / 450.  (n = 7, 10: only past 1 GB, at 600 MB 101 / 108,
-// 110 / 114.)
+// 435, 13 480 / 450; fp32 n = 3 569 / 531, 5 491 / 450.  Some begin later, in MiB: fp64 n = 7, 10 only past 1 GB
+// (600 MB 101 / 108, 110 / 114), 9 too (340 .. 500 MB 1.01 .. 1.04 of the time), 13 at 512 (275 .. 430 MB 0.99 .. 1.03), 3 at 272
+// (275 MB 1.05 .. 1.08, 290 MB 0.92).
+// fp32 n = 12, matrix-core form: non-temporal stores leave the cache to the input until the fields are well
+// past it (time over the vector-FMA form's with / without, forward: 60 MB 0.78 / 1.02, 100 MB 0.79 / 0.83, 290 MB 0.91 /
+// 1.01 .. 1.07, 380 MB 0.91 / 1.05 .. 1.09, 600 MB 0.91 / 0.94, 1.2 GB 0.97 / 0.92; backward 290 MB 0.80 / 0.98).
 template <typename T, int N> struct TransformLargeTune : TransformTune<T, N> {};
 template <int N> struct TransformVectorTune {
     using Tune = PencilSepTune<float, N>;
@@ -212,13 +216,14 @@ template <> struct TransformLargeTune<float, 10> : TransformVectorTune<10> {};
 template <> struct TransformLargeTune<float, 11> : TransformVectorTune<11> {};
 template <> struct TransformLargeTune<float, 3> : TransformSet<24, 2, false, false> {};
 template <> struct TransformLargeTune<float, 5> : TransformSet<2, 0, true, false> {};
-template <> struct TransformLargeTune<double, 3> : TransformSet<24, 0, true, false> {};
+template <> struct TransformLargeTune<float, 12> : TransformSet<3, 0, true, true, 640> {};
+template <> struct TransformLargeTune<double, 3> : TransformSet<24, 0, true, false, 272> {};
 template <> struct TransformLargeTune<double, 4> : TransformSet<2, 2, false, false> {};
 template <> struct TransformLargeTune<double, 7> : TransformSet<6, 0, true, false, 1024> {};
-template <> struct TransformLargeTune<double, 9> : TransformSet<4, 0, true, false> {};
+template <> struct TransformLargeTune<double, 9> : TransformSet<4, 0, true, false, 1024> {};
 template <> struct TransformLargeTune<double, 10> : TransformSet<3, 0, true, false, 1024> {};
 template <> struct TransformLargeTune<double, 12> : TransformSet<2, 2, true, false> {};
-template <> struct TransformLargeTune<double, 13> : TransformSet<2, 0, true, false> {};
+template <> struct TransformLargeTune<double, 13> : TransformSet<2, 0, true, false, 512> {};
 
 template <typename T, int N, bool FWD, typename Tune>
 struct TransformLauncherT {
@@ -257,8 +262,11 @@ struct TransformLauncher {
     using Large = TransformLauncherT<T, N, FWD, TransformLargeTune<T, N>>;
     static hipError_t launch(const TransformArgs &a)
     {
-        constexpr long long most = TransformLargeTune<T, N>::FROM / (2LL * N * N * N * (long long)sizeof(T));
-        return a.num_elems <= most ? Cached::launch(a) : Large::launch(a);
+        return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
+    }
+    static bool takes_large(long long num_elems)
+    {
+        return num_elems > TransformLargeTune<T, N>::FROM / (2LL * N * N * N * (long long)sizeof(T));
     }
     static hipError_t prepare()
     {
@@ -269,6 +277,7 @@ struct TransformLauncher {
 
 #define TPO_TRANSFORM_ENTRY(T, N)                                                          \
     TransformEntry { &TransformLauncher<T, N, true>::launch, &TransformLauncher<T, N, false>::launch, \
-                     &TransformLauncher<T, N, true>::prepare, &TransformLauncher<T, N, false>::prepare }
+                     &TransformLauncher<T, N, true>::prepare, &TransformLauncher<T, N, false>::prepare,   \
+                     &TransformLauncher<T, N, true>::takes_large }
 
 }  // namespace tpo

@@ -44,3 +44,16 @@ def test_convection_over_integrated(convection_setting, dtype, nv, nq, rule, row
         assert convection_setting(dtype, nv, nq, mb) == 0, mb
     for mb in row:
         assert convection_setting(dtype, nv, nq, mb) == 1, mb
+
+
+@pytest.mark.parametrize("dtype,n,first,second", [
+    ("f64", 3, (100, 275), (290, 2500)), ("f64", 9, (100, 275, 500, 900), (1200, 2500)),
+    ("f64", 13, (100, 275, 430), (600, 2500)), ("f64", 7, (600, 900), (1200,)), ("f64", 12, (240,), (290, 2500)),
+    ("f32", 12, (30, 290, 500, 600), (800, 2500)), ("f32", 3, (240,), (290, 2500))])
+def test_transform(dtype, n, first, second):
+    fn = tpo.lib().tpo_internal_transform_setting
+    fn.argtypes = [ctypes.c_int] * 2 + [ctypes.c_longlong]
+    code, word = DT[dtype]
+    for line, sizes in ((0, first), (1, second)):
+        for mb in sizes:
+            assert fn(n, code, int(mb * 1e6 / (2 * n ** 3 * word))) == line, mb
