@@ -57,12 +57,12 @@ namespace tpo {
 __device__ __forceinline__ void lds_load_x4(const void *src, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory");
+                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_load_x1(const void *src, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
-                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory");
+                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory", "m0");
 }
 // A field of one element (whole words, word aligned) as a flat copy in LDS: 16-byte chunks, then
 // one instruction for the up to three words past the last whole chunk.
