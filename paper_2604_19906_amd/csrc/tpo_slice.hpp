@@ -53,16 +53,17 @@
 namespace tpo {
 
 // 16 (x4) or 4 (x1) bytes per lane from memory straight to LDS, lane L to lds + 16 L (4 L); lds is
-// uniform.  Counted by vmcnt; the caller waits.
+// uniform.  Counted by vmcnt; the caller waits.  The address goes through m0, as an operand, so that the
+// compiler knows what m0 holds; the s_nop is the wait state that such a load needs behind a write of m0.
 __device__ __forceinline__ void lds_load_x4(const void *src, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory", "m0");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "{m0}"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory");
 }
 __device__ __forceinline__ void lds_load_x1(const void *src, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
-                 :: "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory", "m0");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :: "{m0}"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src) : "memory");
 }
 // A field of one element (whole words, word aligned) as a flat copy in LDS: 16-byte chunks, then
 // one instruction for the up to three words past the last whole chunk.
