@@ -201,8 +201,12 @@ def _runtime():
     if _rt is None:
         import torch
 
-        _rt = ({torch.float64: TPO_F64, torch.float32: TPO_F32}, torch._C._cuda_getDevice,
-               torch._C._cuda_getCurrentRawStream)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if device is None or stream is None:    # not part of torch's public interface
+            device = torch.cuda.current_device
+            stream = lambda dev: torch.cuda.current_stream(dev).cuda_stream
+        _rt = ({torch.float64: TPO_F64, torch.float32: TPO_F32}, device, stream)
     return _rt
 
 
