@@ -1,8 +1,10 @@
-"""The convection term on both sides of the batch size where its launch settings change (fields that
-fit the last-level cache or not): every element against plain fp64 products on the device, the last
-elements against the CPU oracle, ragged last workgroups.  Both settings add in the same order, so a
-batch's results are the same bits as those of its parts.  One shape per kind of setting: other units
-per workgroup, lanes numbered per phase, SPLIT, the 4x4x1 form, all loads first."""
+"""The convection term on both sides of the batch sizes where its launch settings change.  Both settings
+add in the same order, so a batch's results are the same bits as those of its parts: checked for every
+shape at its own line, with ragged last workgroups and the last elements against the CPU oracle.  For one
+shape per kind of setting (other units per workgroup, lanes numbered per phase, SPLIT, the 4x4x1 form, all
+loads first) also every element against plain fp64 products on the device."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -27,6 +29,73 @@ SHAPES = [("f64", 3, 3), ("f64", 9, 9), ("f64", 7, 7), ("f64", 10, 10), ("f64", 
           ("f64", 7, 11), ("f64", 8, 12), ("f64", 9, 14), ("f64", 11, 12), ("f64", 11, 11), ("f64", 16, 16), ("f32", 3, 3), ("f32", 5, 5),
           ("f32", 7, 7), ("f32", 11, 11), ("f32", 13, 13), ("f32", 2, 3), ("f32", 6, 9), ("f32", 8, 12), ("f32", 10, 12),
           ("f32", 11, 13), ("f32", 12, 14)]
+
+
+def first_large(dtype, nv, nq):
+    """Smallest batch from which on the second setting is taken (asked of the library), or None."""
+    fn = tpo.lib().tpo_internal_convection_setting
+    fn.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    large = lambda e: fn(nv, nq, tpo.TPO_F64 if dtype == "f64" else tpo.TPO_F32, e) == 1
+    if not large(1 << 40):
+        return None
+    lo, hi = 0, 1 << 40
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if large(mid) else (mid, hi)
+    return hi
+
+
+ALL = [(dtype, nv, nq) for dtype in ("f64", "f32")
+       for nv, nq in [(n, n) for n in range(1, 17)]
+       + [(n, q) for n in range(2, 13) for q in sorted({n + 1, n + 2, (3 * n + 1) // 2}) if q <= 16]]
+
+
+@pytest.mark.parametrize("dtype,nv,nq", ALL)
+def test_every_shape_at_its_line(dtype, nv, nq):
+    """The first batch of the second setting, two elements more for a ragged last workgroup: the same bits as
+    the parts, which take the first setting, and the last elements against the CPU oracle."""
+    line = first_large(dtype, nv, nq)
+    e = (line if line and line > 1 else 1000) + 2       # one setting for every batch: 1002
+    dt = torch.float64 if dtype == "f64" else torch.float32
+    w = wl.conv_custom(nv, e, dtype, key=1900 + 20 * nv + nq, nq=nq)
+    d, i = (torch.from_numpy(np.ascontiguousarray(m)).cuda() for m in wl.conv_matrices(w))
+    g = torch.Generator(device="cuda").manual_seed(nv * 20 + nq)
+    P = torch.empty((3, 3, e, nq, nq, nq), dtype=dt, device="cuda").uniform_(-1, 1, generator=g)
+    M = torch.empty((e, nq, nq, nq), dtype=dt, device="cuda").uniform_(0.5, 2, generator=g)
+    print(f"case convection {dtype} ({nv},{nq}) E={e}", flush=True)
+    large = tpo.convection_tensors(P, M, d, i, F=torch.full((3, e, nv, nv, nv), float("nan"), dtype=dt,
+                                                            device="cuda"))
+    torch.cuda.synchronize()
+    assert not torch.isnan(large).any()
+    cut = max(1, e // 2)
+    for lo, hi in ((0, cut), (cut, e), (0, 1)):
+        if hi > lo:
+            part = tpo.convection_tensors(P[:, :, lo:hi].contiguous(), M[lo:hi].contiguous(), d, i)
+            torch.cuda.synchronize()
+            assert torch.equal(part, large[:, lo:hi])
+    tail = slice(max(0, e - 7), e)
+    h = lambda t: t.contiguous().cpu().numpy()
+    want = oracle.convection_apply(h(P[:, :, tail]), h(M[tail]), h(d), h(i))
+    assert oracle.max_rel_err_per_element(h(large[:, tail]).reshape(want.shape[0] * want.shape[1], nv, nv, nv),
+                                          want.reshape(-1, nv, nv, nv)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("nv,nq", [(8, 10), (8, 12)])
+def test_one_workgroup_per_cu(nv, nq):
+    """fp32 shapes that leave the table's setting while only the other one's workgroups are one per CU."""
+    fn = tpo.lib().tpo_internal_convection_setting
+    fn.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    settings = [fn(nv, nq, tpo.TPO_F32, e) for e in range(1, 1000)]
+    edges = [e for e in range(1, 999) if settings[e - 1] != settings[e]]
+    assert len(edges) == 2 and settings[0] == settings[-1] == 1
+    w = wl.conv_custom(nv, 1000, "f32", key=1950 + nv, nq=nq)
+    p, m, d, i = (torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in wl.conv_inputs(w))
+    whole = tpo.convection_tensors(p, m, d, i)
+    for e in (edges[0], edges[0] + 1, edges[1], edges[1] + 1):
+        print(f"case convection f32 ({nv},{nq}) E={e}", flush=True)
+        part = tpo.convection_tensors(p[:, :, :e].contiguous(), m[:e].contiguous(), d, i)
+        torch.cuda.synchronize()
+        assert torch.equal(part, whole[:, :e])
 
 
 @pytest.mark.parametrize("dtype,nv,nq", SHAPES)
