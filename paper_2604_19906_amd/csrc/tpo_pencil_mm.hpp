@@ -45,16 +45,21 @@ struct MmShape {
 // backward; the quadruple of row group rg and input l is number RGP l + rg.  Rows past the matrix repeat
 // its last row (their results are never used) and input indices past it some entry (never multiplied),
 // so the only index arithmetic is one lane offset per direction; the registers are constant distances
-// apart.  Dense packing (RG instead of RGP) needs a division and masks per register: 109 instead of 60
-// vector instructions in the prologue of the n = 13 kernel below, of 590 in all.  Us
-// per call, dense / this, with the load orders of the kernels: inverse Helmholtz at 3 GB n = 11 598 / 561, 12
-// 588 / 583, 13 592 / 584, at 150 MB 31.4 / 27.2, 30.7 / 29.6, 32.4 / 30.2; separable form n = 13 823 / 802.
+// apart.  Dense packing (RG instead of RGP) needs a division and masks per register: the n = 13 kernel below
+// issued 213 vector and 234 matrix instructions, now 164 and 234; n = 11 156 vector instructions, now 82.  The
+// arithmetic is unsigned: with signed indices an offset may be negative for all the compiler knows and is
+// widened per lane (n = 8 59 vector instructions, now 49 as with dense packing; separable form 1.02 of the time).  Us per
+// call, dense / this, with the load orders of the kernels: inverse Helmholtz at 3 GB n = 10 597 / 582, 11 585 / 549, 12
+// 572 / 567, 13 580 / 575, at 150 MB 31.2 / 30.0, 31.0 / 27.9, 29.8 / 29.1, 31.3 / 30.8; separable form at 3 GB n = 8 588 / 584,
+// 10 834 / 813, 11 814 / 771, 13 825 / 793.
 template <int N>
 __device__ __forceinline__ float mm_coef(const float *__restrict__ S, bool fwd, int t, int lane)
 {
-    constexpr int ROWS = 4 * MmShape<N>::RGP, LPT = 64 / ROWS;      // rows, input indices per register
-    const int row = (lane % ROWS) < N ? lane % ROWS : N - 1, q = lane / ROWS;
-    int idx = fwd ? q * N + row + LPT * t * N : row * N + q + LPT * t;
+    constexpr unsigned ROWS = 4 * MmShape<N>::RGP, LPT = 64 / ROWS;
+    const unsigned l = lane & 63, q = l / ROWS;
+    unsigned row = l % ROWS;
+    if (ROWS > N) row = row < N - 1 ? row : N - 1;
+    unsigned idx = fwd ? q * N + row + LPT * t * N : row * N + q + LPT * t;
     if (N % LPT != 0) idx = idx < N * N - 1 ? idx : N * N - 1;
     return S[idx];
 }
