@@ -70,7 +70,8 @@ KERNEL_SOURCES = {
     "ihelm": _COMMON + ["tpo_mfma.hpp", "tpo_mfma_f64.hip", "tpo_mfma_f32.hip", "tpo_pencil_f64.hip",
                         "tpo_pencil_f32.hip", "tpo_pencil_mm_f32.hip"],
     "transform": _COMMON + ["tpo_transform.hpp", "tpo_transform_f64.hip", "tpo_transform_f32.hip"],
-    "convection": _COMMON + ["tpo_convection.hpp", "tpo_convection_f64.hip", "tpo_convection_f32.hip"],
+    "convection": _COMMON + ["tpo_convection.hpp", "tpo_convection_f64.hip", "tpo_convection_f32.hip",
+                             "tpo_convection_rect_f64.hip", "tpo_convection_rect_f32.hip"],
     "aniso": _COMMON + ["tpo_mfma.hpp", "tpo_generic.hip", "tpo_slice.hpp", "tpo_slice_f32.hip"],
 }
 
