@@ -126,29 +126,28 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
         load_words<(HINT & 1) != 0>(Mq + (size_t)e * QC + (size_t)(p * N), mq);
         if constexpr (LOADS_FIRST) {
             // All four long loads go out before anything waits for one of them (the fences keep the third
-            // one, whose use is far below, from sinking).  It takes 17 .. 30 registers more per lane.
-            T x1[N];
+            // one, whose use is far below, from sinking).  It takes 19 .. 31 registers more per lane.
+            T x01[2][N];
             auto load_p = [&](int dir, T (&w)[N]) {
                 const size_t cube = ((size_t)(c * 3 + dir) * (size_t)num_elems + (size_t)e) * QC;
                 load_words<(HINT & 1) != 0>(Pq + cube + (size_t)(p * N), w);
             };
-            auto product = [&](const TPO_CONSTANT T *S, T (&w)[N], T *dst) {
+            load_p(0, x01[0]);
+            load_p(1, x01[1]);
+            load_p(2, x2);
+#pragma unroll
+            for (int dir = 0; dir < 3; ++dir) {
+                T (&w)[N] = dir < 2 ? x01[dir] : x2;
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int l = 0; l < N; ++l) w[l] *= mq[l];
-                mode_product<T, N, false>(S, w, y);
+                if (dir < 2) {
+                    mode_product<T, N, false>(dir == 0 ? Dm : Im, w, y);
+                    T *dst = dir == 0 ? c0 : c1;
 #pragma unroll
-                for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
-            };
-            load_p(0, x);
-            load_p(1, x1);
-            load_p(2, x2);
-            __builtin_amdgcn_sched_barrier(0);
-            product(Dm, x, c0);
-            __builtin_amdgcn_sched_barrier(0);
-            product(Im, x1, c1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int l = 0; l < N; ++l) x2[l] *= mq[l];
+                    for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
+                }
+            }
         } else {
 #pragma unroll
             for (int dir = 0; dir < 3; ++dir) {
