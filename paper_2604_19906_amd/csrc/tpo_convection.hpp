@@ -268,7 +268,10 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
     };
     // From n = 13 on all four long loads go out before the tables and before anything waits for one of
     // them; below, the registers they hold cost more than the wait.  At 3 GB, first against last:
-    // n = 13 617 / 651 us, 14 726 / 768, 16 606 / 633; n = 12 614 / 588, 11 636 / 565, 9 605 / 542.
+    // n = 13 617 / 651 us, 14 726 / 768, 16 606 / 633; n = 12 614 / 588, 11 636 / 565, 9 605 / 542.  On smaller
+    // batches, time over that with densely packed tables and the loads last, first / last: 8 MB n = 13 1.01 /
+    // 1.03, 14 0.96 / 1.00, 15 0.99 / 1.00, 16 0.95 / 1.00; 150 MB 1.03 / 1.01, 1.02 / 0.96, 1.02 / 1.01, 0.99 / 1.00; 600 MB 0.94 /
+    // 1.02, 0.96 / 0.98, 0.97 / 0.97, 0.97 / 0.96.
     // The branch on `on` is what keeps the compiler from moving the loads of the others up.
     auto load_field = [&](const float *f, float (&w)[N]) {
         if (LOADS_FIRST || on) {
@@ -750,8 +753,9 @@ struct ConvectionRectEntry {
 // inverse-Helmholtz operator).  A sweep over 1 .. 16 units x SPLIT x form on MI355X found more for
 // some n (us per call on 2.5 GB, rule / setting): fp64 n = 7 454 / 430, n = 10 484 / 432, which also
 // hold on small batches (150 MB: 31.1 / 25.9, 31.8 / 30.3; 2 MB: 4.9 / 4.1, 7.2 / 6.1), as does
-// fp32 n = 7 (462 / 446, 27.5 / 26.1, 4.4 / 4.0); fp64 n = 3 525 / 499, 9 460 / 444 and fp32 n = 3 567 / 516,
-// 5 486 / 468, 11 502 / 466, which only pay once the fields pass the last-level cache.
+// fp32 n = 7 (462 / 446, 27.5 / 26.1, 4.4 / 4.0; but fp64 n = 10 1.00 .. 1.04 at 100 .. 175 MB); fp64 n = 3 525 / 499, 9 460 / 444 and fp32 n = 3 567 / 516,
+// 5 486 / 468, 11 502 / 466, which only pay once the fields pass the last-level cache.  (Swept before all
+// loads went first for fp64 n >= 11 and fp32 n >= 13; not swept again.)
 template <typename T, int N> struct ConvectionTune {
     static constexpr int G = convection_group<T, N>();
     static constexpr bool SPLIT = convection_split<T, N>();

@@ -305,7 +305,9 @@ ihelm_pencil_mm_kernel(const float *u, const float *__restrict__ Sx, const float
 }
 
 // Per n: elements per workgroup, hint bits and die renumbering: the best of the same sweep as
-// for the vector-FMA pencil kernels; n = 13 at E = 1048576.  G = 0: the lane-utilisation rule.
+// for the vector-FMA pencil kernels; n = 13 at E = 1048576.  G = 0: the lane-utilisation rule.  (Swept before
+// the coefficient tables took their present layout, in which n = 10 has three registers per table instead
+// of two; not swept again.)
 struct PencilMmRow { int g, hint, xcd; };
 constexpr PencilMmRow kPencilMmTable[TPO_MAX_N + 1] = {
     {0, 0, 0},

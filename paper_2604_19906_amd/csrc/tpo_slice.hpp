@@ -34,10 +34,12 @@
 // consecutive elements: the next u_e is on its way from the end of the forward products on, the
 // next D_e from the end of the scale on.
 //
-// What bounds it: issue of the matrix instructions (at (12,12,16) 7104 cycles per element and SIMD
-// of about 8600 with everything else), with 18-26 KB of LDS per wavefront (6 to 8 wavefronts per
-// CU) to cover the loads.  Against the runtime-size pencil kernel (bound by vector FMA issue), GB/s
-// of algorithmic traffic on 6 GB: (12,12,16) 4980 against 3820, (11,11,14) 4520 / 3630, (9,14,15)
+// What bounds it: at (12,12,16) issue of the matrix instructions, 7104 cycles per element: they hold a
+// SIMD 65 % of the launch and the other vector instructions 7 %, at a clock that falls to 1.8 GHz,
+// with seven wavefronts per CU (21 KB of LDS each) to cover loads and LDS.  Other shapes take 4 to 32 KB of
+// LDS per wavefront, half of them less than 13 KB; there registers set the number of wavefronts, two
+// per SIMD from n_x KSB = 33 on, one for n_x >= 15 with KSB = 4.  Against the runtime-size pencil
+// kernel, GB/s of algorithmic traffic on 6 GB: (12,12,16) 4980 against 3820, (11,11,14) 4520 / 3630, (9,14,15)
 // 4750 / 3070, (12,16,16) 4850 / 3770, (13,13,12) 4190 / 3730.
 // One element per wavefront instead of a walk over eight: 4150 instead of 4400 at (12,16,16); a
 // grid of resident wavefronts that divide the batch among them: the same at eight wavefronts per CU,
@@ -90,7 +92,8 @@ template <int NX, int KSB, int KSC>
 struct SliceShape {
     // Slices per group of stores.  Four fill the 1 KB store instructions better, two need less LDS:
     // GB/s with four / two on 6 GB, (12,12,16) 4980 / 4510, (11,11,14) 4520 / 4520, (12,16,16)
-    // 4850 / 5020, (13,14,14) 4190 / 4365, (15,15,16) 3960 / 4330.
+    // 4850 / 5020, (13,14,14) 4190 / 4365, (15,15,16) 3960 / 4330.  By n_x alone, although what four
+    // slices cost goes with n_y n_z: (12,16,16) has the slower one of the two.
     static constexpr int OUT = NX <= 12 ? 4 : 2;
     // LDS of one workgroup (one wavefront): both stages and the slices on their way out.
     static size_t lds_bytes(int ny, int nz)

@@ -114,7 +114,7 @@ transform_mm_kernel(const float *u, const float *__restrict__ Sx, const float *_
     float x[N], y[M::NY], tab[M::NTAB];
 
     // axis 2: lane (a,b) = (hi,lo) owns u[a][b][0..n-1], contiguous in memory
-    // From n = 13 on u is asked for before the table (3 GB: n = 13 714 against 758 us, 14 816 / 859, 15 800
+    // From n = 13 on u is asked for before the table (4 GB: n = 13 714 against 758 us, 14 816 / 859, 15 800
     // / 837; n = 12 735 / 724).
     constexpr bool U_FIRST = N >= 13;
     auto load_u = [&]() { load_words<(HINT & 1) != 0>(u + wg_base + (unsigned)(g * N3 + p * N), x); };
@@ -172,7 +172,8 @@ transform_mm_kernel(const float *u, const float *__restrict__ Sx, const float *_
 // Elements per workgroup and die renumbering as for the separable-diagonal operator kernels
 // (same traffic: one field in, one out); cached loads, since each lane's n-word run shares its
 // cache lines with its neighbours' runs.  The matrix-core form has its own rows: the best of 1 .. 3
-// elements per workgroup x non-temporal stores x renumbering.
+// elements per workgroup x non-temporal stores x renumbering (swept before the coefficient tables took their
+// present layout and u went first from n = 13 on; the settings were not swept again).
 template <typename T, int N> struct TransformTune {
     using Tune = PencilSepTune<T, N>;
     static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
