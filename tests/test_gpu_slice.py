@@ -140,3 +140,20 @@ def test_slice_infinities_and_nan(dims):
     assert np.isposinf(ref[3]).all() and np.isposinf(ref[5]).all() and np.isnan(ref[6]).all()
     keep = [i for i in range(16) if i not in (3, 5, 6, 9)]
     assert oracle.max_rel_err_per_element(got[keep], ref[keep]) <= TOL["f32"]
+
+
+def test_slice_under_capture():
+    """A captured call, replayed on new input, gives what the call gives."""
+    dims, e = (12, 12, 16), 20000
+    assert takes_slice(dims, e)
+    t = device_inputs(dims, e)
+    out = torch.empty_like(t[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tpo.apply_aniso_tensors(*t, v=out)
+    for k in range(3):
+        t[0].mul_(0.5 + k)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, tpo.apply_aniso_tensors(*t))
