@@ -79,6 +79,19 @@ constexpr int convection_group()
     return best;
 }
 
+// Words per batch of scalar loads in the vector-FMA products (matrix_product): batches in fp64 for n >= 7 and
+// from 77 entries on where n_q != n_v (not for n = 9, which they take from 64 to 76 registers and from eight to six
+// wavefronts per SIMD): they give 0.73 .. 0.95 of the time at 0.5 MB and 0.80 .. 1.00 at 2.5 GB ((8,10) and (9,10) lose 4 to 6 % at
+// 100 .. 250 MB).  Smaller matrices lose as much as they gain ((6,6) up to 1.10, (7,8) and (8,9) 1.05 at 100 .. 320 MB),
+// and in fp32 the fences cost more than the waits (up to 1.12 on n_q >= 9 from 60 MB on).
+template <typename T, int NV, int NQ = NV>
+constexpr int convection_batch_words()
+{
+    if (sizeof(T) == 4) return 0;
+    if (NV == NQ) return NV >= 7 && NV != 9 ? kScalarBatch : 0;
+    return NV * NQ >= 77 ? kScalarBatch : 0;
+}
+
 // HINT bit 0 / 1: non-temporal loads / stores.  XCD: the SAME_DIE renumbering above.
 // SPLIT: the third term's axis-l and axis-m products run after the first two terms have been
 // merged, in the LDS cube that merge frees: two cubes per unit instead of three (more
@@ -90,6 +103,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
                          const T *Im_, T *__restrict__ F, long long num_elems)
 {
     using Sh = PencilShape<T, N, G>;
+    constexpr int SB = convection_batch_words<T, N>();
     constexpr int P = Sh::P, PA = Sh::PA, PB = Sh::PB, CUBE = Sh::CUBE;
     extern __shared__ __align__(16) unsigned char tpo_lds[];
     T *lds = reinterpret_cast<T *>(tpo_lds);
@@ -142,7 +156,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 #pragma unroll
                 for (int l = 0; l < N; ++l) w[l] *= mq[l];
                 if (dir < 2) {
-                    mode_product<T, N, false>(dir == 0 ? Dm : Im, w, y);
+                    mode_product<T, N, false, SB>(dir == 0 ? Dm : Im, w, y);
                     T *dst = dir == 0 ? c0 : c1;
 #pragma unroll
                     for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
@@ -159,7 +173,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 #pragma unroll
                     for (int l = 0; l < N; ++l) x2[l] = x[l];
                 } else {
-                    mode_product<T, N, false>(dir == 0 ? Dm : Im, x, y);
+                    mode_product<T, N, false, SB>(dir == 0 ? Dm : Im, x, y);
                     T *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
 #pragma unroll
                     for (int i = 0; i < N; ++i) dst[hi * PA + lo * PB + i] = y[i];
@@ -173,17 +187,17 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     if (on) {
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = c0[hi * PA + m * PB + lo];
-        mode_product<T, N, false>(Im, x, y);
+        mode_product<T, N, false, SB>(Im, x, y);
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = c1[hi * PA + m * PB + lo];
-        mode_product<T, N, false>(Dm, x, z);
+        mode_product<T, N, false, SB>(Dm, x, z);
 #pragma unroll
         for (int j = 0; j < N; ++j) c0[hi * PA + j * PB + lo] = y[j] + z[j];
     }
     if constexpr (SPLIT) {
         __syncthreads();                      // every lane has read its pencils of cube 1
         if (on) {                             // axis l of the third term: lane (n,m)
-            mode_product<T, N, false>(Im, x2, y);
+            mode_product<T, N, false, SB>(Im, x2, y);
 #pragma unroll
             for (int i = 0; i < N; ++i) c2[hi * PA + lo * PB + i] = y[i];
         }
@@ -192,7 +206,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     if (on) {
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = c2[hi * PA + m * PB + lo];
-        mode_product<T, N, false>(Im, x, y);
+        mode_product<T, N, false, SB>(Im, x, y);
 #pragma unroll
         for (int j = 0; j < N; ++j) c2[hi * PA + j * PB + lo] = y[j];
     }
@@ -202,10 +216,10 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
     if (on) {
 #pragma unroll
         for (int n = 0; n < N; ++n) x[n] = c0[n * PA + hi * PB + lo];
-        mode_product<T, N, false>(Im, x, y);
+        mode_product<T, N, false, SB>(Im, x, y);
 #pragma unroll
         for (int n = 0; n < N; ++n) x[n] = c2[n * PA + hi * PB + lo];
-        mode_product<T, N, false>(Dm, x, z);
+        mode_product<T, N, false, SB>(Dm, x, z);
         const size_t out = ((size_t)c * (size_t)num_elems + (size_t)e) * QC;
 #pragma unroll
         for (int k = 0; k < N; ++k) gstore<(HINT & 2) != 0>(F + out + (size_t)(k * P + p), y[k] + z[k]);
@@ -357,20 +371,6 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
 // after the merge of the first two terms); the lane sets differ per axis: n_q*n_q pencils along
 // l, n_q*n_v along m, n_v*n_v along n.
 
-// y[i] = sum_l A[i][l] * x[l], A [NV][NQ] row-major, entries through the scalar data path.
-template <typename T, int NV, int NQ>
-__device__ __forceinline__ void mode_product_rect(const TPO_CONSTANT T *A, const T (&x)[NQ], T (&y)[NV])
-{
-    asm volatile("" : "+s"(A));
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        T acc = A[i * NQ] * x[0];
-#pragma unroll
-        for (int l = 1; l < NQ; ++l) acc = fma_(A[i * NQ + l], x[l], acc);
-        y[i] = acc;
-    }
-}
-
 template <typename T, int NV, int NQ, int G>
 struct ConvRectShape {
     static constexpr int NB = NQ > NV ? NQ : NV;
@@ -431,7 +431,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
 #pragma unroll
                 for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
             } else {
-                mode_product_rect<T, NV, NQ>(dir == 0 ? Dm : Im, xq, yv);
+                matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(dir == 0 ? Dm : Im, xq, yv);
                 T *dst = dir == 0 ? c0 : c1;
 #pragma unroll
                 for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
@@ -445,10 +445,10 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c0[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
     }
     __syncthreads();                                    // every pencil of cubes 0 and 1 has been read
     if (on_m) {
@@ -458,7 +458,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     // axis l of the third term, into the freed cube 1: lane (n,m)
     if (on_l) {
         const int nn = p / NQ, mm = p - nn * NQ;
-        mode_product_rect<T, NV, NQ>(Im, x2, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, x2, yv);
 #pragma unroll
         for (int i = 0; i < NV; ++i) c1[nn * PA + mm * PB + i] = yv[i];
     }
@@ -467,7 +467,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int j = 0; j < NV; ++j) c1[bn * PA + j * PB + bi] = yv[j];   // the lane's own pencil
     }
@@ -478,10 +478,10 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
         const int jj = p / NV, ii = p - jj * NV;
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = c0[n * PA + jj * PB + ii];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = c1[n * PA + jj * PB + ii];
-        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
         const size_t out = ((size_t)c * (size_t)num_elems + (size_t)e) * VC;
 #pragma unroll
         for (int k = 0; k < NV; ++k)
@@ -545,7 +545,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
 #pragma unroll
                 for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
             } else {
-                mode_product_rect<T, NV, NQ>(dir == 0 ? Dm : Im, xq, yv);
+                matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(dir == 0 ? Dm : Im, xq, yv);
                 T *dst = lds + (2 * gl + dir) * CUBE;
                 const int nn = pl / NQ, mm = pl - nn * NQ;
 #pragma unroll
@@ -561,10 +561,10 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c0[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
     }
     __syncthreads();                                    // every pencil of cubes 0 and 1 has been read
     if (on_m) {
@@ -575,7 +575,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_l) {
         T *dst = lds + (2 * gl + 1) * CUBE;
         const int nn = pl / NQ, mm = pl - nn * NQ;
-        mode_product_rect<T, NV, NQ>(Im, x2, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, x2, yv);
 #pragma unroll
         for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
     }
@@ -584,7 +584,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int j = 0; j < NV; ++j) c1[bn * PA + j * PB + bi] = yv[j];   // the lane's own pencil
     }
@@ -596,10 +596,10 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
         const int jj = pn / NV, ii = pn - jj * NV;
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = d0[n * PA + jj * PB + ii];
-        mode_product_rect<T, NV, NQ>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = d1[n * PA + jj * PB + ii];
-        mode_product_rect<T, NV, NQ>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
         const long long unit = batch * G + gn;
         const long long e = unit / 3;
         const size_t out = ((size_t)(unit - 3 * e) * (size_t)num_elems + (size_t)e) * VC;

@@ -20,6 +20,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "tpo_internal.h"
 
 namespace tpo {
@@ -86,34 +89,91 @@ constexpr int pencil_group()
     return best;
 }
 
-// y[i] = sum_l S[l][i] * x[l]   (FWD: the transpose of the stored matrix is applied)
-// y[i] = sum_l S[i][l] * x[l]   (!FWD)
-// S is read through the constant address space so that its entries arrive in SGPRs.
-template <typename T, int N, bool FWD>
-__device__ __forceinline__ void mode_product(const TPO_CONSTANT T *S, const T (&x)[N],
-                                             T (&y)[N])
+// f(integral_constant<int, 0>) .. f(integral_constant<int, K - 1>)
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Product with a matrix S of R rows and C columns (row-major), read through the constant address
+// space so that its entries arrive in SGPRs:
+//   FWD : y[c] = sum_r S[r][c] * x[r]   (the transpose of the stored matrix is applied)
+//   !FWD: y[r] = sum_c S[r][c] * x[c]
+//
+// What bounds it with few wavefronts on a SIMD is the scalar loads: they come back in any order, so that
+// a wavefront can only wait for all of them, and left to itself the compiler issues one right before that
+// wait: 16 FMAs (64 cycles), then the whole latency of a load, 13 times a product at fp64 n = 14.  Matrices
+// of more than 2 * SB words therefore come in batches of SB words in two buffers: wait for batch b, issue
+// the loads of batch b + 1, then the FMAs of batch b; the fences hold that order.  Time over the unbatched
+// product's (MI355X, fp64): 0.5 MB a call, n = 8 0.86, 11 0.83, 14 0.78, 16 0.72; 200 MB 0.97, 0.93, 0.93,
+// 0.91; 2.5 GB n <= 11 1.00, 12 0.92, 13 0.96, 14 0.95, 16 0.94; square convection n = 15, 16 0.86, 0.80 at
+// 2.5 GB.  Batches of 16 / 24 / 40 words: 1.03 .. 1.30 at 60 MB / 0.87 .. 0.97 at all sizes / ahead by 2 .. 12 % at
+// 60 and 200 MB for n >= 11, behind by 3 .. 8 % at 2.5 GB.  Matrices of up to two batches fit the SGPRs at
+// once and lose up to 12 % by the fences (convection n <= 8 in fp32, 4 and 5 in fp64, at 60 and 200 MB).
+// SB = 0 leaves the order to the compiler, for the kernels that are slower with batches.
+constexpr int kScalarBatch = 32;
+template <typename T, int R, int C, bool FWD, int SB = kScalarBatch>
+__device__ __forceinline__ void matrix_product(const TPO_CONSTANT T *S, const T (&x)[FWD ? R : C],
+                                               T (&y)[FWD ? C : R])
 {
     // Make the pointer opaque per product: otherwise two products with the same matrix share
-    // one set of scalar loads, all n*n entries stay live across both and spill out of the
+    // one set of scalar loads, all entries stay live across both and spill out of the
     // SGPR file.
     asm volatile("" : "+s"(S));
-    if constexpr (FWD) {
+    constexpr int NE = R * C;                                   // entries
+    constexpr int B = SB * 4 / (int)sizeof(T);                  // entries per batch
+    if constexpr (SB == 0 || NE <= 2 * B) {
+        if constexpr (FWD) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) y[i] = S[i] * x[0];
+            for (int c = 0; c < C; ++c) y[c] = S[c] * x[0];
 #pragma unroll
-        for (int l = 1; l < N; ++l) {
+            for (int r = 1; r < R; ++r) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) y[i] = fma_(S[l * N + i], x[l], y[i]);
+                for (int c = 0; c < C; ++c) y[c] = fma_(S[r * C + c], x[r], y[c]);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                T acc = S[r * C] * x[0];
+#pragma unroll
+                for (int c = 1; c < C; ++c) acc = fma_(S[r * C + c], x[c], acc);
+                y[r] = acc;
+            }
         }
     } else {
+        T buf[2][B];
+        auto load = [&](int b) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            T acc = S[i * N] * x[0];
+            for (int k = 0; k < B; ++k)
+                if (b * B + k < NE) buf[b & 1][k] = S[b * B + k];
+        };
+        auto term = [&](int b, int k) {
+            const int q = b * B + k;
+            if (q >= NE) return;
+            const int r = q / C, c = q - r * C;
+            const int i = FWD ? c : r, l = FWD ? r : c;
+            y[i] = l == 0 ? buf[b & 1][k] * x[0] : fma_(buf[b & 1][k], x[l], y[i]);
+        };
+        load(0);
+        for_each_index([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            term(b, 0);                                 // waits for batch b
+            __builtin_amdgcn_sched_barrier(0);
+            load(b + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int l = 1; l < N; ++l) acc = fma_(S[i * N + l], x[l], acc);
-            y[i] = acc;
-        }
+            for (int k = 1; k < B; ++k) term(b, k);
+            __builtin_amdgcn_sched_barrier(0);
+        }, std::make_integer_sequence<int, (NE + B - 1) / B>{});
     }
+}
+
+// The square product of the operators: y[i] = sum_l S[l][i] * x[l] (FWD), sum_l S[i][l] * x[l] (!FWD).
+template <typename T, int N, bool FWD, int SB = kScalarBatch>
+__device__ __forceinline__ void mode_product(const TPO_CONSTANT T *S, const T (&x)[N], T (&y)[N])
+{
+    matrix_product<T, N, N, FWD, SB>(S, x, y);
 }
 
 // Global accesses with or without the non-temporal hint (streamed once, never re-read).
@@ -208,8 +268,9 @@ __device__ __forceinline__ long long pencil_batch(long long nbatch)
 //            D_e[a][b][c] = 1 / (lam_x[a] + lam_y[b] + lam_z[c] + mu[e])
 //            (sum left to right; SEP = 1: IEEE division, SEP = 2: recip_<false>); D is ignored
 //            and may be null.
+// SB: see matrix_product.
 template <typename T, int N, int G, int HINT, bool DDIRECT = false, bool XCD = false,
-          int SEP = 0>
+          int SEP = 0, int SB = kScalarBatch>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
 ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
                     const T *__restrict__ D, T *v, long long num_elems,
@@ -258,7 +319,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
 #pragma unroll
             for (int l = 0; l < N; ++l) dd[l] = gload<(HINT & 1) != 0>(D + base + (size_t)(l * P + p));
         }
-        mode_product<T, N, true>(Sx, x, y);
+        mode_product<T, N, true, SB>(Sx, x, y);
 #pragma unroll
         for (int i = 0; i < N; ++i) cube[i * PA + hi * PB + lo] = y[i];
         if constexpr (!DDIRECT && SEP == 0) {
@@ -272,7 +333,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
     if (on) {
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = cube[hi * PA + m * PB + lo];
-        mode_product<T, N, true>(Sy, x, y);
+        mode_product<T, N, true, SB>(Sy, x, y);
 #pragma unroll
         for (int j = 0; j < N; ++j) cube[hi * PA + j * PB + lo] = y[j];
     }
@@ -282,15 +343,15 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
     if (on) {
 #pragma unroll
         for (int q = 0; q < N; ++q) x[q] = cube[hi * PA + lo * PB + q];
-        if constexpr (SEP != 0) {
+        mode_product<T, N, true, SB>(Sz, x, y);
+        if constexpr (SEP != 0) {       // after the product: the reciprocals would hold N registers through it
             const TPO_CONSTANT T *lam_z = (const TPO_CONSTANT T *)lam_z_;
 #pragma unroll
             for (int k = 0; k < N; ++k) dd[k] = recip_<SEP == 1>((sep_ab + lam_z[k]) + sep_mu);
         }
-        mode_product<T, N, true>(Sz, x, y);
 #pragma unroll
         for (int k = 0; k < N; ++k) y[k] *= (DDIRECT || SEP != 0) ? dd[k] : dpark[hi * PA + lo * PB + k];
-        mode_product<T, N, false>(Sz, y, x);
+        mode_product<T, N, false, SB>(Sz, y, x);
 #pragma unroll
         for (int k = 0; k < N; ++k) cube[hi * PA + lo * PB + k] = x[k];
     }
@@ -300,7 +361,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
     if (on) {
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = cube[hi * PA + m * PB + lo];
-        mode_product<T, N, false>(Sy, x, y);
+        mode_product<T, N, false, SB>(Sy, x, y);
 #pragma unroll
         for (int j = 0; j < N; ++j) cube[hi * PA + j * PB + lo] = y[j];
     }
@@ -310,7 +371,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
     if (on) {
 #pragma unroll
         for (int l = 0; l < N; ++l) x[l] = cube[l * PA + hi * PB + lo];
-        mode_product<T, N, false>(Sx, x, y);
+        mode_product<T, N, false, SB>(Sx, x, y);
 #pragma unroll
         for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(v + base + (size_t)(i * P + p), y[i]);
     }
@@ -350,6 +411,7 @@ struct PencilTune {
     static constexpr bool DDIRECT = R.ddirect != 0;
     static constexpr bool XCD = R.xcd != 0;
     static constexpr size_t LDS_MIN = 0;    // LDS requested at least (caps workgroups per CU)
+    static constexpr int SB = kScalarBatch; // words per batch of scalar loads (matrix_product)
 };
 // n = 11: two elements per workgroup (242 of 256 lanes), non-temporal loads of u_e, and an LDS
 // request of 28 KB (20.8 KB are used), which holds the CU at 5 workgroups = 10 elements instead
@@ -363,6 +425,7 @@ template <> struct PencilTune<double, 11> {
     static constexpr int G = 2, HINT = 1;
     static constexpr bool DDIRECT = true, XCD = true;
     static constexpr size_t LDS_MIN = 28 * 1024;
+    static constexpr int SB = kScalarBatch;
 };
 
 // Settings for small batches, used when LO < num_elems <= HI (HI = 0: never).  With a few
@@ -397,7 +460,7 @@ template <> struct PencilSmallTune<double, 9> : PencilTune<double, 9> {
     static constexpr long long LO = 0, HI = 16384;
 };
 template <> struct PencilSmallTune<double, 8> : PencilTune<double, 8> {
-    static constexpr int G = 1, HINT = 0;
+    static constexpr int G = 1, HINT = 0, SB = 0;       // (with batches of scalar loads 1.04 of the time)
     static constexpr bool DDIRECT = true;
     static constexpr long long LO = 4096, HI = 24576;
 };
@@ -418,12 +481,17 @@ template <> struct PencilSepTune<double, 8> : PencilTune<double, 8> {
 template <> struct PencilSepTune<double, 9> : PencilTune<double, 9> {
     static constexpr int G = 2, HINT = 0;       // (the D form's retuning at n = 9 was not repeated here)
 };
+// n = 12: with batches of scalar loads 1.06 .. 1.12 of the time at 100 MB .. 2.5 GB (0.82 .. 0.94 up to 25 MB)
+template <> struct PencilSepTune<double, 12> : PencilTune<double, 12> {
+    static constexpr int SB = 0;
+};
 
 // Settings of a pencil kernel spelled out.
 template <int GG, int H, bool X> struct PencilSet {
     static constexpr int G = GG, HINT = H;
     static constexpr bool DDIRECT = true, XCD = X;
     static constexpr size_t LDS_MIN = 0;
+    static constexpr int SB = kScalarBatch;
 };
 // Separable form on batches whose two fields pass the last-level cache, where a sweep over 1 .. 32
 // elements per workgroup x hints x renumbering on 2 GB per call found 4 % or more against the D form's
@@ -454,7 +522,7 @@ struct PencilLauncherT {
 
     static constexpr auto kernel()
     {
-        return &ihelm_pencil_kernel<T, N, G, Tune::HINT, DDIRECT, Tune::XCD, SEP>;
+        return &ihelm_pencil_kernel<T, N, G, Tune::HINT, DDIRECT, Tune::XCD, SEP, Tune::SB>;
     }
 
     static hipError_t launch(const ApplyArgs &a)
