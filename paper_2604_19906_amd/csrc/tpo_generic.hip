@@ -180,6 +180,159 @@ ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T
         });
 }
 
+// The same passes with more elements per workgroup than its lanes can hold pencils: a pass runs in turns of
+// one pencil per lane.  For shapes whose passes differ much in their number of pencils: there the kernel
+// above sizes the workgroup by the largest pass, and in the others most of the lanes idle.  What bounds it then is
+// the loads: u_e and D_e are asked for by few lanes, so few bytes are on their way (fp64 (3,9,16) 34 KB per CU against
+// 216 KB here).  us per call on 800 MB, kernel above / this one: fp64 (3,9,16) 329 / 155, (16,9,3) 279 / 157, (13,3,12)
+// 267 / 157, (10,7,13) 192 / 161; fp32 (3,9,15) 438 / 184, (14,4,3) 279 / 190, (8,15,6) 225 / 189.
+// With one turn per pass it is the slower one by 3 .. 15 % (quotients, loops).
+struct AnisoTurns {
+    int nx, ny, nz, g;
+    unsigned div_yz, div_xz, div_xy, div_y, div_z;      // for quotient()
+};
+// t / d for t < 2^24 and d <= 256, with m = ceil(2^32 / d) (d = 1: does not fit, m = 0): m * d exceeds 2^32 by less
+// than d, so the quotient is exact while t * d < 2^32
+__device__ __forceinline__ int quotient(int t, unsigned m) { return m == 0 ? t : (int)__umulhi((unsigned)t, m); }
+
+template <typename T, int MAXN, int HINT, bool XCD>
+__global__ void __launch_bounds__(ANISO_MAX_NT)
+ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T *__restrict__ D,
+                   T *v, AnisoTurns sh, long long num_elems, long long groups)
+{
+    extern __shared__ __align__(16) unsigned char tpo_lds[];
+    T *cube = reinterpret_cast<T *>(tpo_lds);
+    const TPO_CONSTANT T *Sx = (const TPO_CONSTANT T *)Sx_;
+    const TPO_CONSTANT T *Sy = (const TPO_CONSTANT T *)Sy_;
+    const TPO_CONSTANT T *Sz = (const TPO_CONSTANT T *)Sz_;
+    const int nx = sh.nx, ny = sh.ny, nz = sh.nz;
+
+    const int tid = threadIdx.x;
+    const int NT = blockDim.x;
+    const long long batch = pencil_batch<XCD>(groups);
+    if (batch >= groups) return;                           // padding workgroup of the renumbering
+    const long long e0 = batch * sh.g;
+    const long long left = num_elems - e0;
+    const int here = left < sh.g ? (int)left : sh.g;       // elements of this workgroup
+    const int pz = aniso_pz(nz), pyz = aniso_pyz(ny, nz);
+    const int cube_words = nx * pyz;
+    const int face = ny * nz, side = nx * nz, base = nx * ny;
+    const size_t total = (size_t)nx * face;
+    const T *ub = u + (size_t)e0 * total, *db = D + (size_t)e0 * total;
+    T *vb = v + (size_t)e0 * total;
+
+    // Pencil t of a pass with `limit` of them goes to lane t % NT in turn t / NT; the wavefront takes part in a
+    // turn if its first lane has a pencil, lanes past the end shadow the last one and do not store.
+    const int first = __builtin_amdgcn_readfirstlane(tid & ~63);
+
+    // D_e in the layout of the axis-2 pass (pencils (a, b), nz consecutive words), asked for before anything else
+    T dreg[MAXN];
+    dispatch_size<MAXN>(nz, [&](auto nc) {
+        constexpr int N = decltype(nc)::value, K = MAXN / N;
+        const int limit = here * base;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (first + k * NT < limit) {
+                const int t = min(tid + k * NT, limit - 1);
+                T w[N];
+                load_words<(HINT & 4) != 0, T, N>(db + (unsigned)(t * N), w);
+#pragma unroll
+                for (int i = 0; i < N; ++i) dreg[k * N + i] = w[i];
+            }
+        }
+    });
+
+    // forward, axis 0, from global memory: pencils (b, c)
+    dispatch_size<MAXN>(nx, [&](auto nc) {
+        constexpr int N = decltype(nc)::value, K = MAXN / N;
+        const int limit = here * face;
+        T x[K][N];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (first + k * NT < limit) {
+                const int t = min(tid + k * NT, limit - 1);
+                const T *p = ub + (unsigned)(t + quotient(t, sh.div_yz) * ((int)total - face));
+#pragma unroll
+                for (int l = 0; l < N; ++l) x[k][l] = gload<(HINT & 1) != 0>(p + l * face);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int t = tid + k * NT;
+            if (t < limit) {
+                const int q = quotient(t, sh.div_yz), p = t - q * face;
+                const int b = quotient(p, sh.div_z);
+                T *col = cube + q * cube_words + p + b * (pz - nz);
+                T y[N];
+                mode_product<T, N, true>(Sx, x[k], y);
+#pragma unroll
+                for (int i = 0; i < N; ++i) col[i * pyz] = y[i];
+            }
+        }
+    });
+    __syncthreads();
+    // axis 1, in place: pencils (a, c)
+    auto axis1 = [&](auto fwd) {
+        dispatch_size<MAXN>(ny, [&](auto nc) {
+            constexpr int N = decltype(nc)::value;
+            for (int t = tid; t < here * side; t += NT) {
+                const int q = quotient(t, sh.div_xz), p = t - q * side;
+                const int a = quotient(p, sh.div_z), c = p - a * nz;
+                T *col = cube + q * cube_words + a * pyz + c;
+                T x[N], y[N];
+#pragma unroll
+                for (int m = 0; m < N; ++m) x[m] = col[m * pz];
+                mode_product<T, N, decltype(fwd)::value>(Sy, x, y);
+#pragma unroll
+                for (int m = 0; m < N; ++m) col[m * pz] = y[m];
+            }
+        });
+    };
+    axis1(std::integral_constant<bool, true>{});
+    __syncthreads();
+    // axis 2 forward, scale, axis 2 backward, in place
+    dispatch_size<MAXN>(nz, [&](auto nc) {
+        constexpr int N = decltype(nc)::value, K = MAXN / N;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int t = tid + k * NT;
+            if (t < here * base) {
+                const int q = quotient(t, sh.div_xy), p = t - q * base;
+                const int a = quotient(p, sh.div_y), b = p - a * ny;
+                T *row = cube + q * cube_words + a * pyz + b * pz;
+                T x[N], y[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) x[i] = row[i];
+                mode_product<T, N, true>(Sz, x, y);
+#pragma unroll
+                for (int i = 0; i < N; ++i) y[i] *= dreg[k * N + i];
+                mode_product<T, N, false>(Sz, y, x);
+#pragma unroll
+                for (int i = 0; i < N; ++i) row[i] = x[i];
+            }
+        }
+    });
+    __syncthreads();
+    axis1(std::integral_constant<bool, false>{});
+    __syncthreads();
+    // backward, axis 0, to global memory
+    dispatch_size<MAXN>(nx, [&](auto nc) {
+        constexpr int N = decltype(nc)::value;
+        for (int t = tid; t < here * face; t += NT) {
+            const int q = quotient(t, sh.div_yz), p = t - q * face;
+            const int b = quotient(p, sh.div_z), c = p - b * nz;
+            const T *col = cube + q * cube_words + b * pz + c;
+            T x[N], y[N];
+#pragma unroll
+            for (int l = 0; l < N; ++l) x[l] = col[l * pyz];
+            mode_product<T, N, false>(Sx, x, y);
+            T *o = vb + (unsigned)(q * (int)total + p);
+#pragma unroll
+            for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(o + i * face, y[i]);
+        }
+    });
+}
+
 // Elements per workgroup: the g with the best lane utilisation in the pass with the most
 // pencils, among those with at most 256 lanes and at most 40 KB of LDS.
 template <typename T>
@@ -205,14 +358,88 @@ void aniso_shape(const AnisoArgs &a, int &g, int &nt, size_t &lds)
     lds = g * cube_bytes;                                          // at most 40 KB (34 KB for g = 1)
 }
 
-template <typename T, int MAXN>
-hipError_t launch_bound(const AnisoArgs &a)
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Lane-cycles that the products of g elements need over those that nt lanes spend on them in turns.
+double aniso_lane_use(int nx, int ny, int nz, int g, int nt)
 {
-    int g, nt;
-    size_t lds;
-    aniso_shape<T>(a, g, nt, lds);
-    if (sizeof(T) == 4 && slice_kernel_pays(a.nx, a.ny, a.nz, a.num_elems, g, nt / 64))
-        return launch_ihelm_slice(a);
+    double need = 0, spent = 0;
+    const int pencils[3] = {ny * nz, nx * nz, nx * ny}, n[3] = {nx, ny, nz};
+    for (int d = 0; d < 3; ++d) {
+        need += (double)g * pencils[d] * n[d] * n[d];
+        spent += (double)ceil_div(g * pencils[d], nt) * nt * n[d] * n[d];
+    }
+    return need / spent;
+}
+
+// Register class of the turns kernel: it holds turns * n words of u_e and of D_e in that many registers.
+// (Elements with at most eight points along every axis hardly take it.)
+constexpr int turns_class(int n) { return n <= 8 ? 8 : (n + 1) / 2 * 2; }
+
+// Elements and lanes per workgroup of the turns kernel: the best lane use, ties to the fewer lanes (over 46 shapes
+// at 100 and 800 MB within 3 % of the best of fourteen settings on average); g = 0: none fits.
+template <typename T>
+void aniso_turns_shape(int nx, int ny, int nz, int &g, int &nt)
+{
+    int most = nx > ny ? nx : ny;
+    if (nz > most) most = nz;
+    const int regs = turns_class(most);
+    const size_t cube_bytes = (size_t)nx * aniso_pyz(ny, nz) * sizeof(T);
+    g = nt = 0;
+    double best = 0;
+    for (int lanes = 64; lanes <= ANISO_MAX_NT; lanes += 64)
+        for (int c = 1; c <= 64 && c * cube_bytes <= 48 * 1024; ++c) {
+            if (ceil_div(c * ny * nz, lanes) * nx > regs || ceil_div(c * nx * ny, lanes) * nz > regs) break;
+            const double use = aniso_lane_use(nx, ny, nz, c, lanes);
+            if (use > best + 1e-9) {
+                best = use;
+                g = c;
+                nt = lanes;
+            }
+        }
+}
+
+// Whether the turns kernel is the faster one, given the lane use q of the one-turn kernel over its own.  From the times
+// of 140 shapes at 4 .. 800 MB: turns / one turn in fp32 0.51 .. 0.73 for q <= 0.4 and 0.68 .. 0.93 for q <= 0.8 at 800 MB, 0.60 .. 0.82
+// and 0.79 .. 1.02 at 100 MB, 0.68 .. 0.93 for q <= 0.4 at 40 MB; in fp64, q <= 0.4: 0.47 .. 0.98 at 800 MB, 0.61 .. 1.06 at 100 MB;
+// q <= 0.6 where an axis has more than 12 points (four wavefronts per SIMD in the one-turn kernel) 0.83 .. 0.97 at 800 MB,
+// elsewhere 0.9 .. 1.06.  On smaller batches a launch is a few rounds of workgroups and the turns are only a longer chain: 0.9 .. 1.5.
+// Elements of 108 points and fewer stay ((12,3,3) 1.05, (3,12,3) 1.08), and in fp64 those of less than 300 until 256 MiB
+// ((14,4,4) 1.05 at 100 MB, 0.92 at 300).
+template <typename T>
+bool turns_pay(const AnisoArgs &a, int g1, int nt1, int &g, int &nt)
+{
+    const int points = a.nx * a.ny * a.nz;
+    const long long mib = 3LL * a.num_elems * points * (long long)sizeof(T) >> 20;
+    if (points < 112 || mib < (sizeof(T) == 4 ? 32 : points < 300 ? 256 : 64)) return false;
+    aniso_turns_shape<T>(a.nx, a.ny, a.nz, g, nt);
+    if (g == 0) return false;
+    const double q = aniso_lane_use(a.nx, a.ny, a.nz, g1, nt1) / aniso_lane_use(a.nx, a.ny, a.nz, g, nt);
+    if (q <= 0.4) return true;
+    const bool wide = a.nx > 12 || a.ny > 12 || a.nz > 12;
+    if (sizeof(T) == 8) return wide && q <= 0.6 && mib >= 256;
+    return q <= 0.8 && mib >= 96;
+}
+
+template <typename T, int MAXN>
+hipError_t launch_turns(const AnisoArgs &a, int g, int nt)
+{
+    const long long groups = (a.num_elems + g - 1) / g;
+    auto inverse = [](int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); };
+    const AnisoTurns sh{a.nx, a.ny, a.nz, g, inverse(a.ny * a.nz), inverse(a.nx * a.nz), inverse(a.nx * a.ny),
+                        inverse(a.ny), inverse(a.nz)};
+    drop_stale_error();
+    hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, ANISO_HINT, ANISO_XCD>),
+                       dim3((unsigned)pencil_grid<ANISO_XCD>(groups)), dim3(nt),
+                       (size_t)g * a.nx * aniso_pyz(a.ny, a.nz) * sizeof(T), a.stream,
+                       (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
+                       (const T *)a.d, (T *)a.v, sh, a.num_elems, groups);
+    return hipGetLastError();
+}
+
+template <typename T, int MAXN>
+hipError_t launch_bound(const AnisoArgs &a, int g, int nt, size_t lds)
+{
     const long long groups = (a.num_elems + g - 1) / g;
     drop_stale_error();
     hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, ANISO_HINT, ANISO_XCD>),
@@ -228,10 +455,24 @@ hipError_t launch_generic(const AnisoArgs &a)
     if (a.num_elems <= 0 || a.num_elems > 0x7fffffffLL) return kGridTooLarge;
     int n = a.nx > a.ny ? a.nx : a.ny;
     if (a.nz > n) n = a.nz;
-    if (n <= 4) return launch_bound<T, 4>(a);
-    if (n <= 8) return launch_bound<T, 8>(a);
-    if (n <= 12) return launch_bound<T, 12>(a);
-    return launch_bound<T, 16>(a);
+    int g, nt, gt, ntt;
+    size_t lds;
+    aniso_shape<T>(a, g, nt, lds);
+    if (sizeof(T) == 4 && slice_kernel_pays(a.nx, a.ny, a.nz, a.num_elems, g, nt / 64))
+        return launch_ihelm_slice(a);
+    if (turns_pay<T>(a, g, nt, gt, ntt)) {
+        switch (turns_class(n)) {
+        case 8: return launch_turns<T, 8>(a, gt, ntt);
+        case 10: return launch_turns<T, 10>(a, gt, ntt);
+        case 12: return launch_turns<T, 12>(a, gt, ntt);
+        case 14: return launch_turns<T, 14>(a, gt, ntt);
+        default: return launch_turns<T, 16>(a, gt, ntt);
+        }
+    }
+    if (n <= 4) return launch_bound<T, 4>(a, g, nt, lds);
+    if (n <= 8) return launch_bound<T, 8>(a, g, nt, lds);
+    if (n <= 12) return launch_bound<T, 12>(a, g, nt, lds);
+    return launch_bound<T, 16>(a, g, nt, lds);
 }
 
 }  // namespace
@@ -254,4 +495,25 @@ extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype,
     size_t lds;
     tpo::aniso_shape<float>(a, g, nt, lds);
     return tpo::slice_kernel_pays(nx, ny, nz, num_elems, g, nt / 64);
+}
+
+// 0: one turn per pass (or the slice kernel); else 1000 * elements + lanes per workgroup of the turns kernel.
+extern "C" int tpo_internal_aniso_turns(int nx, int ny, int nz, int dtype, long long num_elems)
+{
+    tpo::AnisoArgs a = {};
+    a.nx = nx;
+    a.ny = ny;
+    a.nz = nz;
+    a.num_elems = num_elems;
+    int g, nt, gt = 0, ntt = 0;
+    size_t lds;
+    bool turns;
+    if (dtype == TPO_F64) {
+        tpo::aniso_shape<double>(a, g, nt, lds);
+        turns = tpo::turns_pay<double>(a, g, nt, gt, ntt);
+    } else {
+        tpo::aniso_shape<float>(a, g, nt, lds);
+        turns = !tpo::slice_kernel_pays(nx, ny, nz, num_elems, g, nt / 64) && tpo::turns_pay<float>(a, g, nt, gt, ntt);
+    }
+    return turns ? 1000 * gt + ntt : 0;
 }

@@ -1,0 +1,92 @@
+"""GPU parity of the anisotropic kernel whose passes run in turns, against plain fp64 products on the device and the
+CPU oracle: in every register class the shape with the most turns in a pass, one with the fewest elements per workgroup and
+one with the most, on the smallest batch that takes it, which leaves a ragged last workgroup.  Each case asks the
+library that the call does run in turns.  Bars as for the anisotropic operator: six sums of at most 16 terms."""
+import ctypes
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TOL, dev
+from paper_2604_19906_amd import tpo
+from paper_2604_19906_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DTYPES = {"f64": (tpo.TPO_F64, torch.float64, 8), "f32": (tpo.TPO_F32, torch.float32, 4)}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    yield
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
+
+
+def turns(dims, dtype, e):
+    fn = tpo.lib().tpo_internal_aniso_turns
+    fn.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
+    return divmod(fn(*dims, DTYPES[dtype][0], e), 1000)
+
+
+def batch(dims, dtype):
+    """The smallest batch that runs in turns with a ragged last workgroup (0: none of up to 260 MiB does)."""
+    for mib in (32, 64, 96, 256):
+        e = -(-(mib << 20) // (3 * dims[0] * dims[1] * dims[2] * DTYPES[dtype][2]))
+        g = turns(dims, dtype, e)[0]
+        if g:
+            return e if g == 1 or e % g else e + 1
+    return 0
+
+
+def shapes(dtype, regs):
+    found = []
+    for dims in itertools.product(range(1, regs + 1), repeat=3):
+        if len(set(dims)) == 1 or max(8, (max(dims) + 1) // 2 * 2) != regs:
+            continue
+        e = batch(dims, dtype)
+        if e:
+            g, lanes = turns(dims, dtype, e)
+            nx, ny, nz = dims
+            found.append((max(-(-g * p // lanes) for p in (ny * nz, nx * nz, nx * ny)), g, dims))
+    return sorted({max(found)[2], min(found, key=lambda f: f[1])[2], max(found, key=lambda f: f[1])[2]})
+
+
+def along(x, m, axis):
+    x = x.movedim(axis, 3)
+    return (x.reshape(-1, x.shape[3]) @ m).reshape(x.shape).movedim(3, axis)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("regs", [8, 10, 12, 14, 16])
+def test_turns(dtype, regs):
+    assert shapes(dtype, regs)
+    for dims in shapes(dtype, regs):
+        e = batch(dims, dtype)
+        print(f"case turns {dtype} dims={dims} E={e} {turns(dims, dtype, e)}", flush=True)
+        rng = np.random.default_rng([19906, 81, *dims])
+        real = np.float64 if dtype == "f64" else np.float32
+        mats = [dev(wl.orthogonal_matrix(n, rng).astype(real)) for n in dims]
+        gen = torch.Generator(device="cuda").manual_seed(100 * dims[0] + 10 * dims[1] + dims[2])
+        field = lambda lo, hi: torch.empty((e, *dims), device="cuda", dtype=DTYPES[dtype][1]).uniform_(lo, hi, generator=gen)
+        u, d = field(-1, 1), field(0.03, 3.3)
+        out = torch.full_like(u, float("nan"))
+        tpo.apply_aniso_tensors(u, *mats, d, v=out)
+        torch.cuda.synchronize()
+        f, m64 = u.double(), [m.double() for m in mats]
+        for axis in (1, 2, 3):
+            f = along(f, m64[axis - 1], axis)
+        f = f * d.double()
+        for axis in (1, 2, 3):
+            f = along(f, m64[axis - 1].t().contiguous(), axis)
+        err = (out.double() - f).abs().flatten(1).max(dim=1).values / f.abs().flatten(1).max(dim=1).values
+        assert float(err.max()) <= TOL[dtype]               # a NaN left in the output fails this too
+        tail = slice(e - 70, e)
+        ref = oracle.ihelm_apply_aniso(*(x.cpu().numpy() for x in (u[tail], *mats, d[tail])))
+        assert oracle.max_rel_err_per_element(out[tail].cpu().numpy(), ref) <= TOL[dtype]
+        tpo.apply_aniso_tensors(u, *mats, d, v=u)            # in place
+        torch.cuda.synchronize()
+        assert torch.equal(u, out)
