@@ -9,7 +9,9 @@
 // time (for the unrolled FMAs and the batched scalar loads of the matrix); the other two sizes
 // only enter pencil counts and strides, which may be runtime values.  So every product is a
 // uniform switch over the size of its axis, and the kernel is compiled once per size class
-// (largest of the three sizes at most 4, 8, 12 or 16: the class bounds the registers).
+// (largest of the three sizes at most 4, 8, 12 or 16, in fp64 also 10, in fp32 6: the class bounds the registers; with
+// the class of 10 fp64 shapes of 9 and 10 points keep six wavefronts per SIMD instead of five, 0.94 .. 0.98 of
+// the time; a class of 14 changes nothing, four wavefronts per SIMD either way, and five cost spills, 1.05 .. 1.20).
 //
 // Order of the products, as in the pencil kernels: axis 0 first, on words read coalesced from
 // u_e (for a fixed index along axis 0 the lanes of that pass are consecutive words), axis 1,
@@ -28,12 +30,22 @@ namespace tpo {
 namespace {
 
 constexpr int ANISO_MAX_NT = 256;
-// Non-temporal stores of v_e, workgroups renumbered per die: the best or within 2 % of the best
-// of a sweep over eight shapes on MI355X (hint bits x renumbering x elements per workgroup x LDS
-// floor).  Non-temporal loads of u_e as well measured the same rate on average with 5 % more
-// HBM reads (the 32-byte pieces two rows of a pass share are then fetched twice).
-constexpr int ANISO_HINT = 2;
-constexpr bool ANISO_XCD = true;
+// Hints and die renumbering: non-temporal stores of v_e and workgroups renumbered per die, or (STREAM) non-temporal
+// loads of u_e as well and no renumbering.  STREAM over the other in fp64, geometric means over 120 shapes: 0.93 at 52 and 60 MB,
+// 0.98 at 150, 0.96 at 300, 0.97 at 800 MB; 1.00 .. 1.02 with maxima of 1.09 at 100 and 130 MB (fields that the
+// last-level cache holds in part) and at 2.5 GB, 1.0 .. 1.1 at 30 MB, up to 1.07 on elements of less than 128 points and at 50 MB
+// of less than 300.  In fp32 1.00, up to 1.24 on faces of a dozen points: not there.
+constexpr int aniso_hint(bool stream) { return stream ? 3 : 2; }
+constexpr bool aniso_xcd(bool stream) { return !stream; }
+template <typename T>
+bool aniso_stream(const AnisoArgs &a, bool turns)
+{
+    const int points = a.nx * a.ny * a.nz;
+    const long long mib = 3LL * a.num_elems * points * (long long)sizeof(T) >> 20;
+    if (sizeof(T) == 4) return false;
+    if (!turns && mib >= 48 && mib < 80) return points >= 300;
+    return points >= 128 && mib >= 144 && mib < 1536;
+}
 
 // f(integral_constant<int, n>) for the runtime n in 1 .. MAXN (uniform over the workgroup).
 template <int MAXN, typename F>
@@ -421,16 +433,16 @@ bool turns_pay(const AnisoArgs &a, int g1, int nt1, int &g, int &nt)
     return q <= 0.8 && mib >= 96;
 }
 
-template <typename T, int MAXN>
-hipError_t launch_turns(const AnisoArgs &a, int g, int nt)
+template <typename T, int MAXN, bool STREAM>
+hipError_t launch_turns_as(const AnisoArgs &a, int g, int nt)
 {
     const long long groups = (a.num_elems + g - 1) / g;
     auto inverse = [](int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); };
     const AnisoTurns sh{a.nx, a.ny, a.nz, g, inverse(a.ny * a.nz), inverse(a.nx * a.nz), inverse(a.nx * a.ny),
                         inverse(a.ny), inverse(a.nz)};
     drop_stale_error();
-    hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, ANISO_HINT, ANISO_XCD>),
-                       dim3((unsigned)pencil_grid<ANISO_XCD>(groups)), dim3(nt),
+    hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
+                       dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt),
                        (size_t)g * a.nx * aniso_pyz(a.ny, a.nz) * sizeof(T), a.stream,
                        (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
                        (const T *)a.d, (T *)a.v, sh, a.num_elems, groups);
@@ -438,15 +450,31 @@ hipError_t launch_turns(const AnisoArgs &a, int g, int nt)
 }
 
 template <typename T, int MAXN>
-hipError_t launch_bound(const AnisoArgs &a, int g, int nt, size_t lds)
+hipError_t launch_turns(const AnisoArgs &a, int g, int nt)
+{
+    if constexpr (sizeof(T) == 8)
+        if (aniso_stream<T>(a, true)) return launch_turns_as<T, MAXN, true>(a, g, nt);
+    return launch_turns_as<T, MAXN, false>(a, g, nt);
+}
+
+template <typename T, int MAXN, bool STREAM>
+hipError_t launch_bound_as(const AnisoArgs &a, int g, int nt, size_t lds)
 {
     const long long groups = (a.num_elems + g - 1) / g;
     drop_stale_error();
-    hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, ANISO_HINT, ANISO_XCD>),
-                       dim3((unsigned)pencil_grid<ANISO_XCD>(groups)), dim3(nt), lds, a.stream,
+    hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
+                       dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt), lds, a.stream,
                        (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
                        (const T *)a.d, (T *)a.v, a.nx, a.ny, a.nz, g, a.num_elems, groups);
     return hipGetLastError();
+}
+
+template <typename T, int MAXN>
+hipError_t launch_bound(const AnisoArgs &a, int g, int nt, size_t lds)
+{
+    if constexpr (sizeof(T) == 8)
+        if (aniso_stream<T>(a, false)) return launch_bound_as<T, MAXN, true>(a, g, nt, lds);
+    return launch_bound_as<T, MAXN, false>(a, g, nt, lds);
 }
 
 template <typename T>
@@ -470,7 +498,9 @@ hipError_t launch_generic(const AnisoArgs &a)
         }
     }
     if (n <= 4) return launch_bound<T, 4>(a, g, nt, lds);
+    if (sizeof(T) == 4 && n <= 6) return launch_bound<T, 6>(a, g, nt, lds);
     if (n <= 8) return launch_bound<T, 8>(a, g, nt, lds);
+    if (sizeof(T) == 8 && n <= 10) return launch_bound<T, 10>(a, g, nt, lds);
     if (n <= 12) return launch_bound<T, 12>(a, g, nt, lds);
     return launch_bound<T, 16>(a, g, nt, lds);
 }
