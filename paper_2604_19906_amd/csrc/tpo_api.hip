@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "tpo.h"
+#include "tpo_batch_rows.hpp"
 #include "tpo_internal.h"
 
 namespace {
@@ -15,7 +16,7 @@ std::mutex g_mu;
 int g_refs[kMaxDevices] = {0};
 
 // Family chosen by TPO_VARIANT_AUTO, from measurements on MI355X.
-int auto_variant(int n, int dtype, bool shared_s, long long num_elems)
+int auto_variant(int n, int dtype, bool shared_s, long long num_elems, bool sep)
 {
     // Measured on MI355X at the sizes of the named workloads (ms per launch, pencil / MFMA):
     // fp64 n=8 0.25 / 0.27, n=11 1.46 / 1.69, fp32 n=13 5.99 / 6.09: pencil.
@@ -24,8 +25,14 @@ int auto_variant(int n, int dtype, bool shared_s, long long num_elems)
     // matrices.  With a shared matrix the matrix-core kernel leads at every batch size (us per
     // launch, pencil / MFMA: E = 1024 26.2 / 22.1, 2048 46.2 / 36.4, 4096 80.9 / 77.1, 8192 148.5 /
     // 145.4, 12288 236 / 220, 16384 311 / 292), so the choice does not depend on num_elems.
-    (void)num_elems;
     if (dtype == TPO_F64 && n == 16 && shared_s) return TPO_VARIANT_MFMA;
+    // fp64, one workgroup per CU or less: the tiles load their matrices at once into registers, the pencils wait for
+    // scalar loads that miss with every matrix (time of the tiles over the pencils', three matrices / one: n = 11 0.91 / 0.96,
+    // 12 0.85 / 0.84, 13 0.95 / 0.95, 14 0.94 / 1.03, 15 0.90 / 1.00; separable 0.83, 0.86, 0.94, 0.93, 0.86 / 0.86 .. 1.02).
+    // n = 16 with three matrices 0.77 .. 0.95 up to 450 MB of fields (0.76 up to 12 MB, then 1.0 .. 1.1 in the separable form).
+    if (dtype == TPO_F64 && num_elems <= 256 && n >= 11 && n <= 15 && (!shared_s || n == 12 || n == 13))
+        return TPO_VARIANT_MFMA;
+    if (dtype == TPO_F64 && n == 16 && num_elems <= (sep ? 256 : 4096)) return TPO_VARIANT_MFMA;
     // fp32: with 4x4x1 matrix-core products the pencil kernel leaves the vector-FMA bound
     // (n=13, E=1048576: 5.5 against 6.0 ms).  All three families on 1 GiB fields, every n, each at
     // its best setting (GB/s, vector-FMA pencil / 4x4x1 pencil / MFMA tiles): n=8 6079/5853/4790,
@@ -33,8 +40,13 @@ int auto_variant(int n, int dtype, bool shared_s, long long num_elems)
     // n=14 3748/3990/4071, n=15 3873/4361/4607, n=16 4012/4878/5599: vector FMA up to n=7, the
     // 4x4x1 kernels for n=8..13 (n=8 with non-temporal u loads and stores: 6181/6401), the
     // 16-wide tiles once n fills them (n >= 14).
+    // With the present coefficient tables and rows by batch the 4x4x1 kernels lead at n = 14 on everything measured
+    // (1 MB .. 2.5 GB: 0.66 .. 0.95 of the tiles' time, separable 0.67 .. 0.95), at n = 15 up to 900 MB (0.87 .. 1.00, separable 0.91 ..
+    // 0.98), and at n = 7 they pass the vector kernels from 10 MB on (0.86 .. 0.96, separable 0.84 .. 0.96 at all sizes).
+    if (dtype == TPO_F32 && n == 14 && num_elems <= 100000) return TPO_VARIANT_PENCIL_MM;
+    if (dtype == TPO_F32 && n == 15 && num_elems <= (sep ? 40000 : 24000)) return TPO_VARIANT_PENCIL_MM;
     if (dtype == TPO_F32 && n >= 14) return TPO_VARIANT_MFMA;
-    if (dtype == TPO_F32 && n >= 8) return TPO_VARIANT_PENCIL_MM;
+    if (dtype == TPO_F32 && (n >= 8 || (n == 7 && (sep || num_elems > 2292)))) return TPO_VARIANT_PENCIL_MM;
     return TPO_VARIANT_PENCIL;
 }
 
@@ -140,7 +152,7 @@ int tpo_ihelm_variant_for_batch(int n, int dtype, int shared_s, long long num_el
     if (dtype != TPO_F64 && dtype != TPO_F32) return TPO_ERR_INVALID_ARG;
     if (n < 1 || num_elems < 0) return TPO_ERR_INVALID_ARG;
     if (n > TPO_MAX_N) return TPO_ERR_UNSUPPORTED;
-    int var = auto_variant(n, dtype, shared_s != 0, num_elems);
+    int var = auto_variant(n, dtype, shared_s != 0, num_elems, false);
     if (!lookup(n, dtype, var)) var = TPO_VARIANT_PENCIL;
     return var;
 }
@@ -221,7 +233,7 @@ int tpo_ihelm_sep_variant_for_batch(int n, int dtype, int shared_s, long long nu
     // on MI355X (ms per launch, best pencil family / matrix-core tiles): fp64 n=16, E=65536, one
     // shared matrix 1.112 / 1.052; fp32, E=262144: n=14 2.038 / 2.029, n=15 2.323 / 2.203,
     // n=16 2.407 / 2.070.
-    int var = auto_variant(n, dtype, shared_s != 0, num_elems);
+    int var = auto_variant(n, dtype, shared_s != 0, num_elems, true);
     const tpo::KernelEntry *k = lookup(n, dtype, var);
     if (!k || !k->launch_sep)
         var = (dtype == TPO_F32 && n >= 8) ? TPO_VARIANT_PENCIL_MM : TPO_VARIANT_PENCIL;
@@ -307,3 +319,21 @@ const char *tpo_status_string(int status)
 }
 
 }  // extern "C"
+
+// The row of launch settings that a batch takes (-1: past the rows).  list: 0 operator, 1 separable form, 2 and 3 the same
+// in the 4x4x1 kernels, 4 transform halves.
+extern "C" int tpo_internal_batch_row(int list, int n, int dtype, long long num_elems)
+{
+    if (n < 1 || n > TPO_MAX_N || list < 0 || list > 4) return -1;
+    const bool f64 = dtype == TPO_F64;
+    const tpo::BatchRows &rows =
+        list == 0 ? (f64 ? tpo::PencilRows<double>::rows : tpo::PencilRows<float>::rows)
+        : list == 1 ? (f64 ? tpo::PencilSepRows<double>::rows : tpo::PencilSepRows<float>::rows)
+        : list == 2 ? tpo::PencilMmRows::rows
+        : list == 3 ? tpo::PencilMmSepRows::rows
+                    : (f64 ? tpo::TransformRows<double>::rows : tpo::TransformRows<float>::rows);
+    const long long per_elem = (list == 0 || list == 2 ? 3LL : 2LL) * n * n * n * (f64 ? 8 : 4);
+    for (int k = 0; k < tpo::kBatchRows && rows.row[n][k].mib > 0; ++k)
+        if (num_elems <= ((long long)rows.row[n][k].mib << 20) / per_elem) return k;
+    return -1;
+}

@@ -1,0 +1,206 @@
+// Launch settings by the size of the batch.  Each kernel family has a setting for large batches (its tuning
+// table) and, per type and n, up to four rows before it: a batch whose fields take at most `mib` MiB takes the
+// first row that it fits.
+//
+// Why the size decides: up to a dozen MiB a launch is one round of workgroups and the fewest elements per workgroup
+// finish first; up to about 130 MB of fields non-temporal stores (hint 2) leave the last-level cache (256 MB) to the inputs
+// of the next calls; up to about half a GB the fields are cached in part, and loads that pass the cache too (hint 3)
+// and smaller workgroups lead; beyond, the steady stream decides.  fp64 products of n >= 9 and the fp64 halves take longer batches
+// of scalar loads (SB = 40 words) on batches of that middle range.
+//
+// The rows are the best of 15 .. 20 settings per n at 19 sizes from 1 MB to 2.5 GB, three sets of fields in turn (a row
+// has to gain 6 to 8 % summed over its sizes), MI355X; time over the settings for large and small batches that were there before:
+//   operator fp64    n = 3 .. 6 0.73 .. 0.98 up to 130 MB; n = 8 0.85 .. 0.91 at 64 .. 300 MB; n = 9, 11 0.84 .. 0.94 at 25 .. 220 MB;
+//                    n = 12 0.79 .. 0.82 up to 8 MB, 0.84 .. 0.89 at 80 .. 220 MB; n = 13 0.71 .. 0.91 up to 450 MB; n = 14, 15 0.75 .. 0.95 at 35 .. 450 MB
+//   separable fp64   n = 2 .. 6 0.69 .. 0.92 up to 170 MB; n = 9, 11 0.80 .. 0.93 at 12 .. 220 MB; n = 12 0.71 .. 0.94 up to 64 MB; n = 13 .. 15
+//                    0.78 .. 0.93 at 35 .. 300 MB
+//   operator fp32    n = 9 .. 11, 13 0.84 .. 0.95 at 18 .. 170 MB; n = 13 0.80 up to 4 MB
+//   separable fp32   n = 2 .. 6 0.63 .. 0.92 at 12 .. 170 MB; n = 9, 10 0.85 .. 0.94
+//   halves           fp64 n = 3, 5, 9 .. 15 0.68 .. 0.93 at 25 .. 170 MB, n = 10 .. 13 0.91 .. 0.96 at 300 MB .. 1.2 GB; fp32 n = 3, 5, 6,
+//                    10, 11, 13 .. 15 0.66 .. 0.9 at 100 .. 170 MB
+#pragma once
+
+#include <type_traits>
+
+#include "tpo.h"
+
+namespace tpo {
+
+// sb: words per batch of scalar loads (matrix_product); mm: 4x4x1 matrix-core form (halves in fp32).
+struct BatchRow { int mib, g, hint, xcd, sb, mm; };
+constexpr int kBatchRows = 4;                   // a row with mib = 0 ends the list
+struct BatchRows { BatchRow row[TPO_MAX_N + 1][kBatchRows]; };
+
+// Operator, vector-FMA kernels.
+template <typename T> struct PencilRows;
+template <> struct PencilRows<double> {
+    static constexpr BatchRows rows = {{
+        {}, {},
+        /* 2 */ {{85, 16, 0, 0, 32}},
+        /* 3 */ {{1650, 24, 2, 0, 32}},
+        /* 4 */ {{142, 8, 2, 0, 32}},
+        /* 5 */ {{5, 16, 0, 0, 32}, {874, 8, 2, 0, 32}},
+        /* 6 */ {{14, 3, 0, 0, 32}, {85, 3, 2, 0, 32}, {350, 1, 3, 1, 32}},
+        /* 7 */ {{14, 1, 0, 0, 32}},
+        /* 8 */ {{39, 1, 3, 0, 32}, {142, 1, 2, 0, 0}, {350, 1, 3, 1, 0}},
+        /* 9 */ {{14, 1, 0, 0, 32}, {39, 3, 3, 0, 32}, {142, 3, 2, 0, 40}, {245, 2, 3, 0, 40}},
+        /* 10 */ {{85, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
+        /* 11 */ {{14, 1, 0, 0, 32}, {39, 1, 3, 0, 32}, {184, 2, 2, 0, 40}, {1650, 2, 3, 0, 32}},
+        /* 12 */ {{53, 1, 3, 0, 32}, {68, 3, 3, 0, 32}, {350, 1, 3, 0, 40}},
+        /* 13 */ {{14, 1, 0, 0, 32}, {53, 1, 3, 1, 32}, {535, 1, 2, 0, 40}, {1650, 3, 1, 0, 40}},
+        /* 14 */ {{53, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
+        /* 15 */ {{20, 1, 0, 0, 32}, {53, 1, 3, 1, 32}, {350, 1, 2, 0, 40}, {535, 1, 3, 0, 32}},
+        /* 16 */ {{53, 1, 3, 0, 32}, {142, 2, 2, 0, 40}, {535, 1, 3, 1, 40}},
+    }};
+};
+template <> struct PencilRows<float> {
+    static constexpr BatchRows rows = {{
+        {}, {},
+        /* 2 */ {{9, 16, 0, 0, 32}},
+        /* 3 */ {{14, 32, 0, 0, 32}, {85, 6, 0, 0, 32}},
+        /* 4 */ {{14, 8, 2, 0, 32}, {184, 3, 2, 0, 32}},
+        /* 5 */ {{14, 2, 0, 0, 32}},
+        /* 6 */ {{53, 6, 2, 0, 32}, {350, 3, 3, 0, 32}},
+        /* 7 */ {{14, 1, 0, 0, 32}},
+    }};
+};
+// Separable form, vector-FMA kernels.
+template <typename T> struct PencilSepRows;
+template <> struct PencilSepRows<double> {
+    static constexpr BatchRows rows = {{
+        {}, {},
+        /* 2 */ {{14, 32, 0, 0, 32}},
+        /* 3 */ {{53, 6, 2, 0, 32}, {142, 16, 2, 0, 32}, {1650, 24, 2, 0, 32}},
+        /* 4 */ {{5, 6, 2, 0, 32}, {142, 8, 2, 0, 32}},
+        /* 5 */ {{9, 16, 0, 0, 32}, {245, 2, 2, 0, 32}},
+        /* 6 */ {{535, 3, 2, 0, 32}},
+        /* 7 */ {{9, 1, 1, 0, 32}},
+        {},
+        /* 9 */ {{5, 2, 0, 0, 32}, {53, 3, 2, 0, 32}, {184, 2, 3, 0, 32}, {350, 3, 3, 0, 32}},
+        {},
+        /* 11 */ {{9, 1, 1, 0, 32}, {85, 1, 2, 0, 32}, {535, 2, 3, 0, 32}},
+        /* 12 */ {{53, 1, 3, 0, 32}},
+        /* 13 */ {{9, 1, 0, 0, 32}, {245, 1, 3, 0, 32}, {535, 3, 3, 0, 32}},
+        /* 14 */ {{245, 1, 3, 0, 32}},
+        /* 15 */ {{14, 1, 0, 0, 32}, {535, 1, 3, 0, 32}},
+        {},
+    }};
+};
+template <> struct PencilSepRows<float> {
+    static constexpr BatchRows rows = {{
+        {}, {},
+        /* 2 */ {{184, 32, 2, 0, 32}},
+        /* 3 */ {{245, 12, 2, 0, 32}},
+        /* 4 */ {{5, 2, 2, 0, 32}, {245, 4, 2, 0, 32}},
+        /* 5 */ {{9, 2, 0, 0, 32}, {874, 2, 2, 0, 32}},
+        /* 6 */ {{245, 6, 2, 0, 32}},
+    }};
+};
+// fp32 kernels with 4x4x1 matrix-core products: operator, separable form.
+struct PencilMmRows {
+    static constexpr BatchRows rows = {{
+        {}, {}, {}, {}, {}, {}, {},
+        /* 7 */ {{142, 2, 2, 1}, {350, 1, 3, 0}},
+        /* 8 */ {{142, 1, 2, 0}},
+        /* 9 */ {{14, 3, 0, 0}, {142, 3, 2, 1}, {245, 3, 3, 0}},
+        /* 10 */ {{20, 2, 0, 0}, {142, 3, 2, 1}, {535, 3, 3, 0}},
+        /* 11 */ {{14, 2, 0, 0}, {142, 2, 2, 1}, {245, 2, 3, 0}, {1650, 4, 0, 0}},
+        /* 12 */ {{5, 1, 0, 0}},
+        /* 13 */ {{9, 1, 0, 0}, {20, 3, 0, 0}, {184, 3, 2, 0}},
+        /* 14 */ {{14, 1, 0, 0}, {245, 1, 2, 0}},
+        /* 15 */ {{14, 1, 0, 0}},
+        {},
+    }};
+};
+struct PencilMmSepRows {
+    static constexpr BatchRows rows = {{
+        {}, {}, {}, {}, {}, {}, {}, {},
+        /* 8 */ {{53, 1, 2, 0}, {350, 4, 2, 0}},
+        /* 9 */ {{14, 3, 0, 0}, {245, 3, 2, 0}},
+        /* 10 */ {{14, 2, 0, 0}, {39, 3, 2, 0}, {1650, 4, 2, 0}},
+        /* 11 */ {{9, 2, 0, 0}, {874, 2, 2, 0}},
+        /* 12 */ {{2, 1, 0, 0}},
+        /* 13 */ {{9, 1, 0, 0}, {14, 3, 0, 0}, {350, 3, 2, 0}},
+        /* 14 */ {{9, 1, 0, 0}, {53, 1, 2, 0}},
+        /* 15 */ {{9, 1, 0, 0}},
+        {},
+    }};
+};
+// Transform halves.
+template <typename T> struct TransformRows;
+template <> struct TransformRows<double> {
+    static constexpr BatchRows rows = {{
+        {}, {}, {},
+        /* 3 */ {{2, 32, 0, 0, 32}, {184, 4, 2, 1, 32}, {350, 24, 2, 0, 32}},
+        /* 4 */ {{14, 2, 2, 1, 32}, {53, 4, 2, 0, 32}, {245, 3, 2, 0, 32}},
+        /* 5 */ {{5, 16, 0, 0, 32}, {85, 2, 2, 1, 32}, {245, 1, 2, 1, 32}},
+        {},
+        /* 7 */ {{2, 1, 2, 0, 32}, {53, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
+        /* 8 */ {{53, 1, 2, 0, 32}, {1650, 1, 2, 0, 40}},
+        /* 9 */ {{20, 2, 0, 0, 32}, {245, 1, 2, 0, 40}, {1024, 1, 0, 0, 40}},
+        /* 10 */ {{5, 1, 2, 0, 32}, {184, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
+        /* 11 */ {{14, 1, 0, 1, 32}, {184, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
+        /* 12 */ {{1650, 1, 2, 0, 40}},
+        /* 13 */ {{9, 1, 0, 0, 40}, {53, 1, 2, 0, 40}, {184, 3, 2, 0, 40}, {1650, 2, 0, 0, 40}},
+        /* 14 */ {{535, 1, 2, 0, 40}},
+        /* 15 */ {{350, 1, 2, 0, 40}},
+        /* 16 */ {{53, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
+    }};
+};
+template <> struct TransformRows<float> {
+    static constexpr BatchRows rows = {{
+        {}, {}, {},
+        /* 3 */ {{53, 12, 2, 0, 32}, {245, 24, 2, 0, 32}},
+        /* 4 */ {{245, 12, 2, 0, 32}},
+        /* 5 */ {{245, 2, 2, 1, 32}},
+        /* 6 */ {{9, 12, 2, 0, 32}, {68, 6, 2, 0, 32}, {535, 4, 2, 0, 32}},
+        /* 7 */ {{9, 1, 2, 1, 32}, {184, 1, 2, 1, 0, 1}},
+        /* 8 */ {{2, 2, 2, 0, 0, 1}, {39, 3, 2, 0, 0, 1}, {245, 3, 2, 1, 0, 1}},
+        /* 9 */ {{85, 3, 0, 0, 0, 1}, {184, 2, 2, 1, 0, 1}},
+        /* 10 */ {{184, 2, 2, 0, 0, 1}, {1650, 2, 0, 0, 32, 0}},
+        /* 11 */ {{39, 1, 2, 1, 0, 1}, {85, 2, 0, 0, 0, 1}, {184, 1, 2, 1, 0, 1}, {1650, 2, 0, 0, 32, 0}},
+        /* 12 */ {{9, 3, 2, 1, 0, 1}, {39, 2, 2, 0, 0, 1}, {640, 3, 2, 0, 0, 1}},
+        /* 13 */ {{184, 1, 2, 1, 0, 1}},
+        /* 14 */ {{874, 1, 2, 0, 0, 1}},
+        /* 15 */ {{14, 1, 0, 0, 0, 1}, {184, 1, 2, 0, 0, 1}},
+        {},
+    }};
+};
+
+// f(integral_constant<int, K>) for the first row K of n that a batch of num_elems elements (bytes_per_elem of
+// fields each) fits; f returns its result.  False: past the rows.
+template <const BatchRows &ROWS, int N, int K = 0, typename F>
+inline bool for_batch_row(long long num_elems, long long bytes_per_elem, F &&f)
+{
+    if constexpr (K < kBatchRows) {
+        if constexpr (ROWS.row[N][K].mib > 0) {
+            if (num_elems <= ((long long)ROWS.row[N][K].mib << 20) / bytes_per_elem) {
+                f(std::integral_constant<int, K>{});
+                return true;
+            }
+            return for_batch_row<ROWS, N, K + 1>(num_elems, bytes_per_elem, f);
+        }
+    }
+    return false;
+}
+template <const BatchRows &ROWS, int N, int K = 0, typename F>
+inline void for_each_batch_row(F &&f)
+{
+    if constexpr (K < kBatchRows) {
+        if constexpr (ROWS.row[N][K].mib > 0) {
+            f(std::integral_constant<int, K>{});
+            for_each_batch_row<ROWS, N, K + 1>(f);
+        }
+    }
+}
+
+// The row as a tuning of the vector-FMA operator kernels, of the 4x4x1 kernels and of the halves.
+template <const BatchRows &ROWS, int N, int K>
+struct BatchTune {
+    static constexpr BatchRow R = ROWS.row[N][K];
+    static constexpr int G = R.g, HINT = R.hint, SB = R.sb;
+    static constexpr bool DDIRECT = true, XCD = R.xcd != 0, MM = R.mm != 0;
+    static constexpr size_t LDS_MIN = 0;
+};
+
+}  // namespace tpo

@@ -108,7 +108,8 @@ int validate_apply_sep(const void *u, const void *sx, const void *sy, const void
 // For the tests (no GPU needed): whether tpo_ihelm_apply_aniso takes the slice kernel for this call, whether
 // the slice kernel is built for a class of shapes, the elements and lanes per workgroup it takes if its passes run
 // in turns (0: they do not), and which of their settings tpo_convection_apply and
-// tpo_transform_apply take for a batch (0 / 1; -1: no such shape).
+// tpo_transform_apply take for a batch past the rows of tpo_batch_rows.hpp (0 / 1; -1: no such shape); which of those rows.
+extern "C" int tpo_internal_batch_row(int list, int n, int dtype, long long num_elems);
 extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype, long long num_elems);
 extern "C" int tpo_internal_aniso_turns(int nx, int ny, int nz, int dtype, long long num_elems);
 extern "C" int tpo_internal_slice_class_built(int nx, int ksb, int ksc);

@@ -23,6 +23,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "tpo_batch_rows.hpp"
 #include "tpo_internal.h"
 
 namespace tpo {
@@ -390,7 +391,7 @@ template <typename T> struct PencilTable;
 template <> struct PencilTable<double> {
     static constexpr PencilRow row[TPO_MAX_N + 1] = {
         {0, 2, 1, 0},
-        {0, 2, 1, 1},  {16, 0, 1, 0}, {32, 0, 1, 0}, {4, 3, 0, 0},  {16, 0, 1, 0}, {1, 3, 1, 0},
+        {0, 2, 1, 1},  {16, 2, 1, 0}, {32, 0, 1, 0}, {4, 3, 0, 0},  {16, 0, 1, 0}, {1, 3, 1, 0},
         {1, 3, 1, 0},  {4, 3, 1, 0},  {3, 1, 1, 0},  {1, 3, 1, 0},  {1, 0, 1, 1},  {3, 3, 1, 0},
         {3, 0, 1, 0},  {1, 0, 1, 0},  {1, 0, 1, 0},  {1, 3, 1, 1},
     };
@@ -398,7 +399,7 @@ template <> struct PencilTable<double> {
 template <> struct PencilTable<float> {
     static constexpr PencilRow row[TPO_MAX_N + 1] = {
         {0, 2, 1, 0},
-        {0, 2, 1, 1},  {16, 0, 1, 0}, {32, 0, 1, 0}, {8, 2, 1, 0},  {16, 0, 1, 0}, {12, 0, 1, 0},
+        {0, 2, 1, 1},  {16, 2, 1, 0}, {24, 2, 1, 0}, {8, 2, 1, 0},  {8, 2, 1, 0}, {12, 0, 1, 0},
         {1, 3, 1, 1},  {2, 3, 1, 0},  {3, 0, 1, 0},  {2, 0, 1, 0},  {2, 0, 1, 0},  {3, 2, 1, 0},
         {3, 0, 1, 0},  {2, 0, 1, 0},  {2, 0, 1, 0},  {1, 3, 1, 0},
     };
@@ -426,43 +427,6 @@ template <> struct PencilTune<double, 11> {
     static constexpr bool DDIRECT = true, XCD = true;
     static constexpr size_t LDS_MIN = 28 * 1024;
     static constexpr int SB = kScalarBatch;
-};
-
-// Settings for small batches, used when LO < num_elems <= HI (HI = 0: never).  With a few
-// thousand workgroups the launch is a handful of rounds of resident workgroups: how the rounds
-// divide the batch and how fast a round drains count for more than the steady-state memory
-// behaviour the large-batch settings were chosen for.  From sweeps over E = 2048 .. 131072 on
-// MI355X (the batch of 8192 elements per call is the one the paper times, Sec. 6.1):
-//  * n = 11: up to 6144 elements one element per workgroup without die renumbering and occupancy
-//    cap is ahead (us per launch, against the large-batch settings: E = 1024 10.9 / 11.3, 4096
-//    27.0 / 29.0, 6144 38.4 / 38.4); beyond, the two leapfrog with the number of rounds of
-//    resident workgroups (8192 49.2 / 47.2, 12288 74.0 / 67.0, 16384 97.8 / 99.7, 24576 142.3 /
-//    142.3, 49152 277 / 281, 65536 368.5 / 367.1) and the large-batch settings are kept;
-//  * n = 9 (fp64): three elements per workgroup; non-temporal u_e loads pay from about 30000
-//    elements on (us per launch with / without them: E = 2048 11.6 / 11.1, 8192 28.3 / 27.2, 32768
-//    99.4 / 102.6, 184000 547 / 580; two elements per workgroup with cached loads, the earlier
-//    choice: 11.0, 28.5, 104.0, 569), so they are left out up to 16384 elements;
-//  * n = 8: between 4096 and 24576 elements one element per workgroup with cached accesses and
-//    D_e in its pencil layout beats four per workgroup (8192: 19.5 against 20.5 us, 16384: 33.2
-//    against 35.9); at 4096 and from 32768 on the large-batch settings win.
-template <typename T, int N>
-struct PencilSmallTune : PencilTune<T, N> {
-    static constexpr long long LO = 0, HI = 0;
-};
-template <> struct PencilSmallTune<double, 11> : PencilTune<double, 11> {
-    static constexpr int G = 1, HINT = 0;
-    static constexpr bool XCD = false;
-    static constexpr size_t LDS_MIN = 0;
-    static constexpr long long LO = 0, HI = 6144;
-};
-template <> struct PencilSmallTune<double, 9> : PencilTune<double, 9> {
-    static constexpr int HINT = 0;
-    static constexpr long long LO = 0, HI = 16384;
-};
-template <> struct PencilSmallTune<double, 8> : PencilTune<double, 8> {
-    static constexpr int G = 1, HINT = 0, SB = 0;       // (with batches of scalar loads 1.04 of the time)
-    static constexpr bool DDIRECT = true;
-    static constexpr long long LO = 4096, HI = 24576;
 };
 
 // Tuning of the separable-diagonal form: as the D form unless measured otherwise.  Without the
@@ -504,7 +468,7 @@ template <typename T, int N>
 struct PencilSepLargeTune : PencilSepTune<T, N> {};
 template <> struct PencilSepLargeTune<double, 3> : PencilSet<24, 0, false> {};
 template <> struct PencilSepLargeTune<double, 5> : PencilSet<2, 2, false> {};
-template <> struct PencilSepLargeTune<double, 6> : PencilSet<3, 0, true> {};
+template <> struct PencilSepLargeTune<double, 6> : PencilSet<3, 0, false> {};
 template <> struct PencilSepLargeTune<double, 9> : PencilSet<3, 0, false> {};
 template <> struct PencilSepLargeTune<float, 3> : PencilSet<24, 2, false> {};
 template <> struct PencilSepLargeTune<float, 4> : PencilSet<4, 2, false> {};
@@ -548,26 +512,37 @@ struct PencilLauncherT {
 template <typename T, int N>
 struct PencilLauncher {
     using Plain = PencilLauncherT<T, N, PencilTune<T, N>, 0>;
-    using Small = PencilLauncherT<T, N, PencilSmallTune<T, N>, 0>;
     using Sep = PencilLauncherT<T, N, PencilSepTune<T, N>, 2>;   // fast reciprocal
     using SepLarge = PencilLauncherT<T, N, PencilSepLargeTune<T, N>, 2>;
+    template <int K> using Row = PencilLauncherT<T, N, BatchTune<PencilRows<T>::rows, N, K>, 0>;
+    template <int K> using SepRow = PencilLauncherT<T, N, BatchTune<PencilSepRows<T>::rows, N, K>, 2>;
+    static constexpr long long FIELD = (long long)N * N * N * (long long)sizeof(T);
+
     static hipError_t launch(const ApplyArgs &a)
     {
-        using St = PencilSmallTune<T, N>;
-        if (a.num_elems > St::LO && a.num_elems <= St::HI) return Small::launch(a);
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<PencilRows<T>::rows, N>(a.num_elems, 3 * FIELD,
+                                                  [&](auto k) { rc = Row<decltype(k)::value>::launch(a); }))
+            return rc;
         return Plain::launch(a);
     }
     static hipError_t launch_sep(const ApplyArgs &a)
     {
-        constexpr long long cached = kPencilCachedBytes / (2LL * N * N * N * (long long)sizeof(T));
-        return a.num_elems <= cached ? Sep::launch(a) : SepLarge::launch(a);
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<PencilSepRows<T>::rows, N>(a.num_elems, 2 * FIELD,
+                                                     [&](auto k) { rc = SepRow<decltype(k)::value>::launch(a); }))
+            return rc;
+        return a.num_elems <= kPencilCachedBytes / (2 * FIELD) ? Sep::launch(a) : SepLarge::launch(a);
     }
     static hipError_t prepare()
     {
         hipError_t rc = Plain::prepare();
-        if (rc == hipSuccess) rc = Small::prepare();
         if (rc == hipSuccess) rc = Sep::prepare();
-        return rc != hipSuccess ? rc : SepLarge::prepare();
+        if (rc == hipSuccess) rc = SepLarge::prepare();
+        auto also = [&](hipError_t (*f)()) { if (rc == hipSuccess) rc = f(); };
+        for_each_batch_row<PencilRows<T>::rows, N>([&](auto k) { also(&Row<decltype(k)::value>::prepare); });
+        for_each_batch_row<PencilSepRows<T>::rows, N>([&](auto k) { also(&SepRow<decltype(k)::value>::prepare); });
+        return rc;
     }
 };
 

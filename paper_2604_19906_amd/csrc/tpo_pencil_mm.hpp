@@ -312,7 +312,7 @@ struct PencilMmRow { int g, hint, xcd; };
 constexpr PencilMmRow kPencilMmTable[TPO_MAX_N + 1] = {
     {0, 0, 0},
     {0, 0, 1}, {0, 0, 0}, {0, 0, 1}, {8, 2, 0}, {12, 0, 0}, {12, 0, 0}, {6, 0, 0}, {1, 3, 0},
-    {6, 0, 0}, {3, 0, 1}, {2, 0, 0}, {3, 2, 0}, {3, 0, 0}, {2, 0, 0}, {1, 0, 1}, {1, 3, 0},
+    {6, 0, 0}, {3, 0, 1}, {2, 0, 0}, {3, 2, 0}, {3, 0, 0}, {1, 0, 0}, {1, 2, 0}, {1, 3, 0},
 };
 template <int N>
 struct PencilMmTune {
@@ -320,6 +320,10 @@ struct PencilMmTune {
     static constexpr int HINT = kPencilMmTable[N].hint;
     static constexpr bool XCD = kPencilMmTable[N].xcd != 0;
 };
+// Separable form: as the D form unless measured otherwise (2.5 GB: n = 7 0.96 of the time, 14 0.97).
+template <int N> struct PencilMmSepTune : PencilMmTune<N> {};
+template <> struct PencilMmSepTune<7> { static constexpr int G = 6, HINT = 2; static constexpr bool XCD = false; };
+template <> struct PencilMmSepTune<14> { static constexpr int G = 2, HINT = 2; static constexpr bool XCD = true; };
 // Settings for large batches, used when num_elems > FROM (FROM < 0: never).  n = 13: with die
 // renumbering the lines shared by neighbouring elements (8788 bytes each) stay in one L2; on the
 // 1048576 elements of the named workload that is 5.33-5.35 against 5.38-5.39 ms (alternating
@@ -374,20 +378,37 @@ template <int N>
 struct PencilMmLauncher {
     using Plain = PencilMmLauncherT<N, PencilMmTune<N>>;
     using Large = PencilMmLauncherT<N, PencilMmLargeTune<N>>;
+    template <int K> using Row = PencilMmLauncherT<N, BatchTune<PencilMmRows::rows, N, K>>;
+    template <int K> using SepRow = PencilMmLauncherT<N, BatchTune<PencilMmSepRows::rows, N, K>>;
+    static constexpr long long FIELD = (long long)N * N * N * 4;
     static constexpr long long FROM = PencilMmLargeTune<N>::FROM;
     static bool large(const ApplyArgs &a) { return FROM >= 0 && a.num_elems > FROM; }
     static hipError_t launch(const ApplyArgs &a)
     {
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<PencilMmRows::rows, N>(a.num_elems, 3 * FIELD, [&](auto k) {
+                rc = Row<decltype(k)::value>::template launch_as<false>(a); }))
+            return rc;
         return large(a) ? Large::template launch_as<false>(a) : Plain::template launch_as<false>(a);
     }
     static hipError_t launch_sep(const ApplyArgs &a)
     {
-        return large(a) ? Large::template launch_as<true>(a) : Plain::template launch_as<true>(a);
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<PencilMmSepRows::rows, N>(a.num_elems, 2 * FIELD, [&](auto k) {
+                rc = SepRow<decltype(k)::value>::template launch_as<true>(a); }))
+            return rc;
+        using Rest = PencilMmLauncherT<N, PencilMmSepTune<N>>;
+        return large(a) ? Large::template launch_as<true>(a) : Rest::template launch_as<true>(a);
     }
     static hipError_t prepare()
     {
-        const hipError_t rc = Plain::prepare();
-        return rc != hipSuccess ? rc : Large::prepare();
+        hipError_t rc = Plain::prepare();
+        auto also = [&](hipError_t (*f)()) { if (rc == hipSuccess) rc = f(); };
+        also(&Large::prepare);
+        also(&PencilMmLauncherT<N, PencilMmSepTune<N>>::prepare);
+        for_each_batch_row<PencilMmRows::rows, N>([&](auto k) { also(&Row<decltype(k)::value>::prepare); });
+        for_each_batch_row<PencilMmSepRows::rows, N>([&](auto k) { also(&SepRow<decltype(k)::value>::prepare); });
+        return rc;
     }
 };
 

@@ -15,7 +15,7 @@
 
 namespace tpo {
 
-template <typename T, int N, int G, int HINT, bool XCD, bool FWD>
+template <typename T, int N, int G, int HINT, bool XCD, bool FWD, int SB>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
 transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T *t,
                         long long num_elems)
@@ -47,7 +47,7 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     // axis 2: lane (a,b) = (hi,lo) owns u[a][b][0..n-1], contiguous in memory
     if (on) {
         load_words<(HINT & 1) != 0>(u + base + (size_t)(p * N), x);
-        mode_product<T, N, FWD>(Sz, x, y);
+        mode_product<T, N, FWD, SB>(Sz, x, y);
 #pragma unroll
         for (int k = 0; k < N; ++k) cube[hi * PA + lo * PB + k] = y[k];
     }
@@ -57,7 +57,7 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     if (on) {
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = cube[hi * PA + m * PB + lo];
-        mode_product<T, N, FWD>(Sy, x, y);
+        mode_product<T, N, FWD, SB>(Sy, x, y);
 #pragma unroll
         for (int j = 0; j < N; ++j) cube[hi * PA + j * PB + lo] = y[j];
     }
@@ -67,7 +67,7 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     if (on) {
 #pragma unroll
         for (int l = 0; l < N; ++l) x[l] = cube[l * PA + hi * PB + lo];
-        mode_product<T, N, FWD>(Sx, x, y);
+        mode_product<T, N, FWD, SB>(Sx, x, y);
 #pragma unroll
         for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(t + base + (size_t)(i * P + p), y[i]);
     }
@@ -178,17 +178,19 @@ template <typename T, int N> struct TransformTune {
     using Tune = PencilSepTune<T, N>;
     static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
     static constexpr bool XCD = Tune::XCD, MM = false;
+    static constexpr int SB = kScalarBatch;
     static constexpr long long FROM = kPencilCachedBytes;       // of the settings for large batches
 };
-template <int GG, int H, bool X, bool M, long long MB = 256> struct TransformSet {
-    static constexpr int G = GG, HINT = H;
+template <int GG, int H, bool X, bool M, long long MB = 256, int S = kScalarBatch> struct TransformSet {
+    static constexpr int G = GG, HINT = H, SB = S;
     static constexpr bool XCD = X, MM = M;
     static constexpr long long FROM = MB << 20;
 };
+template <typename T> struct TransformTune<T, 2> : TransformSet<16, 0, false, false> {};
 template <> struct TransformTune<float, 12> : TransformSet<3, 2, true, true> {};
-template <> struct TransformTune<float, 13> : TransformSet<3, 0, true, true> {};
+template <> struct TransformTune<float, 13> : TransformSet<3, 0, false, true> {};
 template <> struct TransformTune<float, 14> : TransformSet<2, 0, false, true> {};
-template <> struct TransformTune<float, 15> : TransformSet<2, 0, true, true> {};
+template <> struct TransformTune<float, 15> : TransformSet<1, 0, false, true> {};
 template <> struct TransformTune<float, 16> : TransformSet<1, 2, false, true> {};
 // While both fields stay in the last-level cache: the matrix-core form from n = 8 on.
 template <> struct TransformTune<float, 8> : TransformSet<2, 2, false, true> {};
@@ -209,6 +211,7 @@ template <int N> struct TransformVectorTune {
     using Tune = PencilSepTune<float, N>;
     static constexpr int G = Tune::G, HINT = Tune::HINT & 2;
     static constexpr bool XCD = Tune::XCD, MM = false;
+    static constexpr int SB = kScalarBatch;
     static constexpr long long FROM = kPencilCachedBytes;
 };
 template <> struct TransformLargeTune<float, 8> : TransformVectorTune<8> {};
@@ -235,7 +238,7 @@ struct TransformLauncherT {
     static constexpr auto kernel()
     {
         if constexpr (Tune::MM) return &transform_mm_kernel<N, G, Tune::HINT, Tune::XCD, FWD>;
-        else return &transform_pencil_kernel<T, N, G, Tune::HINT, Tune::XCD, FWD>;
+        else return &transform_pencil_kernel<T, N, G, Tune::HINT, Tune::XCD, FWD, Tune::SB>;
     }
 
     static hipError_t launch(const TransformArgs &a)
@@ -261,18 +264,26 @@ template <typename T, int N, bool FWD>
 struct TransformLauncher {
     using Cached = TransformLauncherT<T, N, FWD, TransformTune<T, N>>;
     using Large = TransformLauncherT<T, N, FWD, TransformLargeTune<T, N>>;
+    template <int K> using Row = TransformLauncherT<T, N, FWD, BatchTune<TransformRows<T>::rows, N, K>>;
+    static constexpr long long BYTES = 2LL * N * N * N * (long long)sizeof(T);
     static hipError_t launch(const TransformArgs &a)
     {
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<TransformRows<T>::rows, N>(a.num_elems, BYTES,
+                                                     [&](auto k) { rc = Row<decltype(k)::value>::launch(a); }))
+            return rc;
         return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
     }
-    static bool takes_large(long long num_elems)
-    {
-        return num_elems > TransformLargeTune<T, N>::FROM / (2LL * N * N * N * (long long)sizeof(T));
-    }
+    // Of the two settings past the rows.
+    static bool takes_large(long long num_elems) { return num_elems > TransformLargeTune<T, N>::FROM / BYTES; }
     static hipError_t prepare()
     {
-        const hipError_t rc = Cached::prepare();
-        return rc != hipSuccess ? rc : Large::prepare();
+        hipError_t rc = Cached::prepare();
+        if (rc == hipSuccess) rc = Large::prepare();
+        for_each_batch_row<TransformRows<T>::rows, N>([&](auto k) {
+            if (rc == hipSuccess) rc = Row<decltype(k)::value>::prepare();
+        });
+        return rc;
     }
 };
 

@@ -1,0 +1,34 @@
+"""The lists of launch settings by size of the batch, asked of the library on the host: in order of size, and the
+families that a batch takes next to the sizes where they change places."""
+import ctypes
+
+import pytest
+
+from paper_2604_19906_amd import tpo
+
+
+@pytest.mark.parametrize("which", range(5))
+@pytest.mark.parametrize("dtype", [tpo.TPO_F64, tpo.TPO_F32])
+def test_rows_are_in_order(which, dtype):
+    row = tpo.lib().tpo_internal_batch_row
+    row.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    for n in range(1, tpo.TPO_MAX_N + 1):
+        got = [row(which, n, dtype, e) for e in (int(1.05 ** k) for k in range(420))]
+        cut = got.index(-1)
+        assert got[:cut] == sorted(got[:cut]) and set(got[cut:]) == {-1}
+    assert row(which, 17, dtype, 1) == -1
+
+
+P, M, X = tpo.TPO_VARIANT_PENCIL, tpo.TPO_VARIANT_MFMA, tpo.TPO_VARIANT_PENCIL_MM
+
+
+@pytest.mark.parametrize("n,dtype,shared,e,operator,separable", [
+    (11, tpo.TPO_F64, False, 256, M, M), (11, tpo.TPO_F64, False, 257, P, P), (11, tpo.TPO_F64, True, 256, P, P),
+    (12, tpo.TPO_F64, True, 256, M, M), (15, tpo.TPO_F64, False, 256, M, M), (10, tpo.TPO_F64, False, 1, P, P),
+    (16, tpo.TPO_F64, False, 256, M, M), (16, tpo.TPO_F64, False, 4096, M, P), (16, tpo.TPO_F64, False, 4097, P, P),
+    (7, tpo.TPO_F32, False, 2292, P, X), (7, tpo.TPO_F32, False, 2293, X, X), (6, tpo.TPO_F32, False, 1 << 20, P, P),
+    (14, tpo.TPO_F32, False, 100000, X, X), (14, tpo.TPO_F32, False, 100001, M, M),
+    (15, tpo.TPO_F32, False, 24000, X, X), (15, tpo.TPO_F32, False, 24001, M, X), (15, tpo.TPO_F32, False, 40001, M, M)])
+def test_families(n, dtype, shared, e, operator, separable):
+    assert tpo.tpo_ihelm_variant_for_batch(n, dtype, shared, e) == operator
+    assert tpo.tpo_ihelm_sep_variant_for_batch(n, dtype, shared, e) == separable

@@ -1,0 +1,98 @@
+"""The launch settings by size of the batch: every row of every list on the largest batch that takes it and the next
+row on one element more (a ragged last workgroup on one side or the other), in the operator, the separable form and
+the halves.  Every setting of a family adds in the same order, so the first and the last elements are the same bits
+as those of a small batch of their own; the last ones are also held against the CPU oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TOL, dev
+from paper_2604_19906_amd import tpo
+from paper_2604_19906_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+CODE = {"f64": tpo.TPO_F64, "f32": tpo.TPO_F32}
+REAL = {"f64": (np.float64, torch.float64, 8), "f32": (np.float32, torch.float32, 4)}
+LISTS = {"ihelm": 0, "sep": 1, "ihelm_mm": 2, "sep_mm": 3, "half": 4}
+PART = 600          # elements of a small batch: the first or the second row's
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    yield
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
+
+
+def edges(op, n, dtype):
+    """The largest batch of every row."""
+    row = tpo.lib().tpo_internal_batch_row
+    row.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    at = lambda e: row(LISTS[op], n, CODE[dtype], e)
+    found, low = [], 1
+    while at(low) >= 0:
+        k, high = at(low), low
+        while at(high) == k:
+            high *= 2
+        while high - low > 1:
+            mid = (low + high) // 2
+            low, high = (mid, high) if at(mid) == k else (low, mid)
+        found.append(low)
+        low = high
+    return found
+
+
+def run(op, u, mats, lam, mu, d, out):
+    if op in (tpo.TPO_FORWARD, tpo.TPO_BACKWARD):
+        return tpo.transform_tensors(u, *mats, op, t=out)
+    var = tpo.TPO_VARIANT_PENCIL_MM if op.endswith("_mm") else tpo.TPO_VARIANT_PENCIL
+    if op.startswith("ihelm"):
+        return tpo.apply_tensors(u, *mats, d, v=out, variant=var)
+    return tpo.apply_sep_tensors(u, *mats, *lam, mu, v=out, variant=var)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("op", list(LISTS))
+@pytest.mark.parametrize("n", range(2, 17))
+def test_rows(op, n, dtype):
+    if dtype == "f64" and op.endswith("_mm"):
+        pytest.skip("the 4x4x1 kernels are fp32")
+    sizes = edges(op, n, dtype)
+    if not sizes:
+        pytest.skip("no rows")
+    real, kind, _ = REAL[dtype]
+    rng = np.random.default_rng([19906, 83, n])
+    mats = [dev(wl.orthogonal_matrix(n, rng).astype(real)) for _ in range(3)]
+    lam = [dev(rng.uniform(0.1, 10, n).astype(real)) for _ in range(3)]
+    most = sizes[-1] + 1
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    field = lambda shape, lo, hi: torch.empty(shape, device="cuda", dtype=kind).uniform_(lo, hi, generator=gen)
+    u = field((most, n, n, n), -1, 1)
+    d = field((most, n, n, n), 0.03, 3.3) if op.startswith("ihelm") else None
+    mu = field((most,), 0, 1)
+    out = torch.empty_like(u)
+    cut = lambda x, at: None if x is None else x[at]
+    for call in ((tpo.TPO_FORWARD, tpo.TPO_BACKWARD) if op == "half" else (op,)):
+        for e in sorted({x + k for x in sizes for k in (0, 1)}):
+            print(f"case rows {op} {call} {dtype} n={n} E={e}", flush=True)
+            out[:e].fill_(float("nan"))
+            run(call, u[:e], mats, lam, mu[:e], cut(d, slice(0, e)), out[:e])
+            torch.cuda.synchronize()
+            assert not torch.isnan(out[:e]).any()
+            for at in (slice(0, min(PART, e)), slice(max(0, e - PART), e)):
+                part = run(call, u[at], mats, lam, mu[at], cut(d, at), torch.empty_like(u[at]))
+                torch.cuda.synchronize()
+                assert torch.equal(part, out[at])
+        tail = slice(most - 40, most)
+        w, *m = (x.cpu().numpy() for x in (u[tail], *mats))
+        if op == "half":
+            ref = (oracle.forward if call == tpo.TPO_FORWARD else oracle.backward)(w, *m)
+        elif op.startswith("ihelm"):
+            ref = oracle.ihelm_apply(w, *m, d[tail].cpu().numpy())
+        else:
+            ref = oracle.ihelm_apply_sep(w, *m, *(x.cpu().numpy() for x in lam), mu[tail].cpu().numpy())
+        assert oracle.max_rel_err_per_element(out[tail].cpu().numpy(), ref) <= TOL[dtype]
