@@ -321,19 +321,29 @@ const char *tpo_status_string(int status)
 }  // extern "C"
 
 // The row of launch settings that a batch takes (-1: past the rows).  list: 0 operator, 1 separable form, 2 and 3 the same
-// in the 4x4x1 kernels, 4 transform halves.
-extern "C" int tpo_internal_batch_row(int list, int n, int dtype, long long num_elems)
+// in the 4x4x1 kernels, 4 transform halves, 5 convection term with n_v = n_q.
+template <typename Rows>
+static int batch_row(const Rows &rows, int n, long long per_elem, long long num_elems)
 {
-    if (n < 1 || n > TPO_MAX_N || list < 0 || list > 4) return -1;
-    const bool f64 = dtype == TPO_F64;
-    const tpo::BatchRows &rows =
-        list == 0 ? (f64 ? tpo::PencilRows<double>::rows : tpo::PencilRows<float>::rows)
-        : list == 1 ? (f64 ? tpo::PencilSepRows<double>::rows : tpo::PencilSepRows<float>::rows)
-        : list == 2 ? tpo::PencilMmRows::rows
-        : list == 3 ? tpo::PencilMmSepRows::rows
-                    : (f64 ? tpo::TransformRows<double>::rows : tpo::TransformRows<float>::rows);
-    const long long per_elem = (list == 0 || list == 2 ? 3LL : 2LL) * n * n * n * (f64 ? 8 : 4);
     for (int k = 0; k < tpo::kBatchRows && rows.row[n][k].mib > 0; ++k)
         if (num_elems <= ((long long)rows.row[n][k].mib << 20) / per_elem) return k;
     return -1;
+}
+extern "C" int tpo_internal_batch_row(int list, int n, int dtype, long long num_elems)
+{
+    if (n < 1 || n > TPO_MAX_N) return -1;
+    const bool f64 = dtype == TPO_F64;
+    const long long field = (long long)n * n * n * (f64 ? 8 : 4);
+    using namespace tpo;
+    switch (list) {
+    case 0: return batch_row(f64 ? PencilRows<double>::rows : PencilRows<float>::rows, n, 3 * field, num_elems);
+    case 1: return batch_row(f64 ? PencilSepRows<double>::rows : PencilSepRows<float>::rows, n, 2 * field, num_elems);
+    case 2: return batch_row(PencilMmRows::rows, n, 3 * field, num_elems);
+    case 3: return batch_row(PencilMmSepRows::rows, n, 2 * field, num_elems);
+    case 4: return batch_row(f64 ? TransformRows<double>::rows : TransformRows<float>::rows, n, 2 * field, num_elems);
+    case 5:
+        return batch_row(f64 ? SquareConvectionRows<double>::rows : SquareConvectionRows<float>::rows, n, 13 * field,
+                         num_elems);
+    default: return -1;
+    }
 }

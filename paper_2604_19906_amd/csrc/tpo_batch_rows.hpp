@@ -167,9 +167,46 @@ template <> struct TransformRows<float> {
     }};
 };
 
+// Convection term, square shapes: SPLIT and all loads first as in convection_pencil_kernel.  Time over the settings there were
+// before, 16 sizes from 1 MB to 2.5 GB: fp32 n = 8 0.82 .. 1.0 (matrix-core form), 10 0.73 .. 0.97, 13 0.65 .. 0.96 but 1.01 at 55 .. 110 MB, 14 0.73 ..
+// 0.96, 9, 11, 12 0.75 .. 0.96 up to 8 MB; fp64 n = 6, 9 0.79 .. 0.95 up to 220 MB, 11 0.87 .. 0.94 up to 22 MB, 12 .. 16 0.95 .. 0.98 up to 22 MB and,
+// with SB = 40, 0.89 .. 0.98 at 35 .. 220 MB.
+struct ConvectionRow { int mib, g, hint, split, loads_first, sb, mm; };
+struct ConvectionRows { ConvectionRow row[TPO_MAX_N + 1][kBatchRows]; };
+template <typename T> struct SquareConvectionRows;
+template <> struct SquareConvectionRows<double> {
+    static constexpr ConvectionRows rows = {{
+        {}, {}, {}, {}, {}, {},
+        /* 6 */ {{28, 1, 2, 0, 0, 32}, {123, 6, 2, 1, 0, 0}},
+        /* 7 */ {{28, 1, 0, 0, 0, 32}, {123, 1, 2, 1, 0, 32}},
+        /* 8 */ {{43, 1, 2, 0, 0, 32}, {123, 1, 2, 1, 0, 0}},
+        /* 9 */ {{28, 1, 0, 0, 0, 32}, {66, 3, 2, 0, 0, 0}, {253, 2, 2, 1, 0, 32}},
+        /* 10 */ {{43, 1, 2, 0, 0, 32}, {1010, 1, 2, 1, 0, 40}},
+        /* 11 */ {{10, 1, 0, 1, 1, 32}, {22, 2, 0, 1, 1, 32}, {1010, 1, 2, 1, 0, 40}},
+        /* 12 */ {{43, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}, {1010, 1, 2, 1, 1, 32}},
+        /* 13 */ {{28, 1, 2, 0, 0, 32}, {173, 1, 2, 1, 0, 40}},
+        /* 14 */ {{28, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}},
+        /* 15 */ {{28, 1, 2, 0, 0, 32}, {123, 1, 2, 1, 0, 40}, {256, 1, 2, 1, 1, 32}},
+        /* 16 */ {{28, 1, 2, 0, 0, 32}},
+    }};
+};
+template <> struct SquareConvectionRows<float> {
+    static constexpr ConvectionRows rows = {{
+        {}, {}, {}, {}, {}, {}, {}, {}, {},
+        /* 9 */ {{2, 1, 0, 0, 1, 0, 1}, {90, 3, 0, 0, 1, 0, 1}},
+        /* 10 */ {{5, 1, 0, 0, 1, 0, 1}},
+        /* 11 */ {{17, 1, 0, 1, 1, 0, 1}, {253, 2, 2, 1, 0, 0, 1}},
+        /* 12 */ {{13, 1, 2, 0, 1, 0, 1}},
+        /* 13 */ {{17, 1, 0, 0, 1, 0, 1}, {24, 3, 2, 1, 1, 0, 1}},
+        /* 14 */ {{17, 1, 0, 0, 1, 0, 1}, {123, 1, 2, 0, 1, 0, 1}},
+        /* 15 */ {{17, 1, 0, 0, 1, 0, 1}, {64, 1, 2, 1, 0, 0, 1}},
+        {},
+    }};
+};
+
 // f(integral_constant<int, K>) for the first row K of n that a batch of num_elems elements (bytes_per_elem of
 // fields each) fits; f returns its result.  False: past the rows.
-template <const BatchRows &ROWS, int N, int K = 0, typename F>
+template <const auto &ROWS, int N, int K = 0, typename F>
 inline bool for_batch_row(long long num_elems, long long bytes_per_elem, F &&f)
 {
     if constexpr (K < kBatchRows) {
@@ -183,7 +220,7 @@ inline bool for_batch_row(long long num_elems, long long bytes_per_elem, F &&f)
     }
     return false;
 }
-template <const BatchRows &ROWS, int N, int K = 0, typename F>
+template <const auto &ROWS, int N, int K = 0, typename F>
 inline void for_each_batch_row(F &&f)
 {
     if constexpr (K < kBatchRows) {
@@ -201,6 +238,12 @@ struct BatchTune {
     static constexpr int G = R.g, HINT = R.hint, SB = R.sb;
     static constexpr bool DDIRECT = true, XCD = R.xcd != 0, MM = R.mm != 0;
     static constexpr size_t LDS_MIN = 0;
+};
+template <const ConvectionRows &ROWS, int N, int K>
+struct ConvectionBatchTune {
+    static constexpr ConvectionRow R = ROWS.row[N][K];
+    static constexpr int G = R.g, HINT = R.hint, SB = R.sb;
+    static constexpr bool SPLIT = R.split != 0, LOADS_FIRST = R.loads_first != 0, MM = R.mm != 0;
 };
 
 }  // namespace tpo

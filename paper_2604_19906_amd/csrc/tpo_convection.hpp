@@ -23,6 +23,7 @@
 
 #include <type_traits>
 
+#include "tpo_batch_rows.hpp"
 #include "tpo_pencil.hpp"
 #include "tpo_pencil_mm.hpp"
 
@@ -97,13 +98,12 @@ constexpr int convection_batch_words()
 // merged, in the LDS cube that merge frees: two cubes per unit instead of three (more
 // workgroups per CU) for two more barriers.
 // LOADS_FIRST: see the loads.
-template <typename T, int N, int G, int HINT, bool XCD, bool SPLIT, bool LOADS_FIRST>
+template <typename T, int N, int G, int HINT, bool XCD, bool SPLIT, bool LOADS_FIRST, int SB>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
 convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const T *Dm_,
                          const T *Im_, T *__restrict__ F, long long num_elems)
 {
     using Sh = PencilShape<T, N, G>;
-    constexpr int SB = convection_batch_words<T, N>();
     constexpr int P = Sh::P, PA = Sh::PA, PB = Sh::PB, CUBE = Sh::CUBE;
     extern __shared__ __align__(16) unsigned char tpo_lds[];
     T *lds = reinterpret_cast<T *>(tpo_lds);
@@ -231,7 +231,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 // untransposed) stay in registers for the whole kernel.  The matrix instructions run on whole
 // wavefronts, outside the `on` branches (their broadcast coefficients come from active lanes
 // only).
-template <int N, int G, int HINT, bool XCD, bool SPLIT = false>
+template <int N, int G, int HINT, bool XCD, bool SPLIT, bool LOADS_FIRST>
 __global__ void __launch_bounds__((PencilShape<float, N, G>::NT))
 convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
                      const float *__restrict__ Dm, const float *__restrict__ Im,
@@ -252,7 +252,6 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
     const long long nbatch = (units + G - 1) / G;
     const long long batch = convection_batch<XCD>();
     if (XCD && batch >= nbatch) return;
-    constexpr bool LOADS_FIRST = N >= 13;         // see below
     // Lanes without a pencil never write; with LOADS_FIRST they read pencil 0 of the workgroup's first
     // unit (there is one), else the global loads leave them out.
     const int g_ = tid / P;
@@ -748,52 +747,62 @@ struct ConvectionRectEntry {
                                                     &ConvectionRectLauncher<T, NV, NQ>::prepare, \
                                                     &ConvectionRectLauncher<T, NV, NQ>::takes_large } }
 
-// Square shapes: units per workgroup by lane utilisation, SPLIT by size, and in fp32 from n = 9 on
-// the 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there, as for the
-// inverse-Helmholtz operator).  A sweep over 1 .. 16 units x SPLIT x form on MI355X found more for
-// some n (us per call on 2.5 GB, rule / setting): fp64 n = 7 454 / 430, n = 10 484 / 432, which also
-// hold on small batches (150 MB: 31.1 / 25.9, 31.8 / 30.3; 2 MB: 4.9 / 4.1, 7.2 / 6.1), as does
-// fp32 n = 7 (462 / 446, 27.5 / 26.1, 4.4 / 4.0; but fp64 n = 10 1.00 .. 1.04 at 100 .. 175 MB); fp64 n = 3 525 / 499, 9 460 / 444 and fp32 n = 3 567 / 516,
-// 5 486 / 468, 11 502 / 466, which only pay once the fields pass the last-level cache.  (Swept before all
-// loads went first for fp64 n >= 11 and fp32 n >= 13; not swept again.)
+// Square shapes.  ConvectionTune: units per workgroup by lane utilisation, SPLIT by size, and in fp32 from n = 9 on the
+// 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there, as for the operator).  A sweep of units x
+// SPLIT x form x order of the loads x HINT over 0.5 MB .. 2.5 GB on MI355X, with buffers that take turns, found better
+// settings for the n below (time over ConvectionTune's at 400 MB / 2.5 GB: fp64 n = 6 0.97 / 0.98; fp32 n = 10
+// 0.92 / 0.97, 13 0.94 / 1.01, 14 0.86 / 0.98; fp64 n = 7, 10 and fp32 n = 7 from an earlier sweep: 430 / 454, 432 / 484,
+// 446 / 462 us on 2.5 GB), and for smaller batches the rows of SquareConvectionRows.  fp32 n = 8 in the matrix-core
+// form: 0.83 .. 0.95 of the time on 9 .. 200 MB, the same elsewhere.  ConvectionLargeTune pays only once the fields
+// pass the last-level cache (2.5 GB: fp64 n = 3 525 / 499, 9 460 / 444; fp32 n = 3 567 / 516, 5 486 / 468,
+// 11 502 / 466 us).
 template <typename T, int N> struct ConvectionTune {
-    static constexpr int G = convection_group<T, N>();
+    static constexpr int G = convection_group<T, N>(), HINT = 2;
     static constexpr bool SPLIT = convection_split<T, N>();
-    static constexpr bool MM = sizeof(T) == 4 && N >= 9;
+    static constexpr bool MM = sizeof(T) == 4 && N >= 9, LOADS_FIRST = MM && N >= 13;
+    static constexpr int SB = convection_batch_words<T, N>();
 };
-template <int GG, bool S, bool M> struct ConvectionSet {
+template <typename T, int N, int GG, bool S, bool M, bool L = (M && N >= 13)> struct ConvectionSet : ConvectionTune<T, N> {
     static constexpr int G = GG;
-    static constexpr bool SPLIT = S, MM = M;
+    static constexpr bool SPLIT = S, MM = M, LOADS_FIRST = L;
 };
-template <> struct ConvectionTune<double, 7> : ConvectionSet<1, false, false> {};
-template <> struct ConvectionTune<double, 10> : ConvectionSet<1, true, false> {};
-template <> struct ConvectionTune<float, 7> : ConvectionSet<1, true, true> {};
-template <typename T, int N> struct ConvectionLargeTune : ConvectionTune<T, N> {};
-template <> struct ConvectionLargeTune<double, 3> : ConvectionSet<16, false, false> {};
-template <> struct ConvectionLargeTune<double, 9> : ConvectionSet<3, true, false> {};
-template <> struct ConvectionLargeTune<float, 3> : ConvectionSet<16, false, false> {};
-template <> struct ConvectionLargeTune<float, 5> : ConvectionSet<8, false, false> {};
-template <> struct ConvectionLargeTune<float, 11> : ConvectionSet<2, true, true> {};
-
-template <typename T, int N, typename Tune, bool LARGE>
-struct ConvectionLauncherT {
-    static constexpr int G = Tune::G;
-    using Sh = PencilShape<T, N, G>;
-    static constexpr size_t LDS = (size_t)(Tune::SPLIT ? 2 : 3) * G * Sh::CUBE * sizeof(T);
-    // Non-temporal stores are worth 3 to 8 %, non-temporal loads halve the rate (the per-lane runs
-    // share cache lines).
-    static constexpr int HINT = 2;
-    static constexpr bool XCD = G % 3 != 0;    // with G a multiple of 3 an element stays in one workgroup
+template <typename T, int N> struct ConvectionBase : ConvectionTune<T, N> {};
+template <> struct ConvectionBase<double, 6> : ConvectionSet<double, 6, 1, false, false> {};
+template <> struct ConvectionBase<double, 7> : ConvectionSet<double, 7, 1, false, false> {};
+template <> struct ConvectionBase<double, 10> : ConvectionSet<double, 10, 1, true, false> {};
+template <> struct ConvectionBase<float, 7> : ConvectionSet<float, 7, 1, true, true> {};
+template <> struct ConvectionBase<float, 8> : ConvectionSet<float, 8, 1, true, true> {};
+template <> struct ConvectionBase<float, 9> : ConvectionSet<float, 9, 3, true, true> {};
+template <> struct ConvectionBase<float, 10> : ConvectionSet<float, 10, 2, false, true, true> {};
+template <> struct ConvectionBase<float, 12> : ConvectionSet<float, 12, 3, true, true> {};
+template <> struct ConvectionBase<float, 13> : ConvectionSet<float, 13, 1, true, true> {};
+template <> struct ConvectionBase<float, 14> : ConvectionSet<float, 14, 2, false, true> {};
+template <typename T, int N> struct ConvectionLargeTune : ConvectionBase<T, N> {
     // fp64 on large batches (3 GB, with / without: n = 11 527 / 551 us, 12 569 / 582,
     // 13 584 / 622, 14 632 / 672, 15 716 / 772, 16 703 / 750; n = 10 524 / 521, 9 544 / 534, 8 529 / 527,
     // 6 527 / 519), where the wait for memory outweighs the registers; cached ones lose 2 to 9 %
     // (n = 11, 150 MB: 38.4 / 35.2).
-    static constexpr bool LOADS_FIRST = LARGE && sizeof(T) == 8 && N >= 11;
+    static constexpr bool LOADS_FIRST = ConvectionBase<T, N>::LOADS_FIRST || (sizeof(T) == 8 && N >= 11);
+};
+template <> struct ConvectionLargeTune<double, 3> : ConvectionSet<double, 3, 16, false, false> {};
+template <> struct ConvectionLargeTune<double, 9> : ConvectionSet<double, 9, 3, true, false> {};
+template <> struct ConvectionLargeTune<float, 3> : ConvectionSet<float, 3, 16, false, false> {};
+template <> struct ConvectionLargeTune<float, 5> : ConvectionSet<float, 5, 8, false, false> {};
+template <> struct ConvectionLargeTune<float, 11> : ConvectionSet<float, 11, 2, true, true> {};
+
+template <typename T, int N, typename Tune>
+struct ConvectionLauncherT {
+    static constexpr int G = Tune::G, HINT = Tune::HINT;
+    using Sh = PencilShape<T, N, G>;
+    static constexpr size_t LDS = (size_t)(Tune::SPLIT ? 2 : 3) * G * Sh::CUBE * sizeof(T);
+    // Non-temporal stores are worth 3 to 8 %, non-temporal loads halve the rate (the per-lane runs
+    // share cache lines).
+    static constexpr bool XCD = G % 3 != 0;    // with G a multiple of 3 an element stays in one workgroup
 
     static constexpr auto kernel()
     {
-        if constexpr (Tune::MM) return &convection_mm_kernel<N, G, HINT, XCD, Tune::SPLIT>;
-        else return &convection_pencil_kernel<T, N, G, HINT, XCD, Tune::SPLIT, LOADS_FIRST>;
+        if constexpr (Tune::MM) return &convection_mm_kernel<N, G, HINT, XCD, Tune::SPLIT, Tune::LOADS_FIRST>;
+        else return &convection_pencil_kernel<T, N, G, HINT, XCD, Tune::SPLIT, Tune::LOADS_FIRST, Tune::SB>;
     }
 
     static hipError_t launch(const ConvectionArgs &a)
@@ -817,14 +826,20 @@ struct ConvectionLauncherT {
 
 template <typename T, int N>
 struct ConvectionLauncher {
-    using Cached = ConvectionLauncherT<T, N, ConvectionTune<T, N>, false>;
-    using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>, true>;
+    using Cached = ConvectionLauncherT<T, N, ConvectionBase<T, N>>;
+    using Large = ConvectionLauncherT<T, N, ConvectionLargeTune<T, N>>;
+    template <int K> using Row = ConvectionLauncherT<T, N, ConvectionBatchTune<SquareConvectionRows<T>::rows, N, K>>;
     static hipError_t launch(const ConvectionArgs &a)
     {
+        hipError_t rc = hipSuccess;
+        if (for_batch_row<SquareConvectionRows<T>::rows, N>(a.num_elems, 13LL * N * N * N * (long long)sizeof(T),
+                                                            [&](auto k) { rc = Row<decltype(k)::value>::launch(a); }))
+            return rc;
         return takes_large(a.num_elems) ? Large::launch(a) : Cached::launch(a);
     }
     // All loads first at n = 11, 12 costs until the fields are some times the cache (275 .. 430 MB: n = 11 1.02
     // .. 1.09 of the time, n = 12 0.99 .. 1.02; 600 MB 1.00, 0.99; 1.2 GB 0.96, 0.97).
+    // Of the two settings past the rows.
     static bool takes_large(long long num_elems)
     {
         constexpr bool late = sizeof(T) == 8 && (N == 11 || N == 12);
@@ -832,8 +847,12 @@ struct ConvectionLauncher {
     }
     static hipError_t prepare()
     {
-        const hipError_t rc = Cached::prepare();
-        return rc != hipSuccess ? rc : Large::prepare();
+        hipError_t rc = Cached::prepare();
+        if (rc == hipSuccess) rc = Large::prepare();
+        for_each_batch_row<SquareConvectionRows<T>::rows, N>([&](auto k) {
+            if (rc == hipSuccess) rc = Row<decltype(k)::value>::prepare();
+        });
+        return rc;
     }
 };
 

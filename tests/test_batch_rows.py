@@ -7,7 +7,7 @@ import pytest
 from paper_2604_19906_amd import tpo
 
 
-@pytest.mark.parametrize("which", range(5))
+@pytest.mark.parametrize("which", range(6))
 @pytest.mark.parametrize("dtype", [tpo.TPO_F64, tpo.TPO_F32])
 def test_rows_are_in_order(which, dtype):
     row = tpo.lib().tpo_internal_batch_row

@@ -16,7 +16,7 @@ from paper_2604_19906_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 CODE = {"f64": tpo.TPO_F64, "f32": tpo.TPO_F32}
 REAL = {"f64": (np.float64, torch.float64, 8), "f32": (np.float32, torch.float32, 4)}
-LISTS = {"ihelm": 0, "sep": 1, "ihelm_mm": 2, "sep_mm": 3, "half": 4}
+LISTS = {"ihelm": 0, "sep": 1, "ihelm_mm": 2, "sep_mm": 3, "half": 4, "conv": 5}
 PART = 600          # elements of a small batch: the first or the second row's
 
 
@@ -56,7 +56,7 @@ def run(op, u, mats, lam, mu, d, out):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("op", list(LISTS))
+@pytest.mark.parametrize("op", [op for op in LISTS if op != "conv"])
 @pytest.mark.parametrize("n", range(2, 17))
 def test_rows(op, n, dtype):
     if dtype == "f64" and op.endswith("_mm"):
@@ -96,3 +96,34 @@ def test_rows(op, n, dtype):
         else:
             ref = oracle.ihelm_apply_sep(w, *m, *(x.cpu().numpy() for x in lam), mu[tail].cpu().numpy())
         assert oracle.max_rel_err_per_element(out[tail].cpu().numpy(), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", range(5, 17))
+def test_convection_rows(n, dtype):
+    """The same for the convection term.  The matrix-core and the vector form add in the same order too."""
+    sizes = edges("conv", n, dtype)
+    if not sizes:
+        pytest.skip("no rows")
+    real, kind, _ = REAL[dtype]
+    rng = np.random.default_rng([19906, 84, n])
+    d, i = (dev(rng.uniform(-1, 1, (n, n)).astype(real)) for _ in range(2))
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    most = sizes[-1] + 1
+    p = torch.empty((3, 3, most, n, n, n), device="cuda", dtype=kind).uniform_(-1, 1, generator=gen)
+    m = torch.empty((most, n, n, n), device="cuda", dtype=kind).uniform_(0.5, 2, generator=gen)
+    part = lambda at: (p[:, :, at].contiguous(), m[at])
+    for e in sorted({x + k for x in sizes for k in (0, 1)}):
+        print(f"case convection rows {dtype} n={n} E={e}", flush=True)
+        out = torch.full((3, e, n, n, n), float("nan"), device="cuda", dtype=kind)
+        tpo.convection_tensors(*part(slice(0, e)), d, i, F=out)
+        torch.cuda.synchronize()
+        assert not torch.isnan(out).any()
+        for at in (slice(0, min(200, e)), slice(max(0, e - 200), e)):
+            got = tpo.convection_tensors(*part(at), d, i)
+            torch.cuda.synchronize()
+            assert torch.equal(got, out[:, at])
+    tail = slice(most - 20, most)
+    ref = oracle.convection_apply(*(x.cpu().numpy() for x in (*part(tail), d, i)))
+    err = oracle.max_rel_err_per_element(out[:, tail].reshape(-1, n, n, n).cpu().numpy(), ref.reshape(-1, n, n, n))
+    assert err <= TOL[dtype]
