@@ -347,3 +347,15 @@ extern "C" int tpo_internal_batch_row(int list, int n, int dtype, long long num_
     default: return -1;
     }
 }
+// The same for the over-integrated convection term (n_v != n_q).
+template <typename T>
+static int rect_row(int n_v, int n_q, long long num_elems)
+{
+    for (int k = 0; tpo::convection_rect_first<T>(n_v, n_q, k).g != 0; ++k)
+        if (tpo::convection_rect_fits<T>(tpo::convection_rect_first<T>(n_v, n_q, k), num_elems)) return k;
+    return -1;
+}
+extern "C" int tpo_internal_convection_rect_row(int n_v, int n_q, int dtype, long long num_elems)
+{
+    return dtype == TPO_F64 ? rect_row<double>(n_v, n_q, num_elems) : rect_row<float>(n_v, n_q, num_elems);
+}

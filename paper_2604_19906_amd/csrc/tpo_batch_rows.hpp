@@ -204,6 +204,53 @@ template <> struct SquareConvectionRows<float> {
     }};
 };
 
+// Convection term, over-integrated shapes: the first row of a shape that the batch's fields fit (`mib` MiB; 0: every
+// batch, the shape then has no other setting).  form 0: convection_rect_kernel, 1 and 2: convection_rect_large_kernel
+// without and with compact lanes.  With the scalars in batches (sb) one unit per workgroup leads in fp64 far beyond the
+// first round of workgroups; in fp32 it leads while a launch is about one round.  The best of three forms x
+// {1, 2, 3, 4, 6, 8} units x sb at 12 sizes from 1 MB to 2.4 GB, buffers in turns, MI355X; time over the settings of
+// ConvRectTable and of the utilisation rule: fp64 (6,7) 0.69 .. 0.90 up to 200 MB, 0.91 .. 0.96 beyond, (5,7), (6,9), (7,9)
+// 0.78 .. 0.94 and 0.92 .. 0.97, (8,9) 0.79 .. 0.97 (1.01 at 70 MB), (5,8), (6,8), (8,12) 0.88 .. 0.99, (9,14) 0.85 .. 0.91
+// (22 MB: 1.07), (8,10), (9,10) 0.91 .. 0.99 at 76 .. 125 MB, (7,8) 0.93 .. 1.0 (92 .. 108 MB without batches of scalars:
+// 1.03 .. 1.06 with them); fp32 (12,14) 0.66 .. 0.97, (9,10) 0.80 .. 0.95, (10,12) 0.79 .. 0.97, (11,12), (11,13), (12,13)
+// 0.78 .. 0.96 up to 13 MB, (6,7), (5,7), (7,9), (8,12) 0.88 .. 1.0.  The rule's larger workgroups keep the sizes where
+// they still are one round and the smaller ones are not: 1.05 .. 1.12 for (9,10) at 17 .. 19 MB, (10,12) at 16 .. 20,
+// (11,12), (11,13), (12,13) at 16 .. 24.
+struct ConvRectFirst { int nv, nq, mib, g, form, sb; };
+template <typename T> struct ConvRectFirstTable;
+template <> struct ConvRectFirstTable<double> {
+    static constexpr ConvRectFirst row[] = {
+        {5, 6, 16, 1, 0, 32},   {5, 7, 0, 1, 0, 32},    {5, 8, 190, 1, 0, 32},  {5, 8, 0, 4, 1, 32},
+        {6, 7, 0, 1, 0, 32},    {6, 8, 2400, 1, 1, 32}, {6, 9, 0, 1, 0, 32},    {7, 8, 78, 1, 0, 32},
+        {7, 8, 104, 1, 0, 0},   {7, 8, 400, 1, 0, 32},  {7, 9, 2400, 1, 0, 32}, {8, 9, 0, 1, 0, 32},
+        {8, 10, 70, 1, 1, 32},  {8, 10, 122, 2, 2, 32}, {9, 10, 66, 1, 1, 32},  {9, 10, 122, 2, 0, 32},
+        {8, 12, 600, 1, 0, 32}, {9, 14, 13, 1, 0, 32},
+    };
+};
+template <> struct ConvRectFirstTable<float> {
+    static constexpr ConvRectFirst row[] = {
+        {5, 6, 3, 1, 0, 0},    {5, 7, 0, 4, 0, 0},    {5, 8, 7, 1, 0, 0},    {6, 7, 7, 1, 0, 0},     {6, 8, 20, 1, 0, 0},
+        {6, 9, 48, 1, 0, 0},   {7, 9, 50, 1, 0, 0},   {8, 10, 13, 1, 0, 0},  {8, 12, 5, 1, 0, 0},    {9, 10, 15, 2, 1, 0},
+        {9, 10, 18, 5, 0, 0},  {9, 10, 31, 2, 1, 0},  {9, 14, 7, 1, 0, 0},   {10, 12, 13, 1, 0, 0},  {10, 12, 20, 3, 0, 0},
+        {10, 12, 240, 2, 2, 0}, {11, 12, 13, 1, 0, 0}, {11, 13, 13, 1, 0, 0}, {12, 13, 13, 1, 0, 0}, {12, 14, 0, 1, 0, 0},
+    };
+};
+// The k-th row of a shape ({}: it has no more).
+template <typename T>
+constexpr ConvRectFirst convection_rect_first(int nv, int nq, int k)
+{
+    for (const ConvRectFirst &r : ConvRectFirstTable<T>::row)
+        if (r.nv == nv && r.nq == nq && k-- == 0) return r;
+    return {};
+}
+// Whether a batch fits row r of its shape.
+template <typename T>
+constexpr bool convection_rect_fits(const ConvRectFirst &r, long long num_elems)
+{
+    const long long per = (10LL * r.nq * r.nq * r.nq + 3LL * r.nv * r.nv * r.nv) * (long long)sizeof(T);
+    return r.g != 0 && (r.mib == 0 || num_elems <= ((long long)r.mib << 20) / per);
+}
+
 // f(integral_constant<int, K>) for the first row K of n that a batch of num_elems elements (bytes_per_elem of
 // fields each) fits; f returns its result.  False: past the rows.
 template <const auto &ROWS, int N, int K = 0, typename F>

@@ -381,7 +381,7 @@ struct ConvRectShape {
     static constexpr size_t LDS_BYTES = (size_t)2 * G * CUBE * sizeof(T);
 };
 
-template <typename T, int NV, int NQ, int G, int HINT, bool XCD>
+template <typename T, int NV, int NQ, int G, int HINT, bool XCD, int SB>
 __global__ void __launch_bounds__((ConvRectShape<T, NV, NQ, G>::NT))
 convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const T *Dm_,
                        const T *Im_, T *__restrict__ F, long long num_elems)
@@ -430,7 +430,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
 #pragma unroll
                 for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
             } else {
-                matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(dir == 0 ? Dm : Im, xq, yv);
+                matrix_product<T, NV, NQ, false, SB>(dir == 0 ? Dm : Im, xq, yv);
                 T *dst = dir == 0 ? c0 : c1;
 #pragma unroll
                 for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
@@ -444,10 +444,10 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c0[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, SB>(Dm, xq, zv);
     }
     __syncthreads();                                    // every pencil of cubes 0 and 1 has been read
     if (on_m) {
@@ -457,7 +457,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     // axis l of the third term, into the freed cube 1: lane (n,m)
     if (on_l) {
         const int nn = p / NQ, mm = p - nn * NQ;
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, x2, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, x2, yv);
 #pragma unroll
         for (int i = 0; i < NV; ++i) c1[nn * PA + mm * PB + i] = yv[i];
     }
@@ -466,7 +466,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int j = 0; j < NV; ++j) c1[bn * PA + j * PB + bi] = yv[j];   // the lane's own pencil
     }
@@ -477,10 +477,10 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
         const int jj = p / NV, ii = p - jj * NV;
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = c0[n * PA + jj * PB + ii];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = c1[n * PA + jj * PB + ii];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, SB>(Dm, xq, zv);
         const size_t out = ((size_t)c * (size_t)num_elems + (size_t)e) * VC;
 #pragma unroll
         for (int k = 0; k < NV; ++k)
@@ -497,7 +497,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
 // with that phase's own pencil count, so that these phases (fewer pencils) leave whole wavefronts
 // idle; otherwise a unit keeps its NQ*NQ lanes throughout and part of every wavefront idles, which
 // spreads the stores over more wavefronts.
-template <typename T, int NV, int NQ, int G, int HINT, bool XCD, bool COMPACT>
+template <typename T, int NV, int NQ, int G, int HINT, bool XCD, bool COMPACT, int SB>
 __global__ void __launch_bounds__((ConvRectShape<T, NV, NQ, G>::NT))
 convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const T *Dm_,
                              const T *Im_, T *__restrict__ F, long long num_elems)
@@ -544,7 +544,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
 #pragma unroll
                 for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
             } else {
-                matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(dir == 0 ? Dm : Im, xq, yv);
+                matrix_product<T, NV, NQ, false, SB>(dir == 0 ? Dm : Im, xq, yv);
                 T *dst = lds + (2 * gl + dir) * CUBE;
                 const int nn = pl / NQ, mm = pl - nn * NQ;
 #pragma unroll
@@ -560,10 +560,10 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c0[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, SB>(Dm, xq, zv);
     }
     __syncthreads();                                    // every pencil of cubes 0 and 1 has been read
     if (on_m) {
@@ -574,7 +574,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_l) {
         T *dst = lds + (2 * gl + 1) * CUBE;
         const int nn = pl / NQ, mm = pl - nn * NQ;
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, x2, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, x2, yv);
 #pragma unroll
         for (int i = 0; i < NV; ++i) dst[nn * PA + mm * PB + i] = yv[i];
     }
@@ -583,7 +583,7 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
     if (on_m) {
 #pragma unroll
         for (int m = 0; m < NQ; ++m) xq[m] = c1[bn * PA + m * PB + bi];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int j = 0; j < NV; ++j) c1[bn * PA + j * PB + bi] = yv[j];   // the lane's own pencil
     }
@@ -595,10 +595,10 @@ convection_rect_large_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq,
         const int jj = pn / NV, ii = pn - jj * NV;
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = d0[n * PA + jj * PB + ii];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Im, xq, yv);
+        matrix_product<T, NV, NQ, false, SB>(Im, xq, yv);
 #pragma unroll
         for (int n = 0; n < NQ; ++n) xq[n] = d1[n * PA + jj * PB + ii];
-        matrix_product<T, NV, NQ, false, convection_batch_words<T, NV, NQ>()>(Dm, xq, zv);
+        matrix_product<T, NV, NQ, false, SB>(Dm, xq, zv);
         const long long unit = batch * G + gn;
         const long long e = unit / 3;
         const size_t out = ((size_t)(unit - 3 * e) * (size_t)num_elems + (size_t)e) * VC;
@@ -630,9 +630,10 @@ constexpr int convection_rect_group()
 
 // The utilisation rule's group and the first form, or the second form with a row's settings: the best of a
 // sweep on MI355X over {1, 2, 3, 4, 6, 8, 12} units, the rule's group and both lane numberings, 2 GB per
-// call, kept where it gains 2 % or more.  us per call on 2.5 GB, rule / row: fp64 (5,8) 536 / 493, (6,9)
-// 517 / 479, (8,10) 523 / 441, (8,12) 515 / 486, (10,12) 529 / 472, (11,12) 648 / 479; fp32 (3,4) 492 / 454,
-// (10,12) 527 / 498, (11,13) 546 / 510, (9,14) 517 / 473.
+// call, kept where it gains 2 % or more.  us per call on 2.5 GB, rule / row: fp64 (8,10) 523 / 441, (8,12) 515 / 486,
+// (10,12) 529 / 472, (11,12) 648 / 479; fp32 (3,4) 492 / 454, (10,12) 527 / 498, (11,13) 546 / 510, (9,14) 517 / 473;
+// with buffers in turns fp32 (6,8), (10,11) 0.97, (12,13) 0.93 .. 0.98 of the time.
+// These serve the batches past the rows of ConvRectFirstTable.
 // `from`: MiB of fields from which the row is the faster one.
 //   0: on small batches too, mostly because it takes the smaller workgroups of the two (150 MB: fp64 (8,10) 31.3 /
 //   25.9, (11,12) 45.9 / 33.6).  Larger groups lose there, where a launch is a few rounds of workgroups (2 MB:
@@ -640,22 +641,23 @@ constexpr int convection_rect_group()
 //   256: once the fields pass the last-level cache.
 //   320: up to there the fields are cached in part and the smaller workgroups lead (row over rule at 275 .. 310 MB:
 //   fp64 (6,8) 1.05, (7,8) 1.05, (7,9) 1.06, (9,11) 1.06; fp32 (2,3) 1.02 .. 1.10, (3,4) 1.02 .. 1.05).
+//   60: fp32 (9,11) 0.93 .. 0.98 up to 200 MB, 1.00 .. 1.02 below.
 //   26: fp32 (6,9) 0.95 .. 0.98 up to 300 MB; below 1.05 .. 1.12 at 11 .. 16 and 22 .. 24 MB, 0.84 .. 0.98 between.
 struct ConvRectRow { int nv, nq, g, compact, from; };
 template <typename T> struct ConvRectTable;
 template <> struct ConvRectTable<double> {
     static constexpr ConvRectRow row[] = {
-        {2, 4, 6, 1, 256},   {3, 4, 6, 0, 256}, {5, 8, 4, 0, 256},  {6, 7, 9, 0, 256},  {6, 8, 8, 1, 320},
-        {6, 9, 6, 0, 256},   {7, 8, 8, 0, 320}, {7, 9, 6, 0, 320},  {7, 11, 4, 1, 256}, {8, 9, 3, 0, 256},
-        {8, 10, 1, 0, 0},    {8, 12, 3, 1, 256}, {9, 10, 1, 0, 0},  {9, 11, 2, 0, 320}, {9, 14, 2, 1, 0},
-        {10, 12, 1, 0, 0},   {11, 12, 1, 0, 0},
+        {2, 4, 6, 1, 256},   {3, 4, 6, 0, 256},  {6, 8, 8, 1, 320},  {7, 8, 8, 0, 320}, {7, 9, 6, 0, 320},
+        {7, 11, 4, 1, 256},  {8, 10, 1, 0, 0},   {8, 12, 3, 1, 256}, {9, 10, 1, 0, 0},  {9, 11, 2, 0, 320},
+        {9, 14, 2, 1, 0},    {10, 12, 1, 0, 0},  {11, 12, 1, 0, 0},
     };
 };
 template <> struct ConvRectTable<float> {
     static constexpr ConvRectRow row[] = {
         {2, 3, 12, 1, 320},  {2, 4, 12, 0, 256},  {3, 4, 8, 1, 320},   {3, 5, 8, 1, 256}, {4, 5, 8, 1, 256},
-        {5, 8, 6, 0, 256},   {6, 9, 4, 1, 26},    {8, 10, 3, 1, 0},    {8, 12, 2, 1, 0},  {9, 11, 2, 1, 256},
-        {9, 14, 2, 1, 0},    {10, 12, 2, 1, 256}, {11, 13, 3, 1, 256}, {12, 14, 2, 1, 256},
+        {5, 8, 6, 0, 256},   {6, 8, 6, 1, 256},   {6, 9, 4, 1, 26},    {8, 10, 3, 1, 0},  {8, 12, 2, 1, 0},
+        {9, 11, 2, 1, 60},   {9, 14, 2, 1, 0},    {10, 11, 2, 0, 256}, {10, 12, 2, 1, 256}, {11, 13, 3, 1, 256},
+        {12, 13, 3, 1, 256},
     };
 };
 template <typename T>
@@ -674,7 +676,7 @@ constexpr long long convection_elems(long long bytes)
     return bytes / ((10LL * NQ * NQ * NQ + 3LL * NV * NV * NV) * (long long)sizeof(T));
 }
 
-template <typename T, int NV, int NQ, int G, bool LARGE, bool COMPACT>
+template <typename T, int NV, int NQ, int G, bool LARGE, bool COMPACT, int SB = convection_batch_words<T, NV, NQ>()>
 struct ConvectionRectLauncherT {
     using Sh = ConvRectShape<T, NV, NQ, G>;
     static constexpr size_t LDS = Sh::LDS_BYTES;
@@ -683,8 +685,8 @@ struct ConvectionRectLauncherT {
 
     static constexpr auto kernel()
     {
-        if constexpr (LARGE) return &convection_rect_large_kernel<T, NV, NQ, G, HINT, XCD, COMPACT>;
-        else return &convection_rect_kernel<T, NV, NQ, G, HINT, XCD>;
+        if constexpr (LARGE) return &convection_rect_large_kernel<T, NV, NQ, G, HINT, XCD, COMPACT, SB>;
+        else return &convection_rect_kernel<T, NV, NQ, G, HINT, XCD, SB>;
     }
 
     static hipError_t launch(const ConvectionArgs &a)
@@ -716,11 +718,24 @@ struct ConvectionRectLauncher {
     using Row = ConvectionRectLauncherT<T, NV, NQ, R.g != 0 ? R.g : 1, true, R.compact != 0>;
     using Small = std::conditional_t<ROW_ONLY, Row, Rule>;
     using Large = std::conditional_t<R.g != 0, Row, Rule>;
+    // A shape has at most three rows of ConvRectFirstTable; a last one with mib = 0 leaves nothing to the two settings.
+    template <int K> static constexpr ConvRectFirst first_row = convection_rect_first<T>(NV, NQ, K);
+    template <int K> static constexpr bool is_row = first_row<K>.g != 0;
+    template <int K> static constexpr bool every = is_row<K> && first_row<K>.mib == 0;
+    static_assert(!is_row<3>, "launch() looks at three rows");
+    static constexpr bool FIRST_ONLY = every<0> || every<1> || every<2>;
+    template <int K> using First = ConvectionRectLauncherT<T, NV, NQ, first_row<K>.g, first_row<K>.form != 0,
+                                                           first_row<K>.form == 2, first_row<K>.sb>;
 
     static hipError_t launch(const ConvectionArgs &a)
     {
-        return takes_large(a.num_elems) ? Large::launch(a) : Small::launch(a);
+        if constexpr (is_row<0>) if (convection_rect_fits<T>(first_row<0>, a.num_elems)) return First<0>::launch(a);
+        if constexpr (is_row<1>) if (convection_rect_fits<T>(first_row<1>, a.num_elems)) return First<1>::launch(a);
+        if constexpr (is_row<2>) if (convection_rect_fits<T>(first_row<2>, a.num_elems)) return First<2>::launch(a);
+        if constexpr (FIRST_ONLY) return kGridTooLarge;                 // not reached
+        else return takes_large(a.num_elems) ? Large::launch(a) : Small::launch(a);
     }
+    // Of the two settings past the rows.
     static bool takes_large(long long num_elems)
     {
         if (ROW_ONLY) return true;
@@ -733,8 +748,15 @@ struct ConvectionRectLauncher {
     }
     static hipError_t prepare()
     {
-        const hipError_t rc = Large::prepare();
-        return rc != hipSuccess ? rc : Small::prepare();
+        hipError_t rc = hipSuccess;
+        if constexpr (is_row<0>) rc = First<0>::prepare();
+        if constexpr (is_row<1>) if (rc == hipSuccess) rc = First<1>::prepare();
+        if constexpr (is_row<2>) if (rc == hipSuccess) rc = First<2>::prepare();
+        if constexpr (!FIRST_ONLY) {
+            if (rc == hipSuccess) rc = Large::prepare();
+            if (rc == hipSuccess) rc = Small::prepare();
+        }
+        return rc;
     }
 };
 

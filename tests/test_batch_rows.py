@@ -19,6 +19,17 @@ def test_rows_are_in_order(which, dtype):
     assert row(which, 17, dtype, 1) == -1
 
 
+@pytest.mark.parametrize("dtype", [tpo.TPO_F64, tpo.TPO_F32])
+def test_over_integrated_rows_are_in_order(dtype):
+    row = tpo.lib().tpo_internal_convection_rect_row
+    row.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    for nv in range(2, 13):
+        for nq in range(nv + 1, 17):
+            got = [row(nv, nq, dtype, e) for e in (int(1.05 ** k) for k in range(420))]
+            cut = got.index(-1) if -1 in got else len(got)
+            assert got[:cut] == sorted(got[:cut]) and set(got[cut:]) <= {-1}
+
+
 P, M, X = tpo.TPO_VARIANT_PENCIL, tpo.TPO_VARIANT_MFMA, tpo.TPO_VARIANT_PENCIL_MM
 
 

@@ -98,23 +98,38 @@ def test_rows(op, n, dtype):
         assert oracle.max_rel_err_per_element(out[tail].cpu().numpy(), ref) <= TOL[dtype]
 
 
+OVER = [(5, 6), (5, 7), (5, 8), (6, 7), (6, 8), (6, 9), (7, 8), (7, 9), (8, 9), (8, 10), (8, 12), (9, 10), (9, 14), (10, 12),
+        (11, 12), (11, 13), (12, 13), (12, 14)]
+
+
+def rect_edges(nv, nq, dtype):
+    """Largest batch of each row of an over-integrated shape, up to 300 MB; 1001 where one row serves every batch."""
+    row = tpo.lib().tpo_internal_convection_rect_row
+    row.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
+    code, word = (tpo.TPO_F64, 8) if dtype == "f64" else (tpo.TPO_F32, 4)
+    most = int(300e6 / ((10 * nq ** 3 + 3 * nv ** 3) * word))
+    got = [row(nv, nq, code, e) for e in range(1, most + 1)]
+    sizes = [e for e in range(1, most) if got[e - 1] != got[e]]
+    return sizes or ([1001] if got[0] >= 0 else [])
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("n", range(5, 17))
-def test_convection_rows(n, dtype):
+@pytest.mark.parametrize("n,nq", [(n, n) for n in range(5, 17)] + OVER)
+def test_convection_rows(n, nq, dtype):
     """The same for the convection term.  The matrix-core and the vector form add in the same order too."""
-    sizes = edges("conv", n, dtype)
+    sizes = edges("conv", n, dtype) if n == nq else rect_edges(n, nq, dtype)
     if not sizes:
         pytest.skip("no rows")
     real, kind, _ = REAL[dtype]
     rng = np.random.default_rng([19906, 84, n])
-    d, i = (dev(rng.uniform(-1, 1, (n, n)).astype(real)) for _ in range(2))
+    d, i = (dev(rng.uniform(-1, 1, (n, nq)).astype(real)) for _ in range(2))
     gen = torch.Generator(device="cuda").manual_seed(n)
     most = sizes[-1] + 1
-    p = torch.empty((3, 3, most, n, n, n), device="cuda", dtype=kind).uniform_(-1, 1, generator=gen)
-    m = torch.empty((most, n, n, n), device="cuda", dtype=kind).uniform_(0.5, 2, generator=gen)
+    p = torch.empty((3, 3, most, nq, nq, nq), device="cuda", dtype=kind).uniform_(-1, 1, generator=gen)
+    m = torch.empty((most, nq, nq, nq), device="cuda", dtype=kind).uniform_(0.5, 2, generator=gen)
     part = lambda at: (p[:, :, at].contiguous(), m[at])
     for e in sorted({x + k for x in sizes for k in (0, 1)}):
-        print(f"case convection rows {dtype} n={n} E={e}", flush=True)
+        print(f"case convection rows {dtype} ({n},{nq}) E={e}", flush=True)
         out = torch.full((3, e, n, n, n), float("nan"), device="cuda", dtype=kind)
         tpo.convection_tensors(*part(slice(0, e)), d, i, F=out)
         torch.cuda.synchronize()
