@@ -65,7 +65,7 @@ def loaded_state(torch, launch, seconds=0.3, batch=20):
 
 # Sources that make up the kernels of each operation (headers they include, their instantiation
 # files); everything an operation's kernels are compiled from.
-_COMMON = ["tpo_internal.h", "tpo_pencil.hpp", "tpo_pencil_mm.hpp"]
+_COMMON = ["tpo_batch_rows.hpp", "tpo_internal.h", "tpo_pencil.hpp", "tpo_pencil_mm.hpp"]
 KERNEL_SOURCES = {
     "ihelm": _COMMON + ["tpo_mfma.hpp", "tpo_mfma_f64.hip", "tpo_mfma_f32.hip", "tpo_pencil_f64.hip",
                         "tpo_pencil_f32.hip", "tpo_pencil_mm_f32.hip"],

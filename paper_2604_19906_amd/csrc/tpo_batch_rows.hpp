@@ -18,6 +18,7 @@
 //   separable fp32   n = 2 .. 6 0.63 .. 0.92 at 12 .. 170 MB; n = 9, 10 0.85 .. 0.94
 //   halves           fp64 n = 3, 5, 9 .. 15 0.68 .. 0.93 at 25 .. 170 MB, n = 10 .. 13 0.91 .. 0.96 at 300 MB .. 1.2 GB; fp32 n = 3, 5, 6,
 //                    10, 11, 13 .. 15 0.66 .. 0.9 at 100 .. 170 MB
+//                    (n = 13 without renumbering by die: 1.03 .. 1.04 of the time at 8 GB, so up to 1.6 GB only)
 #pragma once
 
 #include <type_traits>
@@ -160,7 +161,7 @@ template <> struct TransformRows<float> {
         /* 10 */ {{184, 2, 2, 0, 0, 1}, {1650, 2, 0, 0, 32, 0}},
         /* 11 */ {{39, 1, 2, 1, 0, 1}, {85, 2, 0, 0, 0, 1}, {184, 1, 2, 1, 0, 1}, {1650, 2, 0, 0, 32, 0}},
         /* 12 */ {{9, 3, 2, 1, 0, 1}, {39, 2, 2, 0, 0, 1}, {640, 3, 2, 0, 0, 1}},
-        /* 13 */ {{184, 1, 2, 1, 0, 1}},
+        /* 13 */ {{184, 1, 2, 1, 0, 1}, {1650, 3, 0, 0, 0, 1}},
         /* 14 */ {{874, 1, 2, 0, 0, 1}},
         /* 15 */ {{14, 1, 0, 0, 0, 1}, {184, 1, 2, 0, 0, 1}},
         {},
@@ -168,7 +169,7 @@ template <> struct TransformRows<float> {
 };
 
 // Convection term, square shapes: SPLIT and all loads first as in convection_pencil_kernel.  Time over the settings there were
-// before, 16 sizes from 1 MB to 2.5 GB: fp32 n = 8 0.82 .. 1.0 (matrix-core form), 10 0.73 .. 0.97, 13 0.65 .. 0.96 but 1.01 at 55 .. 110 MB, 14 0.73 ..
+// before, 16 sizes from 1 MB to 2.5 GB: fp32 n = 8 0.82 .. 1.0 (matrix-core form), 10 0.73 .. 0.97, 13 0.65 .. 0.96 up to 2.5 GB (1.01 at 55 .. 110 MB; beyond 2.5 GB three units lead by 1 %), 14 0.73 ..
 // 0.96, 9, 11, 12 0.75 .. 0.96 up to 8 MB; fp64 n = 6, 9 0.79 .. 0.95 up to 220 MB, 11 0.87 .. 0.94 up to 22 MB, 12 .. 16 0.95 .. 0.98 up to 22 MB and,
 // with SB = 40, 0.89 .. 0.98 at 35 .. 220 MB.
 struct ConvectionRow { int mib, g, hint, split, loads_first, sb, mm; };
@@ -197,7 +198,7 @@ template <> struct SquareConvectionRows<float> {
         /* 10 */ {{5, 1, 0, 0, 1, 0, 1}},
         /* 11 */ {{17, 1, 0, 1, 1, 0, 1}, {253, 2, 2, 1, 0, 0, 1}},
         /* 12 */ {{13, 1, 2, 0, 1, 0, 1}},
-        /* 13 */ {{17, 1, 0, 0, 1, 0, 1}, {24, 3, 2, 1, 1, 0, 1}},
+        /* 13 */ {{17, 1, 0, 0, 1, 0, 1}, {24, 3, 2, 1, 1, 0, 1}, {2600, 1, 2, 1, 1, 0, 1}},
         /* 14 */ {{17, 1, 0, 0, 1, 0, 1}, {123, 1, 2, 0, 1, 0, 1}},
         /* 15 */ {{17, 1, 0, 0, 1, 0, 1}, {64, 1, 2, 1, 0, 0, 1}},
         {},

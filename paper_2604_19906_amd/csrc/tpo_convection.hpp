@@ -773,7 +773,7 @@ struct ConvectionRectEntry {
 // 4x4x1 matrix-core form (the vector-FMA form is bound by FMA issue there, as for the operator).  A sweep of units x
 // SPLIT x form x order of the loads x HINT over 0.5 MB .. 2.5 GB on MI355X, with buffers that take turns, found better
 // settings for the n below (time over ConvectionTune's at 400 MB / 2.5 GB: fp64 n = 6 0.97 / 0.98; fp32 n = 10
-// 0.92 / 0.97, 13 0.94 / 1.01, 14 0.86 / 0.98; fp64 n = 7, 10 and fp32 n = 7 from an earlier sweep: 430 / 454, 432 / 484,
+// 0.92 / 0.97, 14 0.86 / 0.98; fp64 n = 7, 10 and fp32 n = 7 from an earlier sweep: 430 / 454, 432 / 484,
 // 446 / 462 us on 2.5 GB), and for smaller batches the rows of SquareConvectionRows.  fp32 n = 8 in the matrix-core
 // form: 0.83 .. 0.95 of the time on 9 .. 200 MB, the same elsewhere.  ConvectionLargeTune pays only once the fields
 // pass the last-level cache (2.5 GB: fp64 n = 3 525 / 499, 9 460 / 444; fp32 n = 3 567 / 516, 5 486 / 468,
@@ -797,7 +797,6 @@ template <> struct ConvectionBase<float, 8> : ConvectionSet<float, 8, 1, true, t
 template <> struct ConvectionBase<float, 9> : ConvectionSet<float, 9, 3, true, true> {};
 template <> struct ConvectionBase<float, 10> : ConvectionSet<float, 10, 2, false, true, true> {};
 template <> struct ConvectionBase<float, 12> : ConvectionSet<float, 12, 3, true, true> {};
-template <> struct ConvectionBase<float, 13> : ConvectionSet<float, 13, 1, true, true> {};
 template <> struct ConvectionBase<float, 14> : ConvectionSet<float, 14, 2, false, true> {};
 template <typename T, int N> struct ConvectionLargeTune : ConvectionBase<T, N> {
     // fp64 on large batches (3 GB, with / without: n = 11 527 / 551 us, 12 569 / 582,

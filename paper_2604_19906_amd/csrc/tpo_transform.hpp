@@ -188,7 +188,7 @@ template <int GG, int H, bool X, bool M, long long MB = 256, int S = kScalarBatc
 };
 template <typename T> struct TransformTune<T, 2> : TransformSet<16, 0, false, false> {};
 template <> struct TransformTune<float, 12> : TransformSet<3, 2, true, true> {};
-template <> struct TransformTune<float, 13> : TransformSet<3, 0, false, true> {};
+template <> struct TransformTune<float, 13> : TransformSet<3, 0, true, true> {};
 template <> struct TransformTune<float, 14> : TransformSet<2, 0, false, true> {};
 template <> struct TransformTune<float, 15> : TransformSet<1, 0, false, true> {};
 template <> struct TransformTune<float, 16> : TransformSet<1, 2, false, true> {};
