@@ -421,12 +421,13 @@ struct PencilTune {
 // the clock runs higher), alternating libraries on one box, ms per launch: this setting 1.421-
 // 1.424; the same with cached u_e loads 1.450-1.452; 26 KB / 30 KB requests 1.465 / 1.421-1.430;
 // one element per workgroup with 18 KB (the earlier choice) 1.441-1.462, with 14 KB 1.469;
-// three / four elements per workgroup 1.518 / 1.472.
+// three / four elements per workgroup 1.518 / 1.472.  Scalars in batches: 1.444 against 1.435 here (the rows by batch
+// size, which serve everything up to 1650 MiB, take them).
 template <> struct PencilTune<double, 11> {
     static constexpr int G = 2, HINT = 1;
     static constexpr bool DDIRECT = true, XCD = true;
     static constexpr size_t LDS_MIN = 28 * 1024;
-    static constexpr int SB = kScalarBatch;
+    static constexpr int SB = 0;
 };
 
 // Tuning of the separable-diagonal form: as the D form unless measured otherwise.  Without the
@@ -438,6 +439,7 @@ struct PencilSepTune : PencilTune<T, N> {};
 template <> struct PencilSepTune<double, 11> : PencilTune<double, 11> {
     static constexpr int G = 1, HINT = 0;
     static constexpr size_t LDS_MIN = 0;
+    static constexpr int SB = kScalarBatch;
 };
 template <> struct PencilSepTune<double, 8> : PencilTune<double, 8> {
     static constexpr int G = 1;
