@@ -1,11 +1,13 @@
-"""Builds libtpo.so (the C-ABI library of the operator) and libtpo_bench.so (the benchmark's
-measurement aid) for gfx950 with hipcc, in-tree.
+"""Builds libtpo.so (the C-ABI library of the operator), libtpo_bench.so (the benchmark's
+measurement aid) for gfx950 with hipcc and _tpo_torch.so (the native form of the binding's tensor
+functions, host code), in-tree.
 
     python -m paper_2604_19906_amd.build          # compile every source and link
 
 Every translation unit under ``csrc/`` is compiled to an object under ``_build/`` (in
 parallel).  Those named ``bench_*`` are linked into ``paper_2604_19906_amd/libtpo_bench.so``
-(``include/tpo_bench.h``), all others into ``paper_2604_19906_amd/libtpo.so``
+(``include/tpo_bench.h``), ``torch_binding.cpp`` against torch's libraries into
+``paper_2604_19906_amd/_tpo_torch.so``, all others into ``paper_2604_19906_amd/libtpo.so``
 (``include/tpo.h``).  hipcc cross-compiles for gfx950 without a GPU being present.
 """
 from __future__ import annotations
@@ -13,6 +15,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -21,6 +24,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtpo.so")
 BENCH_LIB = os.path.join(HERE, "libtpo_bench.so")
+TORCH_BINDING = os.path.join(HERE, "_tpo_torch.so")
 
 ARCH = "gfx950"
 # Packed-FP32 VALU instructions are switched off for all device code.
@@ -33,7 +37,7 @@ HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall", "-
 
 
 def sources():
-    return sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
+    return sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")) and not f.startswith("torch_"))
 
 
 def _compile(src: str) -> str:
@@ -50,11 +54,32 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_torch_binding() -> None:
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               os.path.join(rocm, "include"), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    tmp = TORCH_BINDING + f".tmp{os.getpid()}"
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           + ["-isystem" + d for d in include]
+           + [os.path.join(CSRC, "torch_binding.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"),
+              "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on torch_binding.cpp:\n" + r.stderr)
+    os.replace(tmp, TORCH_BINDING)
+
+
 def build(jobs: int = 8, verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
-    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(srcs)))) as ex:
+    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(srcs) + 1))) as ex:
+        binding = ex.submit(_build_torch_binding)
         objs = list(ex.map(_compile, srcs))
+        binding.result()
     for lib, part in ((LIB, [o for s_, o in zip(srcs, objs) if not s_.startswith("bench_")]),
                       (BENCH_LIB, [o for s_, o in zip(srcs, objs) if s_.startswith("bench_")])):
         tmp = lib + f".tmp{os.getpid()}"
@@ -65,6 +90,8 @@ def build(jobs: int = 8, verbose: bool = True) -> str:
         os.replace(tmp, lib)
         if verbose:
             print(f"built {lib} from {len(part)} sources")
+    if verbose:
+        print(f"built {TORCH_BINDING}")
     return LIB
 
 

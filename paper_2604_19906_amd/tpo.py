@@ -210,6 +210,42 @@ def _runtime():
     return _rt
 
 
+# The same functions as one native call (csrc/torch_binding.cpp).  It takes the plain case only and returns None for
+# everything else, which the Python forms below then check, refuse or compute; a number is a status.  False: not there.
+TORCH_BINDING_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_tpo_torch.so")
+_native = None
+
+
+def _load_native():
+    global _native
+    _native = False
+    if os.path.exists(TORCH_BINDING_PATH):
+        import importlib.util
+        import warnings
+
+        import torch  # noqa: F401  (the libraries that the binding is linked to)
+
+        l = lib()
+        spec = importlib.util.spec_from_file_location("_tpo_torch", TORCH_BINDING_PATH)
+        try:
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+        except ImportError as e:        # built for another torch
+            warnings.warn(f"{TORCH_BINDING_PATH} cannot be loaded ({e}): tensor functions run in their Python form")
+            return _native
+        module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            l.tpo_ihelm_apply_variant, l.tpo_ihelm_apply_sep_variant, l.tpo_transform_apply, l.tpo_convection_apply,
+            l.tpo_ihelm_apply_aniso)))
+        _native = module
+    return _native
+
+
+def _done(r, what):
+    if type(r) is int:
+        raise TpoError(r, what)
+    return r
+
+
 _CONTIG = "all tensors must be contiguous device tensors of one dtype"
 
 
@@ -246,6 +282,11 @@ def _mat_ptrs(S_x, S_y, S_z):
 def apply_tensors(u, S_x, S_y, S_z, D, v=None, variant: int = TPO_VARIANT_AUTO):
     """Convenience over torch device tensors: marshals pointers, shape and the current
     stream; raises TpoError on a non-zero status.  Returns ``v`` (allocated if None)."""
+    fast = _native if _native is not None else _load_native()
+    if fast:
+        r = fast.apply(u, S_x, S_y, S_z, D, v, variant)
+        if r is not None:
+            return r if r is v else _done(r, "tpo_ihelm_apply")
     shape = u.shape
     if len(shape) != 4 or not u.is_cuda:
         raise ValueError("u must be a device tensor of shape [E,n,n,n]")
@@ -271,6 +312,11 @@ def apply_sep_tensors(u, S_x, S_y, S_z, lam_x, lam_y, lam_z, mu, v=None,
                       variant: int = TPO_VARIANT_AUTO):
     """Separable-diagonal form over torch device tensors (``lam_*`` are ``[n]``, ``mu`` is
     ``[E]``); marshalling only, like :func:`apply_tensors`."""
+    fast = _native if _native is not None else _load_native()
+    if fast:
+        r = fast.apply_sep(u, S_x, S_y, S_z, lam_x, lam_y, lam_z, mu, v, variant)
+        if r is not None:
+            return r if r is v else _done(r, "tpo_ihelm_apply_sep")
     shape = u.shape
     if len(shape) != 4 or not u.is_cuda:
         raise ValueError("u must be a device tensor of shape [E,n,n,n]")
@@ -300,6 +346,11 @@ def apply_sep_tensors(u, S_x, S_y, S_z, lam_x, lam_y, lam_z, mu, v=None,
 
 def transform_tensors(u, S_x, S_y, S_z, direction: int, t=None):
     """One half of the operator over torch device tensors; marshalling only."""
+    fast = _native if _native is not None else _load_native()
+    if fast:
+        r = fast.transform(u, S_x, S_y, S_z, direction, t)
+        if r is not None:
+            return r if r is t else _done(r, "tpo_transform_apply")
     shape = u.shape
     if len(shape) != 4 or not u.is_cuda:
         raise ValueError("u must be a device tensor of shape [E,n,n,n]")
@@ -325,6 +376,11 @@ def convection_tensors(P, M, D_vq, I_vq, F=None):
     """Convection volume term over torch device tensors (``P`` ``[3,3,E,nq,nq,nq]``, ``M``
     ``[E,nq,nq,nq]``, ``D_vq``/``I_vq`` ``[nv,nq]``); marshalling only.  Returns ``F``
     ``[3,E,nv,nv,nv]``."""
+    fast = _native if _native is not None else _load_native()
+    if fast:
+        r = fast.convection(P, M, D_vq, I_vq, F)
+        if r is not None:
+            return r if r is F else _done(r, "tpo_convection_apply")
     dt = P.dtype
     if not (_plain(P, dt) and _plain(M, dt) and _plain(D_vq, dt) and _plain(I_vq, dt)):
         raise ValueError(_CONTIG)
@@ -356,6 +412,11 @@ def apply_aniso_tensors(u, S_x, S_y, S_z, D, v=None):
     """The operator on anisotropic elements over torch device tensors (``u``, ``D``
     ``[E,nx,ny,nz]``; ``S_x`` ``[nx,nx]``, ``S_y`` ``[ny,ny]``, ``S_z`` ``[nz,nz]``);
     marshalling only."""
+    fast = _native if _native is not None else _load_native()
+    if fast:
+        r = fast.apply_aniso(u, S_x, S_y, S_z, D, v)
+        if r is not None:
+            return r if r is v else _done(r, "tpo_ihelm_apply_aniso")
     shape = u.shape
     if len(shape) != 4 or not u.is_cuda or D.shape != shape:
         raise ValueError("u and D must be device tensors of shape [E,nx,ny,nz]")

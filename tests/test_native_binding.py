@@ -1,0 +1,166 @@
+"""The tensor functions' native form against their Python form: the same results, the same errors, the same stream; whatever is
+not a plain device tensor is left to the Python form."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_19906_amd import tpo
+
+N, E = 5, 7
+SHAPES = {  # function -> its arguments' shapes
+    "apply_tensors": [(E, N, N, N), (N, N), (N, N), (N, N), (E, N, N, N)],
+    "apply_sep_tensors": [(E, N, N, N), (N, N), (N, N), (N, N), (N,), (N,), (N,), (E,)],
+    "transform_tensors": [(E, N, N, N), (N, N), (N, N), (N, N)],
+    "convection_tensors": [(3, 3, E, N, N, N), (E, N, N, N), (N, N), (N, N)],
+    "apply_aniso_tensors": [(E, N, N + 1, N + 2), (N, N), (N + 1, N + 1), (N + 2, N + 2), (E, N, N + 1, N + 2)],
+}
+NATIVE = {"apply_tensors": "apply", "apply_sep_tensors": "apply_sep", "transform_tensors": "transform",
+          "convection_tensors": "convection", "apply_aniso_tensors": "apply_aniso"}
+
+
+def arguments(name, device, dtype=torch.float64):
+    g = torch.Generator().manual_seed(len(name))
+    a = [(torch.rand(s, generator=g, dtype=torch.float64) + 0.1).to(dtype).to(device) for s in SHAPES[name]]
+    return a + [tpo.TPO_BACKWARD] if name == "transform_tensors" else a
+
+
+def out_shape(name):
+    return (3, E, N, N, N) if name == "convection_tensors" else SHAPES[name][0]
+
+
+def outcome(name, args, **kw):
+    try:
+        return getattr(tpo, name)(*args, **kw)
+    except Exception as e:      # noqa: BLE001  (compared with the other form's)
+        return type(e), str(e)
+
+
+def test_present_and_declines_host_tensors():
+    module = tpo._load_native()
+    assert module, "the native binding is not built"
+    for name in SHAPES:
+        args = arguments(name, "cpu") + [None] + ([0] if name in ("apply_tensors", "apply_sep_tensors") else [])
+        assert getattr(module, NATIVE[name])(*args) is None
+        assert getattr(module, NATIVE[name])() is None and getattr(module, NATIVE[name])(*[3] * len(args)) is None
+        kind, _ = outcome(name, arguments(name, "cpu"))
+        assert kind is ValueError
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def strided(t):
+    return torch.stack([t, t], dim=-1)[..., 0]
+
+
+# how one tensor argument is replaced; what no form accepts stays refused, what the Python form accepts is computed by it
+FORMS = {
+    "plain": lambda t: t,
+    "subclass": lambda t: t.as_subclass(Sub),
+    "parameter": lambda t: torch.nn.Parameter(t),
+    "requires_grad": lambda t: t.clone().requires_grad_(),
+    "detached view": lambda t: t.detach()[...],
+    "negated view": lambda t: torch.complex(t, -t).conj().imag if t.dtype == torch.float64 else t,
+    "strided": strided,
+    "host": lambda t: t.cpu(),
+    "other type": lambda t: t.to(torch.float32 if t.dtype == torch.float64 else torch.float64),
+    "half": lambda t: t.half(),
+    "wrong size": lambda t: torch.cat([t, t]),
+    "more axes": lambda t: t[None],
+    "empty": lambda t: t[:0],
+    "a number": lambda t: 3.0,
+    "none": lambda t: None,
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(SHAPES))
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_same_outcome(name, dtype, monkeypatch):
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    module = tpo._load_native()
+    assert module
+    key = {"transform_tensors": "t", "convection_tensors": "F"}.get(name, "v")
+
+    def both(args, **kw):
+        got = []
+        for native in (module, False):
+            monkeypatch.setattr(tpo, "_native", native)
+            # results that the call leaves in an output of the caller's are compared too
+            kws = {k: v.clone() if isinstance(v, torch.Tensor) else v for k, v in kw.items()}
+            r = outcome(name, args, **kws)
+            got.append((r, kws.get(key)))
+        monkeypatch.setattr(tpo, "_native", module)
+        (a, va), (b, vb) = got
+        if isinstance(b, torch.Tensor):
+            assert isinstance(a, torch.Tensor) and torch.equal(a, b) and a.stride() == b.stride()
+            assert a.requires_grad == b.requires_grad
+            assert (a is va) == (b is vb)
+        else:
+            assert a == b
+        if isinstance(va, torch.Tensor) and va.shape == vb.shape:
+            assert torch.equal(va, vb)
+
+    base = arguments(name, "cuda", dtype)
+    tensors = [k for k, a in enumerate(base) if isinstance(a, torch.Tensor)]
+    for label, change in FORMS.items():
+        for k in tensors:
+            print(f"case native {name} {dtype} argument {k} {label}", flush=True)
+            both([change(a) if i == k else a for i, a in enumerate(base)])
+        out = torch.zeros(out_shape(name), dtype=dtype, device="cuda")
+        both(base, **{key: change(out)})
+    both([base[0][:0] if i in (0, 4) and name != "transform_tensors" else a for i, a in enumerate(base)])
+    both(base[:1] + [base[1]] * 3 + base[4:])               # one matrix for all directions
+    if name in ("apply_tensors", "apply_sep_tensors"):
+        for variant in (1, 2, 3, 9, -1, 1 << 40, True, np.int64(1)):
+            both(base, variant=variant)
+    if name == "transform_tensors":
+        for direction in (0, 1, 2, -1, True, np.int32(1)):
+            both(base[:4] + [direction])
+
+    # the plain case is the native form's: it returns the caller's tensor, not None
+    tail = [0] if name in ("apply_tensors", "apply_sep_tensors") else []
+    out = torch.zeros(out_shape(name), dtype=dtype, device="cuda")
+    assert getattr(module, NATIVE[name])(*base, out, *tail) is out
+    torch.cuda.synchronize()
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
+
+
+@pytest.mark.gpu
+def test_wrapped_tensors_and_streams():
+    """A vmap wrapper is a torch.Tensor by type: left to the Python form, which refuses it.  The call goes to the current stream
+    and can be captured there."""
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    module = tpo._load_native()
+    u, sx, sy, sz, d = arguments("apply_tensors", "cuda")
+    seen = []
+
+    def inner(x):
+        seen.append(module.apply(x, sx, sy, sz, d, None, 0))
+        return x
+
+    torch.func.vmap(inner)(u[None])
+    torch.func.grad(lambda x: inner(x).sum())(u.clone())
+    assert seen == [None, None]
+
+    want = tpo.apply_tensors(u, sx, sy, sz, d)
+    v = torch.zeros_like(u)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            assert tpo.apply_tensors(u, sx, sy, sz, d, v=v) is v
+    assert not v.any()                                      # recorded, not run
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(v, want)
+        v.zero_()
+        torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        tpo.apply_tensors(u, sx, sy, sz, d, v=v)
+    side.synchronize()
+    assert torch.equal(v, want)
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
