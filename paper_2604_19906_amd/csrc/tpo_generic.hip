@@ -17,7 +17,16 @@
 // u_e (for a fixed index along axis 0 the lanes of that pass are consecutive words), axis 1,
 // then axis 2 forward, the scale and axis 2 backward on the lane's registers (each lane asked
 // for the nz consecutive words of D_e it needs when the kernel started), axis 1, and axis 0
-// last, stored coalesced to v_e.  Four barriers, no index arithmetic per word.
+// last, stored coalesced to v_e.  Four barriers.
+//
+// What the runtime sizes cost is integer work: divisions (20 instructions, five of them at a quarter of the rate) for the place of a
+// lane in each pass, 64-bit address sums per word, and products for LDS addresses, 20 .. 40 % of a wavefront's vector
+// instructions with three axes of 5 .. 7 points, 16 .. 23 % at 8 .. 16.  They are reciprocals in 24 bits, one uniform base that moves
+// along the axis with a 32-bit offset per lane, and one addition per LDS word now; the stores leave in ascending order, which
+// the 128-byte lines that two of them share need (in the compiler's order fp32 (5,5,6) wrote 1.20 of its bytes at 2.4 GB).  Time over
+// the kernels before, arguments in scalar registers included, geometric means over 120 shapes per type at 1 / 8 / 24 / 60 / 100 /
+// 300 MB / 1 / 2.4 GB: fp64 .90 .90 .93 .96 .94 .95 .95 .96 (one turn), turns .94 from 100 MB on; fp32 .88 .84 .90 .92 .91 .90 .89
+// .90, turns .92 .. .94.  One of 1800 calls is slower by more than 4 % (fp64 (14,9,14) at 60 MB, 1.07).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -69,75 +78,182 @@ __device__ __forceinline__ void dispatch_size(int n, F &&f)
 __host__ __device__ inline int aniso_pz(int nz) { return nz | 1; }
 __host__ __device__ inline int aniso_pyz(int ny, int nz) { return (ny * aniso_pz(nz)) | 1; }
 
+// a * b and a * b + c for a, b < 2^24, b uniform: one instruction at the full rate.  Left to itself the compiler takes
+// 32-bit products (a quarter of the rate) where it cannot see the bounds.
+__device__ __forceinline__ unsigned mul24(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_mul_u32_u24 %0, %1, %2" : "=v"(r) : "s"(b), "v"(a));
+    return r;
+}
+__device__ __forceinline__ unsigned mad24(unsigned a, unsigned b, unsigned c)
+{
+    unsigned r;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
+}
+
+// Upper 32 bits of a * b.
+__device__ __forceinline__ unsigned mulhi24(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(r) : "s"(b), "v"(a));
+    return r;
+}
+
+// N words of LDS a runtime number of bytes apart, from byte address `at` on.  The address moves by one addition per word;
+// opaque, since the compiler would rather multiply (v_mad_u64_u32, a quarter of the rate) than keep the chain.
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+template <typename T, int N, typename F>
+__device__ __forceinline__ void each_word(unsigned at, unsigned step, F &&f)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        f(i, *reinterpret_cast<__attribute__((address_space(3))) T *>(reinterpret_cast<lds_byte *>(at)));
+        at += step;
+        asm("" : "+v"(at));
+    }
+}
+template <typename T, int N>
+__device__ __forceinline__ void lds_read(unsigned at, unsigned step, T (&x)[N])
+{
+    each_word<T, N>(at, step, [&](int i, const __attribute__((address_space(3))) T &w) { x[i] = w; });
+}
+template <typename T, int N>
+__device__ __forceinline__ void lds_write(unsigned at, unsigned step, const T (&x)[N])
+{
+    each_word<T, N>(at, step, [&](int i, __attribute__((address_space(3))) T &w) { w = x[i]; });
+}
+__device__ __forceinline__ unsigned lds_address(const void *p)
+{
+    return (unsigned)(unsigned long long)reinterpret_cast<const lds_byte *>((const __attribute__((address_space(3))) void *)p);
+}
+
+// A uniform value as it stands in a scalar register (k * NT + lane would become a v_mad_u64_u32).
+__device__ __forceinline__ unsigned scalar(unsigned s)
+{
+    asm("" : "+s"(s));
+    return s;
+}
+
+// N words of HBM a runtime number of bytes apart: the uniform base moves (scalar additions, kept next to their access: hoisted
+// out of the turns they spill), the lane's 32-bit offset stays.
+template <bool NT, typename T, int N>
+__device__ __forceinline__ void global_read(const char *base, unsigned step, unsigned off, T (&x)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        x[i] = gload<NT>(reinterpret_cast<const T *>(base + off));
+        base += step;
+        asm("" : "+s"(base));
+    }
+}
+template <bool NT, typename T, int N>
+__device__ __forceinline__ void global_write(char *base, unsigned step, unsigned off, const T (&x)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        gstore<NT>(reinterpret_cast<T *>(base + off), x[i]);
+        base += step;
+        asm("" : "+s"(base));
+    }
+}
+
+// Arguments of a call's shape, one word each so that the kernel finds them in scalar registers when it starts (the build has the
+// first 14 words of the arguments preloaded; a struct is not): the three sizes in one word, the elements per workgroup, and
+// reciprocals of the pencil counts of the passes and of two sizes.  (At most 2^31 - 1 elements.)
+#define TPO_ANISO_SHAPE unsigned num_elems, unsigned groups, unsigned sizes, unsigned g, \
+                        unsigned by_yz, unsigned by_xz, unsigned by_xy, unsigned by_y, unsigned by_z
+constexpr unsigned packed_sizes(int nx, int ny, int nz) { return (unsigned)(nx | ny << 8 | nz << 16); }
+template <bool XCD>
+__device__ __forceinline__ unsigned aniso_batch(unsigned groups)        // pencil_batch in 32 bits
+{
+    return XCD ? (blockIdx.x & 7) * ((groups + 7) / 8) + (blockIdx.x >> 3) : blockIdx.x;
+}
+
+constexpr unsigned lane_reciprocal(int d) { return (65536u + d - 1) / d; }
+// t / d for t, d <= 256 (t < 256), m = lane_reciprocal(d): m d exceeds 65536 by r < d, so t m / 65536 exceeds t / d by less than
+// 1 / d while t r < 65536.
+constexpr bool lane_reciprocals_exact()
+{
+    for (unsigned d = 1; d <= 256; ++d)
+        for (unsigned t = 0; t < 256; ++t)
+            if (t * lane_reciprocal((int)d) >> 16 != t / d) return false;
+    return true;
+}
+static_assert(lane_reciprocals_exact());
+__device__ __forceinline__ unsigned lane_quotient(unsigned t, unsigned m) { return mul24(t, m) >> 16; }
+
 // HINT bits as in the pencil kernels: 1 non-temporal loads of u_e, 2 non-temporal stores of v_e,
 // 4 non-temporal loads of D_e.  XCD: workgroups renumbered per accelerator die (the grid must be
 // pencil_grid<XCD>(number of groups)).
 template <typename T, int MAXN, int HINT, bool XCD>
 __global__ void __launch_bounds__(ANISO_MAX_NT)
-ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T *__restrict__ D,
-                   T *v, int nx, int ny, int nz, int g, long long num_elems, long long groups)
+ihelm_aniso_kernel(const T *u, const T *__restrict__ D, TPO_ANISO_SHAPE,
+                   const T *Sx_, const T *Sy_, const T *Sz_, T *v)
 {
     extern __shared__ __align__(16) unsigned char tpo_lds[];
     T *cube = reinterpret_cast<T *>(tpo_lds);
     const TPO_CONSTANT T *Sx = (const TPO_CONSTANT T *)Sx_;
     const TPO_CONSTANT T *Sy = (const TPO_CONSTANT T *)Sy_;
     const TPO_CONSTANT T *Sz = (const TPO_CONSTANT T *)Sz_;
+    const int nx = sizes & 255, ny = sizes >> 8 & 255, nz = sizes >> 16;
 
-    const int tid = threadIdx.x;
-    const long long batch = pencil_batch<XCD>(groups);
+    const unsigned tid = threadIdx.x;
+    const unsigned batch = aniso_batch<XCD>(groups);
     if (batch >= groups) return;                           // padding workgroup of the renumbering
-    const long long e0 = batch * g;
-    const long long left = num_elems - e0;
-    const int here = left < g ? (int)left : g;             // elements of this workgroup
-    const int pz = aniso_pz(nz), pyz = aniso_pyz(ny, nz);
-    const int cube_words = nx * pyz;
-    const int face = ny * nz;
-    const size_t total = (size_t)nx * face;
+    const unsigned e0 = batch * g, left = num_elems - e0;
+    const unsigned here = left < g ? left : g;             // elements of this workgroup
+    const unsigned pz = aniso_pz(nz), pyz = aniso_pyz(ny, nz);
+    const unsigned cube_words = nx * pyz, face = ny * nz, total = nx * face;
+    // addresses in HBM: one base per workgroup and index along the axis (uniform) plus a 32-bit byte offset per lane
+    constexpr unsigned W = sizeof(T);
+    const char *ub = reinterpret_cast<const char *>(u + (size_t)e0 * total);
+    const char *db = reinterpret_cast<const char *>(D + (size_t)e0 * total);
+    char *vb = reinterpret_cast<char *>(v + (size_t)e0 * total);
 
     // the lane's place in a pass with `pencils` pencils per element: element ge, pencil p
-    auto place = [&](int pencils, int &ge, int &p) {
-        ge = tid / pencils;
-        p = tid - ge * pencils;
+    auto place = [&](unsigned pencils, unsigned by, unsigned &ge, unsigned &p) {
+        ge = lane_quotient(tid, by);
+        p = tid - mul24(ge, pencils);
         return ge < here;
     };
 
-    int ge2, p2;
-    const bool act2 = place(nx * ny, ge2, p2);              // lane (a, b): a pencil along axis 2
-    const int a2 = p2 / ny, b2 = p2 - a2 * ny;
-    T *row2 = cube + ge2 * cube_words + a2 * pyz + b2 * pz;
-
+    unsigned ge2, p2;
+    const bool act2 = place(nx * ny, by_xy, ge2, p2);    // lane (a, b): a pencil along axis 2
     // D_e in the layout of the axis-2 pass, asked for before anything else
     T dreg[MAXN];
     if (act2)
         dispatch_size<MAXN>(nz, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
             T t[N];
-            load_words<(HINT & 4) != 0, T, N>(D + (size_t)(e0 + ge2) * total + (size_t)p2 * nz, t);
+            const unsigned off = mad24(ge2, total, mul24(p2, N)) * W;
+            load_words<(HINT & 4) != 0, T, N>(reinterpret_cast<const T *>(db + off), t);
 #pragma unroll
             for (int k = 0; k < N; ++k) dreg[k] = t[k];
         });
+    const unsigned a2 = lane_quotient(p2, by_y), b2 = p2 - mul24(a2, ny);
+    T *row2 = cube + mad24(ge2, cube_words, mad24(a2, pyz, mul24(b2, pz)));
 
-    int ge1, p1;
-    const bool act1 = place(nx * nz, ge1, p1);              // lane (a, c): a pencil along axis 1
-    const int a1 = p1 / nz, c1 = p1 - a1 * nz;
-    T *col1 = cube + ge1 * cube_words + a1 * pyz + c1;
+    unsigned ge1, p1;
+    const bool act1 = place(nx * nz, by_xz, ge1, p1);    // lane (a, c): a pencil along axis 1
+    const unsigned a1 = lane_quotient(p1, by_z), c1 = p1 - mul24(a1, nz);
+    const unsigned col1 = lds_address(cube) + mad24(ge1, cube_words, mad24(a1, pyz, c1)) * W, step1 = pz * W;
 
-    int ge0, p0;
-    const bool act0 = place(face, ge0, p0);                 // lane (b, c): a pencil along axis 0
-    const int b0 = p0 / nz, c0 = p0 - b0 * nz;
-    T *col0 = cube + ge0 * cube_words + b0 * pz + c0;
-    const size_t base0 = (size_t)(e0 + ge0) * total + p0;
+    unsigned ge0, p0;
+    const bool act0 = place(face, by_yz, ge0, p0);       // lane (b, c): a pencil along axis 0
+    const unsigned b0 = lane_quotient(p0, by_z);
+    const unsigned col0 = lds_address(cube) + mad24(ge0, cube_words, mad24(b0, pz - nz, p0)) * W, step0 = pyz * W;
+    const unsigned off0 = mad24(ge0, total, p0) * W, face_bytes = face * W;
 
     // forward, axis 0, from global memory
     if (act0)
         dispatch_size<MAXN>(nx, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
             T x[N], y[N];
-#pragma unroll
-            for (int l = 0; l < N; ++l) x[l] = gload<(HINT & 1) != 0>(u + base0 + (size_t)l * face);
+            global_read<(HINT & 1) != 0>(ub, face_bytes, off0, x);
             mode_product<T, N, true>(Sx, x, y);
-#pragma unroll
-            for (int i = 0; i < N; ++i) col0[i * pyz] = y[i];
+            lds_write(col0, step0, y);
         });
     __syncthreads();
     // forward, axis 1, in place
@@ -145,11 +261,9 @@ ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T
         dispatch_size<MAXN>(ny, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
             T x[N], y[N];
-#pragma unroll
-            for (int m = 0; m < N; ++m) x[m] = col1[m * pz];
+            lds_read(col1, step1, x);
             mode_product<T, N, true>(Sy, x, y);
-#pragma unroll
-            for (int m = 0; m < N; ++m) col1[m * pz] = y[m];
+            lds_write(col1, step1, y);
         });
     __syncthreads();
     // axis 2: forward, scale by D_e, backward, in place
@@ -172,11 +286,9 @@ ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T
         dispatch_size<MAXN>(ny, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
             T x[N], y[N];
-#pragma unroll
-            for (int m = 0; m < N; ++m) x[m] = col1[m * pz];
+            lds_read(col1, step1, x);
             mode_product<T, N, false>(Sy, x, y);
-#pragma unroll
-            for (int m = 0; m < N; ++m) col1[m * pz] = y[m];
+            lds_write(col1, step1, y);
         });
     __syncthreads();
     // backward, axis 0, to global memory
@@ -184,11 +296,9 @@ ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T
         dispatch_size<MAXN>(nx, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
             T x[N], y[N];
-#pragma unroll
-            for (int l = 0; l < N; ++l) x[l] = col0[l * pyz];
+            lds_read(col0, step0, x);
             mode_product<T, N, false>(Sx, x, y);
-#pragma unroll
-            for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(v + base0 + (size_t)i * face, y[i]);
+            global_write<(HINT & 2) != 0>(vb, face_bytes, off0, y);
         });
 }
 
@@ -197,57 +307,71 @@ ihelm_aniso_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T
 // above sizes the workgroup by the largest pass, and in the others most of the lanes idle.  What bounds it then is
 // the loads: u_e and D_e are asked for by few lanes, so few bytes are on their way (fp64 (3,9,16) 34 KB per CU against
 // 216 KB here).  us per call on 800 MB, kernel above / this one: fp64 (3,9,16) 329 / 155, (16,9,3) 279 / 157, (13,3,12)
-// 267 / 157, (10,7,13) 192 / 161; fp32 (3,9,15) 438 / 184, (14,4,3) 279 / 190, (8,15,6) 225 / 189.
+// 267 / 157, (10,7,13) 192 / 161; fp32 (3,9,15) 438 / 184, (14,4,3) 279 / 190, (8,15,6) 225 / 189 (both since 5 .. 10 % faster).
 // With one turn per pass it is the slower one by 3 .. 15 % (quotients, loops).
-struct AnisoTurns {
-    int nx, ny, nz, g;
-    unsigned div_yz, div_xz, div_xy, div_y, div_z;      // for quotient()
-};
-// t / d for t < 2^24 and d <= 256, with m = ceil(2^32 / d) (d = 1: does not fit, m = 0): m * d exceeds 2^32 by less
-// than d, so the quotient is exact while t * d < 2^32
-__device__ __forceinline__ int quotient(int t, unsigned m) { return m == 0 ? t : (int)__umulhi((unsigned)t, m); }
+// t / d for t <= 2^15 and d <= 256, with m = turn_reciprocal(d): m d exceeds 2^23 by r < d, so t m / 2^23 exceeds t / d by less
+// than 1 / d while t r < 2^23.  (A workgroup's elements have at most 48 KB: t <= 12288.)
+constexpr unsigned turn_reciprocal(int d) { return ((1u << 23) + d - 1) / d; }
+constexpr bool turn_reciprocals_exact()       // the excess grows with t: the last two whole multiples of d and the word before
+{
+    for (unsigned long long d = 1; d <= 256; ++d)
+        for (unsigned long long q = 12288 / d, t = q * d - 1; t <= q * d; ++t)
+            if (((t << 9) * turn_reciprocal((int)d)) >> 32 != t / d || (t << 9) >> 24 != 0 || turn_reciprocal((int)d) >> 24 != 0) return false;
+    return true;
+}
+static_assert(turn_reciprocals_exact());
+__device__ __forceinline__ unsigned quotient(unsigned t, unsigned m) { return mulhi24(t << 9, m); }
 
 template <typename T, int MAXN, int HINT, bool XCD>
 __global__ void __launch_bounds__(ANISO_MAX_NT)
-ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, const T *__restrict__ D,
-                   T *v, AnisoTurns sh, long long num_elems, long long groups)
+ihelm_aniso_turns_kernel(const T *u, const T *__restrict__ D, TPO_ANISO_SHAPE,
+                         const T *Sx_, const T *Sy_, const T *Sz_, T *v)
 {
     extern __shared__ __align__(16) unsigned char tpo_lds[];
     T *cube = reinterpret_cast<T *>(tpo_lds);
     const TPO_CONSTANT T *Sx = (const TPO_CONSTANT T *)Sx_;
     const TPO_CONSTANT T *Sy = (const TPO_CONSTANT T *)Sy_;
     const TPO_CONSTANT T *Sz = (const TPO_CONSTANT T *)Sz_;
-    const int nx = sh.nx, ny = sh.ny, nz = sh.nz;
+    const int nx = sizes & 255, ny = sizes >> 8 & 255, nz = sizes >> 16;
 
-    const int tid = threadIdx.x;
-    const int NT = blockDim.x;
-    const long long batch = pencil_batch<XCD>(groups);
+    const unsigned tid = threadIdx.x;
+    const unsigned NT = blockDim.x;
+    const unsigned batch = aniso_batch<XCD>(groups);
     if (batch >= groups) return;                           // padding workgroup of the renumbering
-    const long long e0 = batch * sh.g;
-    const long long left = num_elems - e0;
-    const int here = left < sh.g ? (int)left : sh.g;       // elements of this workgroup
-    const int pz = aniso_pz(nz), pyz = aniso_pyz(ny, nz);
-    const int cube_words = nx * pyz;
-    const int face = ny * nz, side = nx * nz, base = nx * ny;
-    const size_t total = (size_t)nx * face;
-    const T *ub = u + (size_t)e0 * total, *db = D + (size_t)e0 * total;
-    T *vb = v + (size_t)e0 * total;
+    const unsigned e0 = batch * g, left = num_elems - e0;
+    const unsigned here = left < g ? left : g;             // elements of this workgroup
+    const unsigned pz = aniso_pz(nz), pyz = aniso_pyz(ny, nz);
+    const unsigned cube_words = nx * pyz;
+    const unsigned face = ny * nz, side = nx * nz, base = nx * ny, total = nx * face;
+    constexpr unsigned W = sizeof(T);
+    const char *ub = reinterpret_cast<const char *>(u + (size_t)e0 * total);
+    const char *db = reinterpret_cast<const char *>(D + (size_t)e0 * total);
+    char *vb = reinterpret_cast<char *>(v + (size_t)e0 * total);
+    const unsigned lds = lds_address(cube), step0 = pyz * W, step1 = pz * W, face_bytes = face * W;
 
     // Pencil t of a pass with `limit` of them goes to lane t % NT in turn t / NT; the wavefront takes part in a
     // turn if its first lane has a pencil, lanes past the end shadow the last one and do not store.
-    const int first = __builtin_amdgcn_readfirstlane(tid & ~63);
+    const unsigned first = __builtin_amdgcn_readfirstlane(tid & ~63u);
+    // LDS address of pencil (b, c) along axis 0 and of pencil (a, c) along axis 1
+    auto column0 = [&](unsigned q, unsigned p) {
+        return lds + mad24(q, cube_words, mad24(quotient(p, by_z), pz - nz, p)) * W;
+    };
+    auto column1 = [&](unsigned q, unsigned p) {            // p = a nz + c: a pyz + c
+        return lds + mad24(q, cube_words, mad24(quotient(p, by_z), pyz - nz, p)) * W;
+    };
 
     // D_e in the layout of the axis-2 pass (pencils (a, b), nz consecutive words), asked for before anything else
     T dreg[MAXN];
     dispatch_size<MAXN>(nz, [&](auto nc) {
         constexpr int N = decltype(nc)::value, K = MAXN / N;
-        const int limit = here * base;
+        const unsigned limit = here * base;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (first + k * NT < limit) {
-                const int t = min(tid + k * NT, limit - 1);
+            const unsigned turn = scalar(k * NT);
+            if (first + turn < limit) {
+                const unsigned t = min(tid + turn, limit - 1);
                 T w[N];
-                load_words<(HINT & 4) != 0, T, N>(db + (unsigned)(t * N), w);
+                load_words<(HINT & 4) != 0, T, N>(reinterpret_cast<const T *>(db + mul24(t, N * W)), w);
 #pragma unroll
                 for (int i = 0; i < N; ++i) dreg[k * N + i] = w[i];
             }
@@ -257,28 +381,25 @@ ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, c
     // forward, axis 0, from global memory: pencils (b, c)
     dispatch_size<MAXN>(nx, [&](auto nc) {
         constexpr int N = decltype(nc)::value, K = MAXN / N;
-        const int limit = here * face;
+        const unsigned limit = here * face;
         T x[K][N];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (first + k * NT < limit) {
-                const int t = min(tid + k * NT, limit - 1);
-                const T *p = ub + (unsigned)(t + quotient(t, sh.div_yz) * ((int)total - face));
-#pragma unroll
-                for (int l = 0; l < N; ++l) x[k][l] = gload<(HINT & 1) != 0>(p + l * face);
+            const unsigned turn = scalar(k * NT);
+            if (first + turn < limit) {
+                const unsigned t = min(tid + turn, limit - 1);
+                const unsigned off = mad24(quotient(t, by_yz), total - face, t) * W;
+                global_read<(HINT & 1) != 0>(ub, face_bytes, off, x[k]);
             }
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int t = tid + k * NT;
+            const unsigned t = tid + scalar(k * NT);
             if (t < limit) {
-                const int q = quotient(t, sh.div_yz), p = t - q * face;
-                const int b = quotient(p, sh.div_z);
-                T *col = cube + q * cube_words + p + b * (pz - nz);
+                const unsigned q = quotient(t, by_yz);
                 T y[N];
                 mode_product<T, N, true>(Sx, x[k], y);
-#pragma unroll
-                for (int i = 0; i < N; ++i) col[i * pyz] = y[i];
+                lds_write(column0(q, t - mul24(q, face)), step0, y);
             }
         }
     });
@@ -287,16 +408,12 @@ ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, c
     auto axis1 = [&](auto fwd) {
         dispatch_size<MAXN>(ny, [&](auto nc) {
             constexpr int N = decltype(nc)::value;
-            for (int t = tid; t < here * side; t += NT) {
-                const int q = quotient(t, sh.div_xz), p = t - q * side;
-                const int a = quotient(p, sh.div_z), c = p - a * nz;
-                T *col = cube + q * cube_words + a * pyz + c;
+            for (unsigned t = tid; t < here * side; t += NT) {
+                const unsigned q = quotient(t, by_xz), at = column1(q, t - mul24(q, side));
                 T x[N], y[N];
-#pragma unroll
-                for (int m = 0; m < N; ++m) x[m] = col[m * pz];
+                lds_read(at, step1, x);
                 mode_product<T, N, decltype(fwd)::value>(Sy, x, y);
-#pragma unroll
-                for (int m = 0; m < N; ++m) col[m * pz] = y[m];
+                lds_write(at, step1, y);
             }
         });
     };
@@ -307,11 +424,11 @@ ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, c
         constexpr int N = decltype(nc)::value, K = MAXN / N;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int t = tid + k * NT;
+            const unsigned t = tid + scalar(k * NT);
             if (t < here * base) {
-                const int q = quotient(t, sh.div_xy), p = t - q * base;
-                const int a = quotient(p, sh.div_y), b = p - a * ny;
-                T *row = cube + q * cube_words + a * pyz + b * pz;
+                const unsigned q = quotient(t, by_xy), p = t - mul24(q, base);
+                const unsigned a = quotient(p, by_y), b = p - mul24(a, ny);
+                T *row = cube + mad24(q, cube_words, mad24(a, pyz, mul24(b, pz)));
                 T x[N], y[N];
 #pragma unroll
                 for (int i = 0; i < N; ++i) x[i] = row[i];
@@ -330,17 +447,13 @@ ihelm_aniso_turns_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, c
     // backward, axis 0, to global memory
     dispatch_size<MAXN>(nx, [&](auto nc) {
         constexpr int N = decltype(nc)::value;
-        for (int t = tid; t < here * face; t += NT) {
-            const int q = quotient(t, sh.div_yz), p = t - q * face;
-            const int b = quotient(p, sh.div_z), c = p - b * nz;
-            const T *col = cube + q * cube_words + b * pz + c;
+        for (unsigned t = tid; t < here * face; t += NT) {
+            const unsigned q = quotient(t, by_yz);
             T x[N], y[N];
-#pragma unroll
-            for (int l = 0; l < N; ++l) x[l] = col[l * pyz];
+            lds_read(column0(q, t - mul24(q, face)), step0, x);
             mode_product<T, N, false>(Sx, x, y);
-            T *o = vb + (unsigned)(q * (int)total + p);
-#pragma unroll
-            for (int i = 0; i < N; ++i) gstore<(HINT & 2) != 0>(o + i * face, y[i]);
+            const unsigned off = mad24(q, total - face, t) * W;
+            global_write<(HINT & 2) != 0>(vb, face_bytes, off, y);
         }
     });
 }
@@ -437,15 +550,13 @@ template <typename T, int MAXN, bool STREAM>
 hipError_t launch_turns_as(const AnisoArgs &a, int g, int nt)
 {
     const long long groups = (a.num_elems + g - 1) / g;
-    auto inverse = [](int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); };
-    const AnisoTurns sh{a.nx, a.ny, a.nz, g, inverse(a.ny * a.nz), inverse(a.nx * a.nz), inverse(a.nx * a.ny),
-                        inverse(a.ny), inverse(a.nz)};
     drop_stale_error();
     hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
                        dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt),
                        (size_t)g * a.nx * aniso_pyz(a.ny, a.nz) * sizeof(T), a.stream,
-                       (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
-                       (const T *)a.d, (T *)a.v, sh, a.num_elems, groups);
+                       (const T *)a.u, (const T *)a.d, (unsigned)a.num_elems, (unsigned)groups, packed_sizes(a.nx, a.ny, a.nz),
+                       (unsigned)g, turn_reciprocal(a.ny * a.nz), turn_reciprocal(a.nx * a.nz), turn_reciprocal(a.nx * a.ny),
+                       turn_reciprocal(a.ny), turn_reciprocal(a.nz), (const T *)a.sx, (const T *)a.sy, (const T *)a.sz, (T *)a.v);
     return hipGetLastError();
 }
 
@@ -464,8 +575,9 @@ hipError_t launch_bound_as(const AnisoArgs &a, int g, int nt, size_t lds)
     drop_stale_error();
     hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
                        dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt), lds, a.stream,
-                       (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
-                       (const T *)a.d, (T *)a.v, a.nx, a.ny, a.nz, g, a.num_elems, groups);
+                       (const T *)a.u, (const T *)a.d, (unsigned)a.num_elems, (unsigned)groups, packed_sizes(a.nx, a.ny, a.nz),
+                       (unsigned)g, lane_reciprocal(a.ny * a.nz), lane_reciprocal(a.nx * a.nz), lane_reciprocal(a.nx * a.ny),
+                       lane_reciprocal(a.ny), lane_reciprocal(a.nz), (const T *)a.sx, (const T *)a.sy, (const T *)a.sz, (T *)a.v);
     return hipGetLastError();
 }
 
