@@ -1,5 +1,5 @@
 // Launch settings by the size of the batch.  Each kernel family has a setting for large batches (its tuning
-// table) and, per type and n, up to five rows before it: a batch whose fields take at most `mib` MiB takes the
+// table) and, per type and n, up to six rows before it: a batch whose fields take at most `mib` MiB takes the
 // first row that it fits.
 //
 // Why the size decides: up to a dozen MiB a launch is one round of workgroups and the fewest elements per workgroup
@@ -31,9 +31,13 @@
 
 namespace tpo {
 
-// sb: words per batch of scalar loads (matrix_product); mm: 4x4x1 matrix-core form (halves in fp32).
+// Added to the words per batch of scalar loads: the matrices are touched once before the first product (warm_scalar_cache); on
+// rows that end where a launch passes one workgroup per CU.
+constexpr int kWarm = 256;
+
+// sb: words per batch of scalar loads (matrix_product), with or without kWarm; mm: 4x4x1 matrix-core form (halves in fp32).
 struct BatchRow { int mib = 0, g = 0, hint = 0, xcd = 0, sb = 0, mm = 0; };
-constexpr int kBatchRows = 5;                   // a row with mib = 0 ends the list
+constexpr int kBatchRows = 6;                   // a row with mib = 0 ends the list
 struct BatchRows { BatchRow row[TPO_MAX_N + 1][kBatchRows]; };
 
 // Operator, vector-FMA kernels.
@@ -48,13 +52,13 @@ template <> struct PencilRows<double> {
         /* 6 */ {{14, 3, 0, 0, 32}, {50, 3, 2, 0, 32}},
         /* 7 */ {{14, 1, 0, 0, 32}},
         /* 8 */ {{39, 1, 3, 0, 32}, {100, 1, 2, 0, 0}, {288, 1, 0, 0, 0}},
-        /* 9 */ {{14, 1, 0, 0, 32}, {39, 3, 3, 0, 32}, {66, 3, 2, 0, 40}, {145, 3, 0, 0, 40}},
-        /* 10 */ {{85, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
-        /* 11 */ {{14, 1, 0, 0, 32}, {39, 1, 3, 0, 32}, {165, 2, 2, 0, 40}, {430, 2, 1, 0, 32}, {1650, 2, 3, 0, 32}},
+        /* 9 */ {{4, 1, 0, 0, 32 + kWarm}, {14, 1, 0, 0, 32}, {39, 3, 3, 0, 32}, {66, 3, 2, 0, 40}, {145, 3, 0, 0, 40}},
+        /* 10 */ {{5, 1, 3, 0, 32 + kWarm}, {85, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
+        /* 11 */ {{7, 1, 0, 0, 32 + kWarm}, {14, 1, 0, 0, 32}, {39, 1, 3, 0, 32}, {165, 2, 2, 0, 40}, {430, 2, 1, 0, 32}, {1650, 2, 3, 0, 32}},
         /* 12 */ {{53, 1, 3, 0, 32}, {68, 3, 3, 0, 32}, {350, 1, 3, 0, 40}},
-        /* 13 */ {{14, 1, 0, 0, 32}, {53, 1, 3, 1, 32}, {535, 1, 2, 0, 40}, {1650, 3, 1, 0, 40}},
-        /* 14 */ {{53, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
-        /* 15 */ {{20, 1, 0, 0, 32}, {53, 1, 3, 1, 32}, {350, 1, 2, 0, 40}, {535, 1, 3, 0, 32}},
+        /* 13 */ {{12, 1, 0, 0, 32 + kWarm}, {14, 1, 0, 0, 32}, {53, 1, 3, 1, 32}, {535, 1, 2, 0, 40}, {1650, 3, 1, 0, 40}},
+        /* 14 */ {{16, 1, 3, 0, 32 + kWarm}, {53, 1, 3, 0, 32}, {535, 1, 3, 0, 40}},
+        /* 15 */ {{20, 1, 0, 0, 32 + kWarm}, {53, 1, 3, 1, 32}, {350, 1, 2, 0, 40}, {535, 1, 3, 0, 32}},
         /* 16 */ {{53, 1, 3, 0, 32}, {142, 2, 2, 0, 40}, {535, 1, 3, 1, 40}},
     }};
 };
@@ -81,8 +85,8 @@ template <> struct PencilSepRows<double> {
         /* 6 */ {{37, 3, 2, 0, 32}, {50, 3, 0, 0, 32}, {535, 3, 2, 0, 32}},
         /* 7 */ {{9, 1, 1, 0, 32}},
         {},
-        /* 9 */ {{5, 2, 0, 0, 32}, {37, 3, 2, 0, 32}, {50, 3, 0, 0, 32}, {184, 2, 3, 0, 32}, {350, 3, 3, 0, 32}},
-        {},
+        /* 9 */ {{5, 2, 0, 0, 32 + kWarm}, {37, 3, 2, 0, 32}, {50, 3, 0, 0, 32}, {184, 2, 3, 0, 32}, {350, 3, 3, 0, 32}},
+        /* 10 */ {{3, 1, 3, 0, 32 + kWarm}},
         /* 11 */ {{9, 1, 1, 0, 32}, {50, 1, 2, 0, 32}, {85, 1, 0, 0, 32}, {535, 2, 3, 0, 32}},
         /* 12 */ {{31, 1, 3, 0, 32}},
         /* 13 */ {{9, 1, 0, 0, 32}, {245, 1, 3, 0, 32}, {535, 3, 3, 0, 32}},
@@ -145,11 +149,11 @@ template <> struct TransformRows<double> {
         /* 9 */ {{50, 2, 0, 0, 32}, {1024, 1, 0, 0, 40}},
         /* 10 */ {{5, 1, 2, 0, 32}, {184, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
         /* 11 */ {{14, 1, 0, 1, 32}, {37, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
-        /* 12 */ {{1650, 1, 2, 0, 40}},
-        /* 13 */ {{9, 1, 0, 0, 40}, {53, 1, 2, 0, 40}, {184, 3, 0, 0, 40}, {1650, 2, 0, 0, 40}},
-        /* 14 */ {{57, 1, 2, 0, 40}, {343, 1, 0, 0, 40}, {535, 1, 2, 0, 40}},
-        /* 15 */ {{57, 1, 2, 0, 40}, {350, 1, 0, 0, 40}},
-        /* 16 */ {{53, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
+        /* 12 */ {{6, 1, 2, 0, 40 + kWarm}, {1650, 1, 2, 0, 40}},
+        /* 13 */ {{9, 1, 0, 0, 40 + kWarm}, {53, 1, 2, 0, 40}, {184, 3, 0, 0, 40}, {1650, 2, 0, 0, 40}},
+        /* 14 */ {{10, 1, 2, 0, 40 + kWarm}, {57, 1, 2, 0, 40}, {343, 1, 0, 0, 40}, {535, 1, 2, 0, 40}},
+        /* 15 */ {{13, 1, 2, 0, 40 + kWarm}, {57, 1, 2, 0, 40}, {350, 1, 0, 0, 40}},
+        /* 16 */ {{16, 1, 2, 1, 32 + kWarm}, {53, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
     }};
 };
 template <> struct TransformRows<float> {
@@ -186,13 +190,13 @@ template <> struct SquareConvectionRows<double> {
         /* 7 */ {{28, 1, 0, 0, 0, 32}, {123, 1, 2, 1, 0, 32}},
         /* 8 */ {{43, 1, 2, 0, 0, 32}, {123, 1, 2, 1, 0, 0}},
         /* 9 */ {{28, 1, 0, 0, 0, 32}, {66, 3, 2, 0, 0, 0}, {253, 2, 2, 1, 0, 32}},
-        /* 10 */ {{43, 1, 2, 0, 0, 32}, {1010, 1, 2, 1, 0, 40}},
-        /* 11 */ {{10, 1, 0, 1, 1, 32}, {22, 2, 0, 1, 1, 32}, {1010, 1, 2, 1, 0, 40}},
-        /* 12 */ {{43, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}, {1010, 1, 2, 1, 1, 32}},
-        /* 13 */ {{28, 1, 2, 0, 0, 32}, {173, 1, 2, 1, 0, 40}},
-        /* 14 */ {{28, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}},
-        /* 15 */ {{28, 1, 2, 0, 0, 32}, {123, 1, 2, 1, 0, 40}, {256, 1, 2, 1, 1, 32}},
-        /* 16 */ {{28, 1, 2, 0, 0, 32}},
+        /* 10 */ {{8, 1, 2, 0, 0, 32 + kWarm}, {43, 1, 2, 0, 0, 32}, {1010, 1, 2, 1, 0, 40}},
+        /* 11 */ {{10, 1, 0, 1, 1, 32 + kWarm}, {22, 2, 0, 1, 1, 32}, {1010, 1, 2, 1, 0, 40}},
+        /* 12 */ {{14, 1, 2, 0, 0, 32 + kWarm}, {43, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}, {1010, 1, 2, 1, 1, 32}},
+        /* 13 */ {{18, 1, 2, 0, 0, 32 + kWarm}, {28, 1, 2, 0, 0, 32}, {173, 1, 2, 1, 0, 40}},
+        /* 14 */ {{23, 1, 2, 0, 0, 32 + kWarm}, {28, 1, 2, 0, 0, 32}, {253, 1, 2, 1, 0, 40}},
+        /* 15 */ {{28, 1, 2, 0, 0, 32 + kWarm}, {123, 1, 2, 1, 0, 40}, {256, 1, 2, 1, 1, 32}},
+        /* 16 */ {{28, 1, 2, 0, 0, 32 + kWarm}},
     }};
 };
 template <> struct SquareConvectionRows<float> {
@@ -229,7 +233,7 @@ template <> struct ConvRectFirstTable<double> {
         {6, 7, 0, 1, 0, 32},    {6, 8, 2400, 1, 1, 32}, {6, 9, 0, 1, 0, 32},    {7, 8, 78, 1, 0, 32},
         {7, 8, 104, 1, 0, 0},   {7, 8, 400, 1, 0, 32},  {7, 9, 2400, 1, 0, 32}, {8, 9, 0, 1, 0, 32},
         {8, 10, 70, 1, 1, 32},  {8, 10, 122, 2, 2, 32}, {9, 10, 66, 1, 1, 32},  {9, 10, 122, 2, 0, 32},
-        {8, 12, 600, 1, 0, 32}, {9, 14, 13, 1, 0, 32},
+        {8, 12, 12, 1, 0, 32 + kWarm}, {8, 12, 600, 1, 0, 32}, {9, 14, 13, 1, 0, 32 + kWarm},
     };
 };
 template <> struct ConvRectFirstTable<float> {

@@ -157,6 +157,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 #pragma unroll
                 for (int l = 0; l < N; ++l) w[l] *= mq[l];
                 if (dir < 2) {
+                    if (dir == 0) warm_scalar_cache<SB, N * N>(Dm, Im);
                     mode_product<T, N, false, SB>(dir == 0 ? Dm : Im, w, y);
                     T *dst = dir == 0 ? c0 : c1;
 #pragma unroll
@@ -174,6 +175,7 @@ convection_pencil_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, con
 #pragma unroll
                     for (int l = 0; l < N; ++l) x2[l] = x[l];
                 } else {
+                    if (dir == 0) warm_scalar_cache<SB, N * N>(Dm, Im);
                     mode_product<T, N, false, SB>(dir == 0 ? Dm : Im, x, y);
                     T *dst = dir == 0 ? c0 : (dir == 1 ? c1 : c2);
 #pragma unroll
@@ -432,6 +434,7 @@ convection_rect_kernel(const T *__restrict__ Pq, const T *__restrict__ Mq, const
 #pragma unroll
                 for (int l = 0; l < NQ; ++l) x2[l] = xq[l];
             } else {
+                if (dir == 0) warm_scalar_cache<SB, NV * NQ>(Dm, Im);
                 matrix_product<T, NV, NQ, false, SB>(dir == 0 ? Dm : Im, xq, yv);
                 T *dst = dir == 0 ? c0 : c1;
 #pragma unroll

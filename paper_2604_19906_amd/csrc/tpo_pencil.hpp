@@ -125,8 +125,8 @@ __device__ __forceinline__ void matrix_product(const TPO_CONSTANT T *S, const T 
     // SGPR file.
     asm volatile("" : "+s"(S));
     constexpr int NE = R * C;                                   // entries
-    constexpr int B = SB * 4 / (int)sizeof(T);                  // entries per batch
-    if constexpr (SB == 0 || NE <= 2 * B) {
+    constexpr int B = (SB & ~kWarm) * 4 / (int)sizeof(T);       // entries per batch
+    if constexpr (B == 0 || NE <= 2 * B) {
         if constexpr (FWD) {
 #pragma unroll
             for (int c = 0; c < C; ++c) y[c] = S[c] * x[0];
@@ -169,6 +169,33 @@ __device__ __forceinline__ void matrix_product(const TPO_CONSTANT T *S, const T 
             for (int k = 1; k < B; ++k) term(b, k);
             __builtin_amdgcn_sched_barrier(0);
         }, std::make_integer_sequence<int, (NE + B - 1) / B>{});
+    }
+}
+
+// Settings with kWarm in SB (launches of at most one workgroup per CU): every 64-byte line of the matrices is touched by scalar
+// loads that all go out before one wait, right after the wavefront has asked for its first words of the fields.  There the matrices
+// are in no scalar cache yet, and every batch of a product misses, one wait after the other; on larger launches the workgroups
+// before have brought them in, and the touching only costs (1.01 .. 1.05).  Time with / without, fp64, up to the rows' ends: halves n = 12 0.93 .. 0.99, 13
+// 0.90 .. 0.93, 14 and 15 0.92 .. 0.95, 16 0.73 .. 0.83; convection n = 10 .. 14 0.90 .. 0.93, 15 0.85 .. 0.89, 16 0.88 .. 0.90, (8,12) and (9,14) 0.91 ..
+// 0.96; operator n = 9 0.90 (three matrices; one 0.97), 10 0.87 (0.97), with one matrix 11, 13, 14, 15 0.95 .. 0.97 (with three they run in the tiles);
+// separable n = 9, 10 0.90 .. 0.93.  Smaller matrices gain nothing (0.98 .. 1.05).
+template <int SB, int WORDS, typename T, typename... M>
+__device__ __forceinline__ void warm_scalar_cache(const TPO_CONSTANT T *first, M... more)
+{
+    if constexpr ((SB & kWarm) != 0) {
+        unsigned seen = 0;
+        auto touch = [&](const TPO_CONSTANT T *S) {
+            const TPO_CONSTANT unsigned *w = (const TPO_CONSTANT unsigned *)S;
+            constexpr int DW = WORDS * (int)sizeof(T) / 4;
+            seen |= w[DW - 1];
+#pragma unroll
+            for (int k = 0; k < DW; k += 16) seen |= w[k];
+        };
+        __builtin_amdgcn_sched_barrier(0);
+        touch(first);
+        ((more != first ? touch(more) : void()), ...);
+        asm volatile("" :: "s"(seen));
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -322,6 +349,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
 #pragma unroll
             for (int l = 0; l < N; ++l) dd[l] = gload<(HINT & 1) != 0>(D + base + (size_t)(l * P + p));
         }
+        warm_scalar_cache<SB, N * N>(Sx, Sy, Sz);
         mode_product<T, N, true, SB>(Sx, x, y);
 #pragma unroll
         for (int i = 0; i < N; ++i) cube[i * PA + hi * PB + lo] = y[i];

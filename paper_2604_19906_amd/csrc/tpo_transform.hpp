@@ -47,6 +47,7 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     // axis 2: lane (a,b) = (hi,lo) owns u[a][b][0..n-1], contiguous in memory
     if (on) {
         load_words<(HINT & 1) != 0>(u + base + (size_t)(p * N), x);
+        warm_scalar_cache<SB, N * N>(Sz, Sy, Sx);
         mode_product<T, N, FWD, SB>(Sz, x, y);
 #pragma unroll
         for (int k = 0; k < N; ++k) cube[hi * PA + lo * PB + k] = y[k];
