@@ -271,8 +271,8 @@ __device__ __forceinline__ void store_words(T *p, const T (&in)[K])
 
 // HINT bit 0: non-temporal coalesced loads (u, and D_e when it is loaded coalesced); bit 1:
 // non-temporal stores of v; bit 2: non-temporal loads of D_e's per-lane runs (DDIRECT).
-// DDIRECT = false: D_e is loaded coalesced with u_e and parked in LDS until the scale.
-// DDIRECT = true : every lane loads, at kernel start, the n consecutive words of D_e that
+// DDIRECT = 0    : D_e is loaded coalesced with u_e and parked in LDS until the scale.
+// DDIRECT = 1    : every lane loads, at kernel start, the n consecutive words of D_e that
 //                  belong to its axis-2 pencil (no LDS for D_e: half the LDS per workgroup).
 // XCD = true : workgroups are renumbered so that each of the 8 accelerator dies (workgroups
 //              are dealt to them round-robin) works on one contiguous eighth of the elements;
@@ -299,7 +299,9 @@ __device__ __forceinline__ long long pencil_batch(long long nbatch)
 //            (sum left to right; SEP = 1: IEEE division, SEP = 2: recip_<false>); D is ignored
 //            and may be null.
 // SB: see matrix_product.
-template <typename T, int N, int G, int HINT, bool DDIRECT = false, bool XCD = false,
+// DDIRECT = 2    : the same words, asked for after the forward products along axes 0 and 1: half the
+//                  words on their way at a time, for launches that LDS_MIN holds at few workgroups.
+template <typename T, int N, int G, int HINT, int DDIRECT = 0, bool XCD = false,
           int SEP = 0, int SB = kScalarBatch>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
 ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
@@ -343,9 +345,9 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
         if constexpr (SEP != 0) {
             sep_ab = lam_x[hi] + lam_y[lo];
             sep_mu = mu[e];
-        } else if constexpr (DDIRECT) {
+        } else if constexpr (DDIRECT == 1) {
             load_words<(HINT & 4) != 0>(D + base + (size_t)(p * N), dd);   // D_e[a][b][0..n-1]
-        } else {
+        } else if constexpr (DDIRECT == 0) {
 #pragma unroll
             for (int l = 0; l < N; ++l) dd[l] = gload<(HINT & 1) != 0>(D + base + (size_t)(l * P + p));
         }
@@ -365,6 +367,11 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
 #pragma unroll
         for (int m = 0; m < N; ++m) x[m] = cube[hi * PA + m * PB + lo];
         mode_product<T, N, true, SB>(Sy, x, y);
+        if constexpr (DDIRECT == 2 && SEP == 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_words<(HINT & 4) != 0>(D + base + (size_t)(p * N), dd);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int j = 0; j < N; ++j) cube[hi * PA + j * PB + lo] = y[j];
     }
@@ -444,20 +451,26 @@ struct PencilTune {
     static constexpr size_t LDS_MIN = 0;    // LDS requested at least (caps workgroups per CU)
     static constexpr int SB = kScalarBatch; // words per batch of scalar loads (matrix_product)
 };
-// n = 11: two elements per workgroup (242 of 256 lanes), non-temporal loads of u_e, and an LDS
-// request of 28 KB (20.8 KB are used), which holds the CU at 5 workgroups = 10 elements instead
-// of 7: with fewer loads in flight the memory system runs faster.  Chosen on the named workload
+// n = 11: two elements per workgroup (242 of 256 lanes), non-temporal loads of u_e, D_e asked for late
+// (DDIRECT 2), and an LDS request of 36 KB (20.8 KB are used), which holds the CU at 4 workgroups = 8
+// elements instead of 14.  Bound by memory in one-shot bursts: a kernel of the same loads and stores alone
+// runs at 6.28 TB/s with 85 KB asked for per CU and at 5.7 TB/s with 213 KB.  Against D_e at once with 28 KB
+// (5 workgroups) 0.98 of the time at 2.4 GB, 0.977 .. 0.986 at 3, 5.5 and 8.3 GB, one matrix and three; the named
+// workload 1440 -> 1429 us
+// (32 and 40 KB the same within 1 %; late D_e at 24 and 28 KB 0.99 .. 1.00; D_e at once with 32 .. 40 KB
+// 1.02 .. 1.05; D_e after the product along axis 0 instead, 32 .. 40 KB, 1.01 .. 1.03).  Requests of
+// 32 / 32 / 40 KB at n = 9, 15, 16 give 0.97 .. 1.03: not taken.  The first choice was made on the named workload
 // (E = 262144, full-mantissa values; the settings rank differently on low-entropy data, where
-// the clock runs higher), alternating libraries on one box, ms per launch: this setting 1.421-
+// the clock runs higher), alternating libraries on one box, ms per launch: D_e at once with 28 KB 1.421-
 // 1.424; the same with cached u_e loads 1.450-1.452; 26 KB / 30 KB requests 1.465 / 1.421-1.430;
 // one element per workgroup with 18 KB (the earlier choice) 1.441-1.462, with 14 KB 1.469;
 // three / four elements per workgroup 1.518 / 1.472.  Scalars in batches: 1.444 against 1.435 here (the rows by batch
 // size, which serve everything up to 1650 MiB, take them; the other n keep them, 0.99 of the time before them at 4 and 8 GB,
 // geometric mean, no call above 1.045).
 template <> struct PencilTune<double, 11> {
-    static constexpr int G = 2, HINT = 1;
-    static constexpr bool DDIRECT = true, XCD = true;
-    static constexpr size_t LDS_MIN = 28 * 1024;
+    static constexpr int G = 2, HINT = 1, DDIRECT = 2;
+    static constexpr bool XCD = true;
+    static constexpr size_t LDS_MIN = 36 * 1024;
     static constexpr int SB = 0;
 };
 
@@ -510,7 +523,7 @@ template <typename T, int N, typename Tune, int SEP>
 struct PencilLauncherT {
     static constexpr int G = Tune::G;
     using Sh = PencilShape<T, N, G>;
-    static constexpr bool DDIRECT = Tune::DDIRECT || SEP != 0;   // no D_e in LDS either way
+    static constexpr int DDIRECT = SEP != 0 ? 1 : (int)Tune::DDIRECT;       // no D_e in LDS either way
     static constexpr size_t LDS_USED = DDIRECT ? Sh::LDS_BYTES / 2 : Sh::LDS_BYTES;
     static constexpr size_t LDS = LDS_USED > Tune::LDS_MIN ? LDS_USED : Tune::LDS_MIN;
     static constexpr int CODE = setting_code(G, Tune::HINT, Tune::XCD, 0, Tune::SB);
