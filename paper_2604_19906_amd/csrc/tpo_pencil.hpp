@@ -456,7 +456,7 @@ struct PencilTune {
 // elements instead of 14.  Bound by memory in one-shot bursts: a kernel of the same loads and stores alone
 // runs at 6.28 TB/s with 85 KB asked for per CU and at 5.7 TB/s with 213 KB.  Against D_e at once with 28 KB
 // (5 workgroups) 0.98 of the time at 2.4 GB, 0.977 .. 0.986 at 3, 5.5 and 8.3 GB, one matrix and three; the named
-// workload 1440 -> 1429 us
+// workload 1440 -> 1429 us with three sets of fields in turn, 1.429 and 1.430 ms on one set again and again
 // (32 and 40 KB the same within 1 %; late D_e at 24 and 28 KB 0.99 .. 1.00; D_e at once with 32 .. 40 KB
 // 1.02 .. 1.05; D_e after the product along axis 0 instead, 32 .. 40 KB, 1.01 .. 1.03).  Requests of
 // 32 / 32 / 40 KB at n = 9, 15, 16 give 0.97 .. 1.03: not taken.  The first choice was made on the named workload
