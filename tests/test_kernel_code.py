@@ -1,0 +1,28 @@
+"""What the compiler made of the kernels where a comment in the source says so."""
+import re
+
+import pytest
+
+from kernel_code import instructions
+
+
+@pytest.fixture(scope="module")
+def code():
+    found = instructions()
+    assert len(found) > 500
+    return found
+
+
+def test_accesses_keep_their_address_space(code):
+    """A FLAT access has no form with a scalar base and is waited for together with LDS and scalar loads."""
+    flat = {name: n for name, lines in code.items() if (n := sum(x.startswith("flat_") for x in lines))}
+    assert not flat
+
+
+def test_anisotropic_addresses_are_a_scalar_base_and_a_lane_offset(code):
+    kernels = {name: lines for name, lines in code.items() if re.search(r"\d+ihelm_aniso_\w*kernelI", name)}
+    assert len(kernels) >= 20
+    for name, lines in kernels.items():
+        assert not any(x.startswith("v_lshl_add_u64") for x in lines), name
+        stores = [x for x in lines if x.startswith("global_store")]
+        assert stores and all(re.search(r"s\[\d+:\d+\]", x) for x in stores), name
