@@ -282,7 +282,9 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
             tab_i[t] = mm_coef<N>(Im, false, t, lane);
         }
     };
-    // LOADS_FIRST: all four long loads go out before the tables and before anything waits for one of them.  From n = 13
+    // LOADS_FIRST: all four long loads go out before the tables, and the tables before anything waits for one of them.  (Without the
+    // second fence the products with M_e move up between the loads of the tables, whose last words then are a round trip of their own:
+    // n = 10, 14 and 15 1.03 .. 1.09 of the time at 30 MB .. 1 GB.)  From n = 13
     // on on large batches; below, the registers they hold cost more than the wait there, but less with the few units per workgroup of
     // the rows for small batches (n = 9 .. 12) and at n = 10.  At 3 GB, first against last:
     // n = 13 617 / 651 us, 14 726 / 768, 16 606 / 633; n = 12 614 / 588, 11 636 / 565, 9 605 / 542.  On smaller
@@ -308,6 +310,7 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
         for (int dir = 0; dir < 3; ++dir) load_p(dir);
         __builtin_amdgcn_sched_barrier(0);
         load_tables();
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int dir = 0; dir < 3; ++dir) {

@@ -26,3 +26,14 @@ def test_anisotropic_addresses_are_a_scalar_base_and_a_lane_offset(code):
         assert not any(x.startswith("v_lshl_add_u64") for x in lines), name
         stores = [x for x in lines if x.startswith("global_store")]
         assert stores and all(re.search(r"s\[\d+:\d+\]", x) for x in stores), name
+
+
+def test_convection_loads_first_waits_for_no_load_before_the_last_is_out(code):
+    """4x4x1 form, last template argument LOADS_FIRST; up to the first barrier."""
+    kernels = {name: lines for name, lines in code.items() if re.search(r"\d+convection_mm_kernelI\w*Lb1EEEv", name)}
+    assert len(kernels) >= 10
+    for name, lines in kernels.items():
+        lines = lines[:lines.index("s_barrier")]
+        loads = [k for k, x in enumerate(lines) if x.startswith("global_load")]
+        waits = [k for k, x in enumerate(lines) if x.startswith("s_waitcnt") and "vmcnt" in x and k > loads[0]]
+        assert loads[-1] < waits[0], name
