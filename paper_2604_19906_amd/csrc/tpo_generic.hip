@@ -44,8 +44,26 @@ constexpr int ANISO_MAX_NT = 256;
 // 0.98 at 150, 0.96 at 300, 0.97 at 800 MB; 1.00 .. 1.02 with maxima of 1.09 at 100 and 130 MB (fields that the
 // last-level cache holds in part) and at 2.5 GB, 1.0 .. 1.1 at 30 MB, up to 1.07 on elements of less than 128 points and at 50 MB
 // of less than 300.  In fp32 1.00, up to 1.24 on faces of a dozen points: not there.
-constexpr int aniso_hint(bool stream) { return stream ? 3 : 2; }
+// CACHED: v_e stored without the hint.  Thin faces that fill no whole 128-byte lines: the stores of two indices along axis 0 share most
+// lines, and past the last-level cache the hint writes a line out before its second part comes.  Cached over non-temporal, fp64, faces below
+// 192 bytes: in turns 0.79 .. 1.02 at 350 MB .. 2.4 GB (50 shapes, geometric means 0.95 .. 0.89), up to 1.07 at 290 MB, 1.02 .. 1.05 at
+// 200 MB, 1.0 .. 1.08 on faces of 16 and 24 words; one turn, elements of at most eight points along every axis and of less than 128 in all,
+// 0.90 .. 1.00 from 250 MB on, 1.00 .. 1.06 on faces of 8 and 16 words, 1.02 with one or two points along axis 0.  fp32, one turn, at most
+// six points along every axis: faces of 9 words 0.85 .. 0.91 from 200 MB on (1.17 .. 1.25 at 120 MB), of 6 and 10 words 0.98 .. 1.00; of 8,
+// 12 and 16 words 1.01 .. 1.03, in turns 0.93 .. 1.07.
+constexpr int aniso_hint(bool stream, bool cached) { return (stream ? 1 : 0) | (cached ? 0 : 2); }
 constexpr bool aniso_xcd(bool stream) { return !stream; }
+template <typename T>
+bool aniso_cached_stores(const AnisoArgs &a, bool turns)
+{
+    const int face = a.ny * a.nz, points = a.nx * face;
+    const long long mib = 3LL * a.num_elems * points * (long long)sizeof(T) >> 20;
+    const auto all_up_to = [&](int n) { return a.nx <= n && a.ny <= n && a.nz <= n; };
+    if (sizeof(T) == 4)
+        return !turns && a.nx >= 3 && a.ny > 1 && a.nz > 1 && all_up_to(6) && face < 12 && face % 4 != 0 && mib >= 184;
+    if (turns) return face < 24 && face != 16 && mib >= 320;
+    return a.nx >= 3 && all_up_to(8) && !all_up_to(4) && points < 128 && face < 24 && face % 8 != 0 && mib >= 224;
+}
 template <typename T>
 bool aniso_stream(const AnisoArgs &a, bool turns)
 {
@@ -554,12 +572,12 @@ bool turns_pay(const AnisoArgs &a, int g1, int nt1, int &g, int &nt)
     return q <= 0.8 && mib >= 96;
 }
 
-template <typename T, int MAXN, bool STREAM>
+template <typename T, int MAXN, bool STREAM, bool CACHED = false>
 hipError_t launch_turns_as(const AnisoArgs &a, int g, int nt)
 {
     const long long groups = (a.num_elems + g - 1) / g;
     drop_stale_error();
-    hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
+    hipLaunchKernelGGL((ihelm_aniso_turns_kernel<T, MAXN, aniso_hint(STREAM, CACHED), aniso_xcd(STREAM)>),
                        dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt),
                        (size_t)g * a.nx * aniso_pyz(a.ny, a.nz) * sizeof(T), a.stream,
                        (const T *)a.u, (const T *)a.d, (unsigned)a.num_elems, (unsigned)groups, packed_sizes(a.nx, a.ny, a.nz),
@@ -571,17 +589,24 @@ hipError_t launch_turns_as(const AnisoArgs &a, int g, int nt)
 template <typename T, int MAXN>
 hipError_t launch_turns(const AnisoArgs &a, int g, int nt)
 {
-    if constexpr (sizeof(T) == 8)
-        if (aniso_stream<T>(a, true)) return launch_turns_as<T, MAXN, true>(a, g, nt);
+    if constexpr (sizeof(T) == 8) {
+        const bool stream = aniso_stream<T>(a, true);
+        if (aniso_cached_stores<T>(a, true)) {
+            if constexpr (MAXN > 8)                         // class of 8: no shape of 128 points with such a face runs in turns
+                if (stream) return launch_turns_as<T, MAXN, true, true>(a, g, nt);
+            return launch_turns_as<T, MAXN, false, true>(a, g, nt);
+        }
+        if (stream) return launch_turns_as<T, MAXN, true>(a, g, nt);
+    }
     return launch_turns_as<T, MAXN, false>(a, g, nt);
 }
 
-template <typename T, int MAXN, bool STREAM>
+template <typename T, int MAXN, bool STREAM, bool CACHED = false>
 hipError_t launch_bound_as(const AnisoArgs &a, int g, int nt, size_t lds)
 {
     const long long groups = (a.num_elems + g - 1) / g;
     drop_stale_error();
-    hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, aniso_hint(STREAM), aniso_xcd(STREAM)>),
+    hipLaunchKernelGGL((ihelm_aniso_kernel<T, MAXN, aniso_hint(STREAM, CACHED), aniso_xcd(STREAM)>),
                        dim3((unsigned)pencil_grid<aniso_xcd(STREAM)>(groups)), dim3(nt), lds, a.stream,
                        (const T *)a.u, (const T *)a.d, (unsigned)a.num_elems, (unsigned)groups, packed_sizes(a.nx, a.ny, a.nz),
                        (unsigned)g, lane_reciprocal(a.ny * a.nz), lane_reciprocal(a.nx * a.nz), lane_reciprocal(a.nx * a.ny),
@@ -594,6 +619,8 @@ hipError_t launch_bound(const AnisoArgs &a, int g, int nt, size_t lds)
 {
     if constexpr (sizeof(T) == 8 && MAXN > 4)            // STREAM needs 128 points
         if (aniso_stream<T>(a, false)) return launch_bound_as<T, MAXN, true>(a, g, nt, lds);
+    if constexpr (MAXN <= 6 ? sizeof(T) == 4 : sizeof(T) == 8 && MAXN == 8)
+        if (aniso_cached_stores<T>(a, false)) return launch_bound_as<T, MAXN, false, true>(a, g, nt, lds);
     return launch_bound_as<T, MAXN, false>(a, g, nt, lds);
 }
 
@@ -678,4 +705,15 @@ extern "C" int tpo_internal_aniso_streams(int nx, int ny, int nz, int dtype, lon
     a.nz = nz;
     a.num_elems = num_elems;
     return dtype == TPO_F64 && tpo::aniso_stream<double>(a, tpo_internal_aniso_turns(nx, ny, nz, dtype, num_elems) != 0);
+}
+
+extern "C" int tpo_internal_aniso_caches(int nx, int ny, int nz, int dtype, long long num_elems)
+{
+    tpo::AnisoArgs a = {};
+    a.nx = nx;
+    a.ny = ny;
+    a.nz = nz;
+    a.num_elems = num_elems;
+    const bool turns = tpo_internal_aniso_turns(nx, ny, nz, dtype, num_elems) != 0;
+    return dtype == TPO_F64 ? tpo::aniso_cached_stores<double>(a, turns) : tpo::aniso_cached_stores<float>(a, turns);
 }

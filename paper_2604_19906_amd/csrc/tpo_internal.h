@@ -122,3 +122,4 @@ extern "C" int tpo_internal_aniso_takes_slice(int nx, int ny, int nz, int dtype,
 extern "C" int tpo_internal_slice_class_built(int nx, int ksb, int ksc);
 extern "C" int tpo_internal_aniso_turns(int nx, int ny, int nz, int dtype, long long num_elems);
 extern "C" int tpo_internal_aniso_streams(int nx, int ny, int nz, int dtype, long long num_elems);
+extern "C" int tpo_internal_aniso_caches(int nx, int ny, int nz, int dtype, long long num_elems);

@@ -83,6 +83,49 @@ def test_streaming(dims, mib):
     check(dims, "f64", e)
 
 
+def cached_shapes(regs, streams):
+    """fp64 calls in turns on 320 MiB that store v_e without the non-temporal hint: fewest and most elements per workgroup."""
+    found = []
+    for dims in itertools.product(range(1, regs + 1), repeat=3):
+        if max(8, (max(dims) + 1) // 2 * 2) != regs:
+            continue
+        e = -(-(320 << 20) // (24 * dims[0] * dims[1] * dims[2]))
+        g = turns(dims, "f64", e)[0]
+        if g and hints(dims, e) == (streams, 1):
+            found.append((g, dims, e))
+    return [min(found), max(found)]
+
+
+def hints(dims, e, dtype="f64"):
+    """(streaming hints, stores without the hint) of a call."""
+    fns = [getattr(tpo.lib(), f"tpo_internal_aniso_{k}") for k in ("streams", "caches")]
+    for fn in fns:
+        fn.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
+    return tuple(fn(*dims, DTYPES[dtype][0], e) for fn in fns)
+
+
+@pytest.mark.parametrize("regs", [8, 10, 12, 14, 16])
+@pytest.mark.parametrize("streams", [0, 1])
+def test_cached_stores_in_turns(regs, streams):
+    if (regs, streams) == (8, 1):
+        return                  # no shape of this class with 128 points and such a face runs in turns
+    for g, dims, e in cached_shapes(regs, streams):
+        e += g > 1 and e % g == 0
+        assert hints(dims, e) == (streams, 1) and turns(dims, "f64", e)[0] == g
+        print(f"case cached turns dims={dims} E={e} streams={streams} g={g}", flush=True)
+        check(dims, "f64", e)
+
+
+@pytest.mark.parametrize("dims,dtype", [((3, 3, 5), "f64"), ((5, 2, 2), "f64"), ((8, 3, 5), "f64"), ((6, 7, 3), "f64"),
+                                        ((4, 3, 3), "f32"), ((6, 3, 3), "f32"), ((3, 2, 5), "f32")])
+def test_cached_stores_in_one_turn(dims, dtype):
+    mib = 224 if dtype == "f64" else 184
+    e = -(-(mib << 20) // (3 * dims[0] * dims[1] * dims[2] * DTYPES[dtype][2])) + 1
+    assert hints(dims, e, dtype) == (0, 1) and turns(dims, dtype, e)[0] == 0
+    print(f"case cached {dtype} dims={dims} E={e}", flush=True)
+    check(dims, dtype, e)
+
+
 def check(dims, dtype, e):
     rng = np.random.default_rng([19906, 81, *dims])
     real = np.float64 if dtype == "f64" else np.float32

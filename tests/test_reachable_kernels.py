@@ -69,10 +69,12 @@ def test_convection(built):
 
 
 def test_anisotropic(built):
-    """Size classes by the largest of the three sizes; (hint, renumbering) with and without streaming hints (fp64, 128 points up)."""
-    both = ((2, 1), (3, 0))
+    """Size classes by the largest of the three sizes; (hint, renumbering) with and without streaming hints (fp64, 128 points up), and
+    without the hint on the stores of thin faces (in turns in fp64, in one turn small elements)."""
+    both, cached = ((2, 1), (3, 0)), ((0, 1), (1, 0))
     assert built["ihelm_aniso_kernel"] == (
-        {("f", c, 2, 1) for c in (4, 6, 8, 12, 16)} | {("d", 4, 2, 1)}
+        {("f", c, 2, 1) for c in (4, 6, 8, 12, 16)} | {("d", 4, 2, 1), ("d", 8, 0, 1), ("f", 4, 0, 1), ("f", 6, 0, 1)}
         | {("d", c, *h) for c in (8, 10, 12, 16) for h in both})
     assert built["ihelm_aniso_turns_kernel"] == (
-        {("f", c, 2, 1) for c in (8, 10, 12, 14, 16)} | {("d", c, *h) for c in (8, 10, 12, 14, 16) for h in both})
+        {("f", c, 2, 1) for c in (8, 10, 12, 14, 16)}
+        | {("d", c, *h) for c in (8, 10, 12, 14, 16) for h in both + cached if (c, h) != (8, (1, 0))})

@@ -45,6 +45,35 @@ def test_lines(turns, dims, dtype, mb, taken):
     assert (turns(dims, dtype, elems(dims, dtype, mb))[0] > 0) == taken
 
 
+# Calls whose result is stored without the non-temporal hint; time with the hint gone over with it beside each
+F64, F32 = tpo.TPO_F64, tpo.TPO_F32
+
+
+@pytest.mark.parametrize("dims,dtype,mb,taken", [
+    ((13, 3, 3), F64, 400, True),        # 0.81, in turns
+    ((13, 3, 3), F64, 300, False),       # 0.84 there, 1.02 .. 1.07 on (11,4,3), (16,12,1), (15,9,2)
+    ((10, 7, 2), F64, 1000, True),       # 0.92
+    ((13, 1, 15), F64, 2400, True),      # 0.81
+    ((16, 5, 3), F64, 700, True),        # 0.98
+    ((10, 8, 2), F64, 700, False),       # 1.03: faces of whole lines
+    ((9, 12, 2), F64, 700, False),       # 1.03
+    ((3, 3, 5), F64, 250, True),         # 0.95, one turn per pass
+    ((3, 3, 5), F64, 200, False),
+    ((3, 4, 4), F64, 400, False),        # 1.03: lines shared by whole faces
+    ((2, 7, 2), F64, 400, False),        # 1.02
+    ((11, 4, 2), F64, 700, False),      # 1.01
+    ((6, 3, 3), F32, 700, True),        # 0.88
+    ((6, 3, 3), F32, 200, True),        # 0.85
+    ((6, 3, 3), F32, 120, False),       # 1.25
+    ((4, 3, 3), F32, 1500, True),       # 0.87
+    ((4, 6, 2), F32, 400, False),       # 1.02
+    ((13, 3, 3), F32, 700, False)])
+def test_cached_stores(dims, dtype, mb, taken):
+    fn = tpo.lib().tpo_internal_aniso_caches
+    fn.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong]
+    assert fn(*dims, dtype, elems(dims, dtype, mb)) == taken
+
+
 @pytest.mark.parametrize("dtype,word", [(tpo.TPO_F64, 8), (tpo.TPO_F32, 4)])
 def test_what_is_launched_fits(turns, dtype, word):
     """Words per lane within the register class, LDS within 48 KB, whole wavefronts, quotients exact."""
