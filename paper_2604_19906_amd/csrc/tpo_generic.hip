@@ -39,6 +39,8 @@ namespace tpo {
 namespace {
 
 constexpr int ANISO_MAX_NT = 256;
+constexpr int kMaxPencils = TPO_MAX_N * TPO_MAX_N;          // of one element in one pass
+constexpr size_t kTurnsLds = 48 * 1024;                     // of a workgroup of the turns kernel, at most
 // Hints and die renumbering: non-temporal stores of v_e and workgroups renumbered per die, or (STREAM) non-temporal
 // loads of u_e as well and no renumbering.  STREAM over the other in fp64, geometric means over 120 shapes: 0.93 at 52 and 60 MB,
 // 0.98 at 150, 0.96 at 300, 0.97 at 800 MB; 1.00 .. 1.02 with maxima of 1.09 at 100 and 130 MB (fields that the
@@ -198,12 +200,12 @@ __device__ __forceinline__ unsigned aniso_batch(unsigned groups)        // penci
 }
 
 constexpr unsigned lane_reciprocal(int d) { return (65536u + d - 1) / d; }
-// t / d for t, d <= 256 (t < 256), m = lane_reciprocal(d): m d exceeds 65536 by r < d, so t m / 65536 exceeds t / d by less than
+// t / d for a lane t and d pencils, m = lane_reciprocal(d): m d exceeds 65536 by r < d, so t m / 65536 exceeds t / d by less than
 // 1 / d while t r < 65536.
 constexpr bool lane_reciprocals_exact()
 {
-    for (unsigned d = 1; d <= 256; ++d)
-        for (unsigned t = 0; t < 256; ++t)
+    for (unsigned d = 1; d <= kMaxPencils; ++d)
+        for (unsigned t = 0; t < ANISO_MAX_NT; ++t)
             if (t * lane_reciprocal((int)d) >> 16 != t / d) return false;
     return true;
 }
@@ -335,13 +337,15 @@ ihelm_aniso_kernel(const T *u, const T *__restrict__ D, TPO_ANISO_SHAPE,
 // 216 KB here).  us per call on 800 MB, kernel above / this one: fp64 (3,9,16) 329 / 155, (16,9,3) 279 / 157, (13,3,12)
 // 267 / 157, (10,7,13) 192 / 161; fp32 (3,9,15) 438 / 184, (14,4,3) 279 / 190, (8,15,6) 225 / 189 (both since 5 .. 10 % faster).
 // With one turn per pass it is the slower one by 3 .. 15 % (quotients, loops).
-// t / d for t <= 2^15 and d <= 256, with m = turn_reciprocal(d): m d exceeds 2^23 by r < d, so t m / 2^23 exceeds t / d by less
-// than 1 / d while t r < 2^23.  (A workgroup's elements have at most 48 KB: t <= 12288.)
+// t / d for t < 2^15 (24 bits hold t << 9) and d pencils, with m = turn_reciprocal(d): m d exceeds 2^23 by r < d, so t m / 2^23 exceeds
+// t / d by less than 1 / d while t r < 2^23.  A workgroup's pencils are fewer than its words in LDS.
 constexpr unsigned turn_reciprocal(int d) { return ((1u << 23) + d - 1) / d; }
-constexpr bool turn_reciprocals_exact()       // the excess grows with t: the last two whole multiples of d and the word before
+constexpr bool turn_reciprocals_exact()
 {
-    for (unsigned long long d = 1; d <= 256; ++d)
-        for (unsigned long long q = 12288 / d, t = q * d - 1; t <= q * d; ++t)
+    // the excess grows with t and shows first on the word before a multiple of d: the last such word, and the multiple
+    constexpr unsigned long long words = kTurnsLds / sizeof(float);
+    for (unsigned long long d = 1; d <= kMaxPencils; ++d)
+        for (unsigned long long q = words / d, t = q * d - 1; t <= q * d; ++t)
             if (((t << 9) * turn_reciprocal((int)d)) >> 32 != t / d || (t << 9) >> 24 != 0 || turn_reciprocal((int)d) >> 24 != 0) return false;
     return true;
 }
@@ -539,7 +543,7 @@ void aniso_turns_shape(int nx, int ny, int nz, int &g, int &nt)
     g = nt = 0;
     double best = 0;
     for (int lanes = 64; lanes <= ANISO_MAX_NT; lanes += 64)
-        for (int c = 1; c <= 64 && c * cube_bytes <= 48 * 1024; ++c) {
+        for (int c = 1; c <= 64 && c * cube_bytes <= kTurnsLds; ++c) {
             if (ceil_div(c * ny * nz, lanes) * nx > regs || ceil_div(c * nx * ny, lanes) * nz > regs) break;
             const double use = aniso_lane_use(nx, ny, nz, c, lanes);
             if (use > best + 1e-9) {

@@ -91,7 +91,8 @@ def test_what_is_launched_fits(turns, dtype, word):
         assert -(-g * ny * nz // lanes) * nx <= regs and -(-g * nx * ny // lanes) * nz <= regs
         assert g * nx * ((ny * (nz | 1)) | 1) * word <= 48 * 1024
         for d in {ny * nz, nx * nz, nx * ny, ny, nz} - {1}:
-            inverse = -(-(1 << 32) // d)
-            most = g * max(ny * nz, nx * nz, nx * ny) + lanes
-            assert all((t * inverse) >> 32 == t // d for t in {0, 1, d - 1, d, most - most % d, most - most % d - 1, most})
+            inverse = -(-(1 << 23) // d)        # 24-bit product with t << 9, upper half
+            most = g * max(ny * nz, nx * nz, nx * ny) - 1
+            assert most << 9 < 1 << 24 and inverse < 1 << 24
+            assert all(((t << 9) * inverse) >> 32 == t // d for t in {0, 1, d - 1, d, most - most % d, most - most % d - 1, most} if 0 <= t <= most)
     assert reached == {8, 10, 12, 14, 16}
