@@ -32,7 +32,8 @@
 namespace tpo {
 
 // Added to the words per batch of scalar loads: the matrices are touched once before the first product (warm_scalar_cache); on
-// rows that end where a launch passes one workgroup per CU.
+// rows that end where a launch comes to about one workgroup per CU (whole MiB: 171 .. 268 workgroups on 256 CUs).  A row of a kernel
+// that has no such step is refused below.
 constexpr int kWarm = 256;
 
 // sb: words per batch of scalar loads (matrix_product), with or without kWarm; mm: 4x4x1 matrix-core form (halves in fp32).
@@ -329,6 +330,28 @@ static_assert(batch_rows_in_order(PencilMmRows::rows) && batch_rows_in_order(Pen
 static_assert(batch_rows_in_order(TransformRows<double>::rows) && batch_rows_in_order(TransformRows<float>::rows));
 static_assert(batch_rows_in_order(SquareConvectionRows<double>::rows) && batch_rows_in_order(SquareConvectionRows<float>::rows));
 static_assert(convection_rect_first_in_order<double>() && convection_rect_first_in_order<float>());
+
+// kWarm stands only where a kernel takes it: not in the 4x4x1 forms (mm, or all rows of a family) and not in the over-integrated
+// forms 1 and 2.
+template <typename ROWS>
+constexpr bool warm_rows_warm(const ROWS &rows, bool all_mm = false)
+{
+    for (const auto &list : rows.row)
+        for (const auto &r : list)
+            if ((r.sb & kWarm) != 0 && (all_mm || r.mm != 0)) return false;
+    return true;
+}
+template <typename T>
+constexpr bool convection_rect_warm_rows_warm()
+{
+    for (const ConvRectFirst &r : ConvRectFirstTable<T>::row)
+        if ((r.sb & kWarm) != 0 && r.form != 0) return false;
+    return true;
+}
+static_assert(warm_rows_warm(PencilMmRows::rows, true) && warm_rows_warm(PencilMmSepRows::rows, true));
+static_assert(warm_rows_warm(TransformRows<double>::rows) && warm_rows_warm(TransformRows<float>::rows));
+static_assert(warm_rows_warm(SquareConvectionRows<double>::rows) && warm_rows_warm(SquareConvectionRows<float>::rows));
+static_assert(convection_rect_warm_rows_warm<double>() && convection_rect_warm_rows_warm<float>());
 
 // MiB of the last row of n (0: no rows): a setting for smaller batches than that is never taken.
 template <typename ROWS>

@@ -172,29 +172,34 @@ __device__ __forceinline__ void matrix_product(const TPO_CONSTANT T *S, const T 
     }
 }
 
-// Settings with kWarm in SB (launches of at most one workgroup per CU): every 64-byte line of the matrices is touched by scalar
-// loads that all go out before one wait, right after the wavefront has asked for its first words of the fields.  There the matrices
-// are in no scalar cache yet, and every batch of a product misses, one wait after the other; on larger launches the workgroups
-// before have brought them in, and the touching only costs (1.01 .. 1.05).  Time with / without, fp64, up to the rows' ends: halves n = 12 0.93 .. 0.99, 13
-// 0.90 .. 0.93, 14 and 15 0.92 .. 0.95, 16 0.73 .. 0.83; convection n = 10 .. 14 0.90 .. 0.93, 15 0.85 .. 0.89, 16 0.88 .. 0.90, (8,12) and (9,14) 0.91 ..
-// 0.96; operator n = 9 0.90 (three matrices; one 0.97), 10 0.87 (0.97), with one matrix 11, 13, 14, 15 0.95 .. 0.97 (with three they run in the tiles);
-// separable n = 9, 10 0.90 .. 0.93.  Smaller matrices gain nothing (0.98 .. 1.05).
+// Settings with kWarm in SB (launches of about one workgroup per CU at most): every 64-byte line of the matrices is touched right after
+// the wavefront has asked for its first words of the fields, by scalar loads that all go out before one wait per matrix (a second and
+// third one only where they differ: the registers of all three do not fit).  There the matrices are in no scalar cache yet, and every
+// batch of a product misses, one wait after the other; on larger launches the workgroups before have brought them in, and the touching only
+// costs (1.01 .. 1.05).  Time with / without, fp64, up to the rows' ends: halves n = 12 0.90 .. 0.97, 13 0.86 .. 0.96, 14 and 15 0.88 ..
+// 0.92, 16 0.72 .. 0.80; convection n = 10 .. 13 0.89 .. 0.92, 14 0.89 .. 0.98, 15 0.86 .. 0.92, 16 0.88 .. 0.90, (8,12) and (9,14) 0.91 ..
+// 0.98; operator n = 9 0.93 .. 1.00 (three matrices; one 0.99), 10 0.87 .. 0.88 (0.99), with one matrix 11 0.96 .. 0.97, 13 .. 15 0.93 .. 0.97
+// (with three they run in the tiles); separable n = 9, 10 0.89 .. 0.92.  Smaller matrices gain nothing (0.98 .. 1.05).  Touched in groups of
+// eight with a wait after each, as the compiler has it where one register collects the words: halves 1.02 .. 1.06 of this time,
+// convection 1.00 .. 1.03, operator and separable form 1.00 .. 1.02.
 template <int SB, int WORDS, typename T, typename... M>
 __device__ __forceinline__ void warm_scalar_cache(const TPO_CONSTANT T *first, M... more)
 {
     if constexpr ((SB & kWarm) != 0) {
-        unsigned seen = 0;
+        constexpr int LINES = (WORDS * (int)sizeof(T) + 63) / 64 + 1;       // and the last word, which may lie in a line of its own
         auto touch = [&](const TPO_CONSTANT T *S) {
             const TPO_CONSTANT unsigned *w = (const TPO_CONSTANT unsigned *)S;
-            constexpr int DW = WORDS * (int)sizeof(T) / 4;
-            seen |= w[DW - 1];
+            unsigned t[LINES];
 #pragma unroll
-            for (int k = 0; k < DW; k += 16) seen |= w[k];
+            for (int k = 0; k < LINES - 1; ++k) t[k] = w[16 * k];
+            t[LINES - 1] = w[WORDS * (int)sizeof(T) / 4 - 1];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < LINES; ++k) asm volatile("" :: "s"(t[k]));
         };
         __builtin_amdgcn_sched_barrier(0);
         touch(first);
         ((more != first ? touch(more) : void()), ...);
-        asm volatile("" :: "s"(seen));
         __builtin_amdgcn_sched_barrier(0);
     }
 }

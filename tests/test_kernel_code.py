@@ -37,3 +37,21 @@ def test_convection_loads_first_waits_for_no_load_before_the_last_is_out(code):
         loads = [k for k, x in enumerate(lines) if x.startswith("global_load")]
         waits = [k for k, x in enumerate(lines) if x.startswith("s_waitcnt") and "vmcnt" in x and k > loads[0]]
         assert loads[-1] < waits[0], name
+
+
+def test_matrices_are_touched_before_one_wait_each(code):
+    """Settings with kWarm (last template argument 256 and up): one scalar load per 64-byte line and the last word, then a wait."""
+    kernels = {name: lines for name, lines in code.items() if re.search(r"Li(288|296)EEEv", name)}
+    assert len(kernels) >= 20
+    for name, lines in kernels.items():
+        sizes = [int(x) for x in re.findall(r"L[ib](\d+)E", name)]
+        words = sizes[0] * (sizes[1] if "convection_rect" in name else sizes[0])
+        runs, run = [], 0
+        for x in lines[:lines.index("s_barrier")]:
+            if re.match(r"s_load_dword s\d+,", x):
+                run += 1
+            elif x.startswith("s_waitcnt") and "lgkmcnt" in x and run:
+                runs.append(run)
+                run = 0
+        matrices = 2 if "convection" in name else 3
+        assert runs == [-(-words * 8 // 64) + 1] * matrices, name
