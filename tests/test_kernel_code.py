@@ -54,4 +54,5 @@ def test_matrices_are_touched_before_one_wait_each(code):
                 runs.append(run)
                 run = 0
         matrices = 2 if "convection" in name else 3
-        assert runs == [-(-words * 8 // 64) + 1] * matrices, name
+        single = -(-words * 8 // 64) + (1 if words % 8 != 1 else -1)       # the last word of an odd matrix comes with the one before
+        assert runs == [single] * matrices, name
