@@ -16,6 +16,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -84,19 +85,27 @@ def build(jobs: int = 8, verbose: bool = True) -> str:
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(srcs) + 1))) as ex:
         binding = ex.submit(_build_torch_binding)
         objs = list(ex.map(_compile, srcs))
-        binding.result()
     for lib, part in ((LIB, [o for s_, o in zip(srcs, objs) if not s_.startswith("bench_")]),
                       (BENCH_LIB, [o for s_, o in zip(srcs, objs) if s_.startswith("bench_")])):
         tmp = lib + f".tmp{os.getpid()}"
         cmd = ["hipcc", "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + part
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError("link failed:\n" + r.stderr)
+            raise RuntimeError(f"link failed:\n{r.stderr}")
         os.replace(tmp, lib)
         if verbose:
             print(f"built {lib} from {len(part)} sources")
-    if verbose:
-        print(f"built {TORCH_BINDING}")
+    # The C libraries need hipcc alone.  Without torch, g++ or Python's headers the tensor functions keep their Python form; one left
+    # from an earlier build does not stay.
+    try:
+        binding.result()
+    except (ImportError, OSError, RuntimeError) as e:
+        if os.path.exists(TORCH_BINDING):
+            os.remove(TORCH_BINDING)
+        warnings.warn(f"{TORCH_BINDING} is not built, tensor functions run in their Python form: {e}")
+    else:
+        if verbose:
+            print(f"built {TORCH_BINDING}")
     return LIB
 
 
