@@ -63,13 +63,16 @@ def _compile(src: str) -> str:
 def _build_torch_binding() -> None:
     import torch
 
+    from .tpo import binding_versions
+
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                os.path.join(rocm, "include"), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
     tmp = TORCH_BINDING + f".tmp{os.getpid()}"
     cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DTPO_BUILT_FOR="{binding_versions()}"']
            + ["-isystem" + d for d in include]
            + [os.path.join(CSRC, "torch_binding.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"),
               "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
@@ -91,7 +94,7 @@ def build(jobs: int = 8, verbose: bool = True) -> str:
         cmd = ["hipcc", "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + part
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError(f"link failed:\n{r.stderr}")
+            raise RuntimeError("link failed:\n" + r.stderr)
         os.replace(tmp, lib)
         if verbose:
             print(f"built {lib} from {len(part)} sources")

@@ -235,4 +235,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tpo_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tpo_torch(void) { return PyModule_Create(&module); }
+// built_for: what this file was compiled against (binding_versions() in tpo.py), compared before any other use.  The accessors above are
+// inlined with the offsets of that torch, so another one may well load and read the wrong members.
+PyMODINIT_FUNC PyInit__tpo_torch(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", TPO_BUILT_FOR) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -216,27 +216,42 @@ TORCH_BINDING_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_
 _native = None
 
 
+def binding_versions() -> str:
+    """What the native form has compiled in: torch (offsets of a tensor's members), the interpreter, the C header."""
+    import hashlib
+    import sysconfig
+
+    import torch
+
+    header = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "tpo.h")
+    with open(header, "rb") as f:
+        digest = hashlib.sha256(f.read()).hexdigest()[:16]
+    return f"torch {torch.__version__} {torch.version.git_version}, {sysconfig.get_config_var('SOABI')}, tpo.h {digest}"
+
+
 def _load_native():
     global _native
+    import importlib.util
+    import warnings
+
+    import torch  # noqa: F401  (the libraries that the binding is linked to)
+
     _native = False
-    if os.path.exists(TORCH_BINDING_PATH):
-        import importlib.util
-        import warnings
-
-        import torch  # noqa: F401  (the libraries that the binding is linked to)
-
-        l = lib()
+    try:
         spec = importlib.util.spec_from_file_location("_tpo_torch", TORCH_BINDING_PATH)
-        try:
-            module = importlib.util.module_from_spec(spec)
-            spec.loader.exec_module(module)
-        except ImportError as e:        # built for another torch
-            warnings.warn(f"{TORCH_BINDING_PATH} cannot be loaded ({e}): tensor functions run in their Python form")
-            return _native
-        module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-            l.tpo_ihelm_apply_variant, l.tpo_ihelm_apply_sep_variant, l.tpo_transform_apply, l.tpo_convection_apply,
-            l.tpo_ihelm_apply_aniso)))
-        _native = module
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        built_for, here = getattr(module, "built_for", "an unknown torch"), binding_versions()
+        if built_for != here:
+            raise ImportError(f"built for {built_for}, this is {here}")
+    except (ImportError, OSError) as e:     # missing, without a symbol it needs, for another torch, interpreter or header
+        warnings.warn(f"{TORCH_BINDING_PATH} cannot be used ({e}): tensor functions run in their Python form")
+        return _native
+    l = lib()
+    module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        l.tpo_ihelm_apply_variant, l.tpo_ihelm_apply_sep_variant, l.tpo_transform_apply, l.tpo_convection_apply,
+        l.tpo_ihelm_apply_aniso)))
+    _native = module
     return _native
 
 
