@@ -4,10 +4,11 @@
 // shorter than the call 1.4 to 1.8 times as fast; a call that is waited for alone 18 against 22 us).
 //
 // Only the plain case is done here: exact torch.Tensor objects on a device, dense, without any wrapper or mode in their
-// dispatch keys, arguments as documented.  For everything else a function returns None without having done anything, and the
+// dispatch keys, outside of torch function modes (which see the Python form's calls, the new output's among them), arguments as documented.  For everything else a function returns None without having done anything, and the
 // Python form takes the call with its own checks and errors.  A status other than TPO_OK comes back as a number.
 #include <Python.h>
 
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
 #include <c10/core/DispatchKeySet.h>
@@ -40,9 +41,10 @@ const at::Tensor *plain(PyObject *o)
     return &t;
 }
 
-// `count` arguments as plain tensors of the first one's type; false if one is not.
+// `count` arguments as plain tensors of the first one's type; false if one is not, or if a torch function mode is active.
 bool plain_all(PyObject *const *args, int count, const at::Tensor **out)
 {
+    if (at::impl::torch_function_mode_enabled()) return false;
     for (int k = 0; k < count; ++k) {
         int same = 0;
         while (same < k && args[same] != args[k]) ++same;

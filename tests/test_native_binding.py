@@ -164,3 +164,35 @@ def test_wrapped_tensors_and_streams():
     side.synchronize()
     assert torch.equal(v, want)
     tpo.check(tpo.tpo_destroy(), "tpo_destroy")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_torch_function_modes_see_the_call(name, monkeypatch):
+    """A mode that watches or replaces torch's functions sees the same calls in both forms; it may make the output."""
+    class Mode(torch.overrides.TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.seen, self.made = [], []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            r = func(*args, **(kwargs or {}))
+            self.seen.append(getattr(func, "__name__", str(func)))
+            if func in (torch.empty_like, torch.empty):
+                self.made.append(r)
+            return r
+
+    tpo.check(tpo.tpo_create(), "tpo_create")
+    module = tpo._load_native()
+    args = arguments(name, "cuda")
+    want = getattr(tpo, name)(*args)
+    seen = []
+    for native in (module, False):
+        monkeypatch.setattr(tpo, "_native", native)
+        with Mode() as mode:
+            got = getattr(tpo, name)(*args)
+        assert len(mode.made) == 1 and got is mode.made[0] and torch.equal(got, want)
+        seen.append(mode.seen)
+    assert seen[0] == seen[1]
+    torch.cuda.synchronize()
+    tpo.check(tpo.tpo_destroy(), "tpo_destroy")
