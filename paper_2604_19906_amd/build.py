@@ -38,6 +38,8 @@ HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall", "-
              # registers with the launch: a wavefront asks for its first words of u without waiting for a
              # scalar load.  Geometric means over all n, with / without: 1 .. 30 MB 0.96 .. 0.98 (operator,
              # separable form, halves, convection term), 100 MB 0.97 .. 0.99, 1 GB 0.99 .. 1.00
+             # (a launch gets 0.12 us longer by it: settings that lose have their arguments held back, kHeld in
+             # tpo_batch_rows.hpp)
              "-mllvm", "-amdgpu-kernarg-preload-count=14",
              "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 

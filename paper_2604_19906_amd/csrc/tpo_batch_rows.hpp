@@ -36,7 +36,17 @@ namespace tpo {
 // that has no such step is refused below.
 constexpr int kWarm = 256;
 
-// sb: words per batch of scalar loads (matrix_product), with or without kWarm; mm: 4x4x1 matrix-core form (halves in fp32).
+// Added as well: the kernel's arguments stay in memory (KernelField), in both halves or in one of them (the operator and the separable
+// form: both).  Preloaded ones make a launch about 0.12 us longer and every workgroup's first load one scalar load earlier; kernels of few
+// instructions (n <= 4) and the fp64 halves of n = 12 .. 15, which the preloaded registers bring spilled scalars, lose by it until a
+// launch takes several rounds of workgroups.  Preloaded over held, one matrix and three: halves n = 1 and 2 1.02 .. 1.08 up to the rows' ends, n = 3
+// 1.00 .. 1.07, 4 fp32 1.00 .. 1.05, fp64 0.97 .. 1.05 (0.96 .. 1.01 past 1 MB); n = 12 forward 1.02 .. 1.05 (backward 0.91 .. 0.93), 14 0.99 ..
+// 1.02 and 1.02 .. 1.06, 15 1.01 .. 1.03 and 1.03 .. 1.07; on the rows behind, up to 24 MiB, 1.01 .. 1.05 with one matrix, 0.97 .. 1.01
+// with three, which were no slower held than before there were preloaded arguments; operator n = 1 and 2 1.00 .. 1.08, separable n = 1 1.02.
+// Everywhere else 0.86 .. 1.01.
+constexpr int kHeldForward = 512, kHeldBackward = 1024, kHeld = kHeldForward + kHeldBackward;
+
+// sb: words per batch of scalar loads (matrix_product), with or without the flags above; mm: 4x4x1 matrix-core form (halves in fp32).
 struct BatchRow { int mib = 0, g = 0, hint = 0, xcd = 0, sb = 0, mm = 0; };
 constexpr int kBatchRows = 6;                   // a row with mib = 0 ends the list
 struct BatchRows { BatchRow row[TPO_MAX_N + 1][kBatchRows]; };
@@ -45,8 +55,9 @@ struct BatchRows { BatchRow row[TPO_MAX_N + 1][kBatchRows]; };
 template <typename T> struct PencilRows;
 template <> struct PencilRows<double> {
     static constexpr BatchRows rows = {{
-        {}, {},
-        /* 2 */ {{253, 16, 0, 0, 32}},
+        {},
+        /* 1 */ {{3, 64, 2, 1, 32 + kHeld}},
+        /* 2 */ {{3, 16, 0, 0, 32 + kHeld}, {253, 16, 0, 0, 32}},
         /* 3 */ {{26, 24, 2, 0, 32}, {253, 24, 0, 0, 32}, {1650, 24, 2, 0, 32}},
         /* 4 */ {{50, 8, 2, 0, 32}, {102, 8, 0, 0, 32}, {142, 8, 2, 0, 32}},
         /* 5 */ {{5, 16, 0, 0, 32}, {37, 8, 2, 0, 32}, {874, 8, 0, 0, 32}},
@@ -65,8 +76,9 @@ template <> struct PencilRows<double> {
 };
 template <> struct PencilRows<float> {
     static constexpr BatchRows rows = {{
-        {}, {},
-        /* 2 */ {{9, 16, 0, 0, 32}, {253, 16, 0, 0, 32}},
+        {},
+        /* 1 */ {{1, 64, 2, 1, 32 + kHeld}},
+        /* 2 */ {{1, 16, 0, 0, 32 + kHeld}, {9, 16, 0, 0, 32}, {253, 16, 0, 0, 32}},
         /* 3 */ {{14, 32, 0, 0, 32}, {85, 6, 0, 0, 32}, {253, 32, 0, 0, 32}},
         /* 4 */ {{50, 8, 2, 0, 32}, {184, 3, 2, 0, 32}},
         /* 5 */ {{14, 2, 0, 0, 32}, {26, 8, 2, 0, 32}, {253, 8, 0, 0, 32}},
@@ -78,7 +90,8 @@ template <> struct PencilRows<float> {
 template <typename T> struct PencilSepRows;
 template <> struct PencilSepRows<double> {
     static constexpr BatchRows rows = {{
-        {}, {},
+        {},
+        /* 1 */ {{1, 64, 2, 1, 32 + kHeld}},
         /* 2 */ {{14, 32, 0, 0, 32}, {253, 16, 0, 0, 32}},
         /* 3 */ {{50, 6, 0, 0, 32}, {142, 16, 0, 0, 32}, {253, 24, 0, 0, 32}, {1650, 24, 2, 0, 32}},
         /* 4 */ {{5, 6, 2, 0, 32}, {20, 4, 3, 0, 32}, {37, 8, 2, 0, 32}},
@@ -98,7 +111,8 @@ template <> struct PencilSepRows<double> {
 };
 template <> struct PencilSepRows<float> {
     static constexpr BatchRows rows = {{
-        {}, {},
+        {},
+        /* 1 */ {{1, 64, 2, 1, 32 + kHeld}},
         /* 2 */ {{184, 32, 2, 0, 32}},
         /* 3 */ {{245, 12, 0, 0, 32}},
         /* 4 */ {{5, 2, 2, 0, 32}, {245, 4, 2, 0, 32}},
@@ -140,9 +154,11 @@ struct PencilMmSepRows {
 template <typename T> struct TransformRows;
 template <> struct TransformRows<double> {
     static constexpr BatchRows rows = {{
-        {}, {}, {},
-        /* 3 */ {{2, 32, 0, 0, 32}},
-        /* 4 */ {{14, 2, 2, 1, 32}, {43, 4, 2, 0, 32}},
+        {},
+        /* 1 */ {{14, 64, 2, 1, 32 + kHeld}},
+        /* 2 */ {{4, 16, 0, 0, 32 + kHeld}},
+        /* 3 */ {{2, 32, 0, 0, 32 + kHeld}},
+        /* 4 */ {{1, 2, 2, 1, 32 + kHeld}, {14, 2, 2, 1, 32}, {43, 4, 2, 0, 32}},
         /* 5 */ {{5, 16, 0, 0, 32}, {37, 2, 2, 1, 32}},
         {},
         /* 7 */ {{2, 1, 2, 0, 32}, {43, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
@@ -150,18 +166,20 @@ template <> struct TransformRows<double> {
         /* 9 */ {{50, 2, 0, 0, 32}, {1024, 1, 0, 0, 40}},
         /* 10 */ {{5, 1, 2, 0, 32}, {184, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
         /* 11 */ {{14, 1, 0, 1, 32}, {37, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
-        /* 12 */ {{6, 1, 2, 0, 40 + kWarm}, {1650, 1, 2, 0, 40}},
-        /* 13 */ {{9, 1, 0, 0, 40 + kWarm}, {53, 1, 2, 0, 40}, {184, 3, 0, 0, 40}, {1650, 2, 0, 0, 40}},
-        /* 14 */ {{10, 1, 2, 0, 40 + kWarm}, {57, 1, 2, 0, 40}, {343, 1, 0, 0, 40}, {535, 1, 2, 0, 40}},
-        /* 15 */ {{13, 1, 2, 0, 40 + kWarm}, {57, 1, 2, 0, 40}, {350, 1, 0, 0, 40}},
+        /* 12 */ {{6, 1, 2, 0, 40 + kWarm + kHeldForward}, {1650, 1, 2, 0, 40}},
+        /* 13 */ {{9, 1, 0, 0, 40 + kWarm}, {24, 1, 2, 0, 40 + kHeldForward}, {53, 1, 2, 0, 40}, {184, 3, 0, 0, 40}, {1650, 2, 0, 0, 40}},
+        /* 14 */ {{10, 1, 2, 0, 40 + kWarm + kHeld}, {24, 1, 2, 0, 40 + kHeld}, {57, 1, 2, 0, 40}, {343, 1, 0, 0, 40}, {535, 1, 2, 0, 40}},
+        /* 15 */ {{13, 1, 2, 0, 40 + kWarm + kHeld}, {24, 1, 2, 0, 40 + kHeldForward}, {57, 1, 2, 0, 40}, {350, 1, 0, 0, 40}},
         /* 16 */ {{16, 1, 2, 1, 32 + kWarm}, {53, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
     }};
 };
 template <> struct TransformRows<float> {
     static constexpr BatchRows rows = {{
-        {}, {}, {},
-        /* 3 */ {{53, 12, 0, 0, 32}, {245, 24, 0, 0, 32}},
-        /* 4 */ {{14, 12, 2, 0, 32}},
+        {},
+        /* 1 */ {{14, 64, 2, 1, 32 + kHeld}},
+        /* 2 */ {{14, 16, 0, 0, 32 + kHeld}},
+        /* 3 */ {{3, 12, 0, 0, 32 + kHeld}, {53, 12, 0, 0, 32}, {245, 24, 0, 0, 32}},
+        /* 4 */ {{6, 12, 2, 0, 32 + kHeld}, {14, 12, 2, 0, 32}},
         /* 5 */ {{43, 2, 2, 1, 32}, {245, 2, 0, 1, 32}},
         /* 6 */ {{9, 12, 2, 0, 32}, {26, 6, 2, 0, 32}, {253, 12, 0, 0, 32}, {535, 4, 2, 0, 32}},
         /* 7 */ {{9, 1, 2, 1, 32}, {184, 1, 2, 1, 0, 1}},
@@ -331,27 +349,29 @@ static_assert(batch_rows_in_order(TransformRows<double>::rows) && batch_rows_in_
 static_assert(batch_rows_in_order(SquareConvectionRows<double>::rows) && batch_rows_in_order(SquareConvectionRows<float>::rows));
 static_assert(convection_rect_first_in_order<double>() && convection_rect_first_in_order<float>());
 
-// kWarm stands only where a kernel takes it: not in the 4x4x1 forms (mm, or all rows of a family) and not in the over-integrated
-// forms 1 and 2.
+// The flags stand only where a kernel takes them: not in the 4x4x1 forms (mm, or all rows of a family), kWarm not in the over-integrated
+// forms 1 and 2, kHeld in no convection kernel.
 template <typename ROWS>
-constexpr bool warm_rows_warm(const ROWS &rows, bool all_mm = false)
+constexpr bool flags_are_taken(const ROWS &rows, int flags = kWarm | kHeld)
 {
     for (const auto &list : rows.row)
         for (const auto &r : list)
-            if ((r.sb & kWarm) != 0 && (all_mm || r.mm != 0)) return false;
+            if ((r.sb & ~255 & ~(r.mm != 0 ? 0 : flags)) != 0) return false;
     return true;
 }
 template <typename T>
-constexpr bool convection_rect_warm_rows_warm()
+constexpr bool convection_rect_flags_are_taken()
 {
     for (const ConvRectFirst &r : ConvRectFirstTable<T>::row)
-        if ((r.sb & kWarm) != 0 && r.form != 0) return false;
+        if ((r.sb & ~255 & ~(r.form != 0 ? 0 : kWarm)) != 0) return false;
     return true;
 }
-static_assert(warm_rows_warm(PencilMmRows::rows, true) && warm_rows_warm(PencilMmSepRows::rows, true));
-static_assert(warm_rows_warm(TransformRows<double>::rows) && warm_rows_warm(TransformRows<float>::rows));
-static_assert(warm_rows_warm(SquareConvectionRows<double>::rows) && warm_rows_warm(SquareConvectionRows<float>::rows));
-static_assert(convection_rect_warm_rows_warm<double>() && convection_rect_warm_rows_warm<float>());
+static_assert(flags_are_taken(PencilRows<double>::rows) && flags_are_taken(PencilRows<float>::rows));
+static_assert(flags_are_taken(PencilSepRows<double>::rows) && flags_are_taken(PencilSepRows<float>::rows));
+static_assert(flags_are_taken(PencilMmRows::rows, 0) && flags_are_taken(PencilMmSepRows::rows, 0));
+static_assert(flags_are_taken(TransformRows<double>::rows) && flags_are_taken(TransformRows<float>::rows));
+static_assert(flags_are_taken(SquareConvectionRows<double>::rows, kWarm) && flags_are_taken(SquareConvectionRows<float>::rows, kWarm));
+static_assert(convection_rect_flags_are_taken<double>() && convection_rect_flags_are_taken<float>());
 
 // MiB of the last row of n (0: no rows): a setting for smaller batches than that is never taken.
 template <typename ROWS>

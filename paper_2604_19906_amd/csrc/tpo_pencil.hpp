@@ -125,7 +125,7 @@ __device__ __forceinline__ void matrix_product(const TPO_CONSTANT T *S, const T 
     // SGPR file.
     asm volatile("" : "+s"(S));
     constexpr int NE = R * C;                                   // entries
-    constexpr int B = (SB & ~kWarm) * 4 / (int)sizeof(T);       // entries per batch
+    constexpr int B = (SB & 255) * 4 / (int)sizeof(T);          // entries per batch
     if constexpr (B == 0 || NE <= 2 * B) {
         if constexpr (FWD) {
 #pragma unroll
@@ -299,6 +299,20 @@ __device__ __forceinline__ long long pencil_batch(long long nbatch)
     }
 }
 
+// The first argument of a kernel whose setting has kHeld.  The build has arguments preloaded into scalar registers up to the first one that is a
+// struct: none of them here.  (A struct of one member is passed as that member.)
+template <typename T> struct HeldArgument {
+    const T *p;
+    const void *nothing;
+    __host__ __device__ operator const T *() const { return p; }
+};
+template <typename T, bool HELD> using KernelField = std::conditional_t<HELD, HeldArgument<T>, const T *>;
+template <typename FIELD, typename T> FIELD kernel_field(const T *p)
+{
+    if constexpr (std::is_pointer_v<FIELD>) return p;
+    else return {p, nullptr};
+}
+
 // SEP != 0 : D_e is not read; it is evaluated where it is used from the separable form
 //            D_e[a][b][c] = 1 / (lam_x[a] + lam_y[b] + lam_z[c] + mu[e])
 //            (sum left to right; SEP = 1: IEEE division, SEP = 2: recip_<false>); D is ignored
@@ -309,7 +323,7 @@ __device__ __forceinline__ long long pencil_batch(long long nbatch)
 template <typename T, int N, int G, int HINT, int DDIRECT = 0, bool XCD = false,
           int SEP = 0, int SB = kScalarBatch>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
-ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
+ihelm_pencil_kernel(KernelField<T, (SB & kHeld) != 0> u_, const T *Sx_, const T *Sy_, const T *Sz_,
                     const T *__restrict__ D, T *v, long long num_elems,
                     const T *__restrict__ lam_x, const T *__restrict__ lam_y,
                     const T *lam_z_, const T *__restrict__ mu)
@@ -320,6 +334,7 @@ ihelm_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_,
     T *cube_all = reinterpret_cast<T *>(tpo_lds);
     T *dpark_all = cube_all + G * CUBE;
 
+    const T *u = u_;
     const TPO_CONSTANT T *Sx = (const TPO_CONSTANT T *)Sx_;
     const TPO_CONSTANT T *Sy = (const TPO_CONSTANT T *)Sy_;
     const TPO_CONSTANT T *Sz = (const TPO_CONSTANT T *)Sz_;
@@ -537,6 +552,7 @@ struct PencilLauncherT {
     {
         return &ihelm_pencil_kernel<T, N, G, Tune::HINT, DDIRECT, Tune::XCD, SEP, Tune::SB>;
     }
+    using Field = KernelField<T, (Tune::SB & kHeld) != 0>;
 
     static hipError_t launch(const ApplyArgs &a)
     {
@@ -544,7 +560,7 @@ struct PencilLauncherT {
         if (blocks <= 0 || blocks > 0x7fffffffLL) return kGridTooLarge;
         drop_stale_error();
         hipLaunchKernelGGL(kernel(), dim3((unsigned)blocks), dim3(Sh::NT), LDS, a.stream,
-                           (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
+                           kernel_field<Field>((const T *)a.u), (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
                            (const T *)a.d, (T *)a.v, a.num_elems, (const T *)a.lam_x,
                            (const T *)a.lam_y, (const T *)a.lam_z, (const T *)a.mu);
         return hipGetLastError();

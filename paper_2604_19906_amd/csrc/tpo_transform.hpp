@@ -17,7 +17,7 @@ namespace tpo {
 
 template <typename T, int N, int G, int HINT, bool XCD, bool FWD, int SB>
 __global__ void __launch_bounds__((PencilShape<T, N, G>::NT))
-transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T *t,
+transform_pencil_kernel(KernelField<T, (SB & (FWD ? kHeldForward : kHeldBackward)) != 0> u_, const T *Sx_, const T *Sy_, const T *Sz_, T *t,
                         long long num_elems)
 {
     using Sh = PencilShape<T, N, G>;
@@ -25,6 +25,7 @@ transform_pencil_kernel(const T *u, const T *Sx_, const T *Sy_, const T *Sz_, T 
     extern __shared__ __align__(16) unsigned char tpo_lds[];
     T *cube_all = reinterpret_cast<T *>(tpo_lds);
 
+    const T *u = u_;
     const TPO_CONSTANT T *Sx = (const TPO_CONSTANT T *)Sx_;
     const TPO_CONSTANT T *Sy = (const TPO_CONSTANT T *)Sy_;
     const TPO_CONSTANT T *Sz = (const TPO_CONSTANT T *)Sz_;
@@ -241,6 +242,7 @@ struct TransformLauncherT {
         if constexpr (Tune::MM) return &transform_mm_kernel<N, G, Tune::HINT, Tune::XCD, FWD>;
         else return &transform_pencil_kernel<T, N, G, Tune::HINT, Tune::XCD, FWD, Tune::SB>;
     }
+    using Field = KernelField<T, !Tune::MM && (Tune::SB & (FWD ? kHeldForward : kHeldBackward)) != 0>;
 
     static hipError_t launch(const TransformArgs &a)
     {
@@ -248,7 +250,7 @@ struct TransformLauncherT {
         if (blocks <= 0 || blocks > 0x7fffffffLL) return kGridTooLarge;
         drop_stale_error();
         hipLaunchKernelGGL(kernel(), dim3((unsigned)blocks), dim3(Sh::NT), LDS, a.stream,
-                           (const T *)a.u, (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
+                           kernel_field<Field>((const T *)a.u), (const T *)a.sx, (const T *)a.sy, (const T *)a.sz,
                            (T *)a.t, a.num_elems);
         return hipGetLastError();
     }
