@@ -42,8 +42,9 @@ constexpr int kWarm = 256;
 // launch takes several rounds of workgroups.  Preloaded over held, one matrix and three: halves n = 1 and 2 1.02 .. 1.08 up to the rows' ends, n = 3
 // 1.00 .. 1.07, 4 fp32 1.00 .. 1.05, fp64 0.97 .. 1.05 (0.96 .. 1.01 past 1 MB); n = 12 forward 1.02 .. 1.05 (backward 0.91 .. 0.93), 14 0.99 ..
 // 1.02 and 1.02 .. 1.06, 15 1.01 .. 1.03 and 1.03 .. 1.07; on the rows behind, up to 24 MiB, 1.01 .. 1.05 with one matrix, 0.97 .. 1.01
-// with three, which were no slower held than before there were preloaded arguments; operator n = 1 and 2 1.00 .. 1.08, separable n = 1 1.02.
-// Everywhere else 0.86 .. 1.01.
+// with three, which were no slower held than before there were preloaded arguments; operator n = 1 and 2 1.00 .. 1.08, separable n = 1 1.02;
+// halves n = 9 1.02 with one matrix and 1.00 with three from 50 to 500 MB, n = 10 backward 1.00 .. 1.05 from 50 to 150 MB, 1.00 .. 1.01 beyond
+// (forward 0.93 .. 1.00).
 constexpr int kHeldForward = 512, kHeldBackward = 1024, kHeld = kHeldForward + kHeldBackward;
 
 // sb: words per batch of scalar loads (matrix_product), with or without the flags above; mm: 4x4x1 matrix-core form (halves in fp32).
@@ -163,8 +164,8 @@ template <> struct TransformRows<double> {
         {},
         /* 7 */ {{2, 1, 2, 0, 32}, {43, 1, 2, 1, 32}, {1650, 1, 2, 0, 40}},
         /* 8 */ {{53, 1, 2, 0, 32}, {1650, 1, 2, 0, 40}},
-        /* 9 */ {{50, 2, 0, 0, 32}, {1024, 1, 0, 0, 40}},
-        /* 10 */ {{5, 1, 2, 0, 32}, {184, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
+        /* 9 */ {{50, 2, 0, 0, 32}, {1024, 1, 0, 0, 40 + kHeld}},
+        /* 10 */ {{5, 1, 2, 0, 32}, {184, 1, 2, 0, 40 + kHeldBackward}, {1650, 1, 0, 0, 40 + kHeldBackward}},
         /* 11 */ {{14, 1, 0, 1, 32}, {37, 1, 2, 0, 40}, {1650, 1, 0, 0, 40}},
         /* 12 */ {{6, 1, 2, 0, 40 + kWarm + kHeldForward}, {1650, 1, 2, 0, 40}},
         /* 13 */ {{9, 1, 0, 0, 40 + kWarm}, {24, 1, 2, 0, 40 + kHeldForward}, {53, 1, 2, 0, 40}, {184, 3, 0, 0, 40}, {1650, 2, 0, 0, 40}},
