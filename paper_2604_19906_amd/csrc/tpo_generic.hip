@@ -24,9 +24,11 @@
 // instructions with three axes of 5 .. 7 points, 16 .. 23 % at 8 .. 16.  They are reciprocals in 24 bits, one uniform base that moves
 // along the axis with a 32-bit offset per lane, and one addition per LDS word now; the stores leave in ascending order, which
 // the 128-byte lines that two of them share need (in the compiler's order fp32 (5,5,6) wrote 1.20 of its bytes at 2.4 GB).  Time over
-// the kernels before, arguments in scalar registers included, geometric means over 120 shapes per type at 1 / 8 / 24 / 60 / 100 /
-// 300 MB / 1 / 2.4 GB: fp64 .90 .90 .93 .96 .94 .95 .95 .96 (one turn), turns .94 from 100 MB on; fp32 .88 .84 .90 .92 .91 .90 .89
-// .90, turns .92 .. .94.  One of 1800 calls is slower by more than 4 % (fp64 (14,9,14) at 60 MB, 1.07).
+// the kernels before, arguments in scalar registers and cached stores included, geometric means over 120 shapes per type at 1 / 8 / 24 / 60 / 100 /
+// 300 MB / 1 / 2.4 GB: fp64 .91 .90 .88 .91 .90 .88 .89 .89 (one turn), turns .90 .. .92 from 100 MB on; fp32 .90 .84 .83 .88 .87 .85 .88
+// .88, turns .89 .. .90.  One of 1920 calls is slower by more than 2 % (fp64 (2,2,6) at 300 MB, 1.04).  Vector registers fall by 2 .. 8, scalars
+// spilled to them rise in some classes: one turn fp64 class 12 from none to 16, 16 from 6 to 12; in turns fp64 class 14 from 61 to 72, fp32 class
+// 10 from 19 to 30, the others fall or stay.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -46,26 +48,20 @@ constexpr size_t kTurnsLds = 48 * 1024;                     // of a workgroup of
 // 0.98 at 150, 0.96 at 300, 0.97 at 800 MB; 1.00 .. 1.02 with maxima of 1.09 at 100 and 130 MB (fields that the
 // last-level cache holds in part) and at 2.5 GB, 1.0 .. 1.1 at 30 MB, up to 1.07 on elements of less than 128 points and at 50 MB
 // of less than 300.  In fp32 1.00, up to 1.24 on faces of a dozen points: not there.
-// CACHED: v_e stored without the hint.  Thin faces that fill no whole 128-byte lines: the stores of two indices along axis 0 share most
-// lines, and past the last-level cache the hint writes a line out before its second part comes.  Cached over non-temporal, fp64, faces below
-// 192 bytes: in turns 0.79 .. 1.02 at 350 MB .. 2.4 GB (50 shapes, geometric means 0.95 .. 0.89), up to 1.07 at 290 MB, 1.02 .. 1.05 at
-// 200 MB, 1.0 .. 1.08 on faces of 16 and 24 words; one turn, elements of at most eight points along every axis and of less than 128 in all,
-// 0.90 .. 1.00 from 250 MB on, 1.00 .. 1.06 on faces of 8 and 16 words, 1.02 with one or two points along axis 0.  fp32, one turn, at most
-// six points along every axis: faces of 9 words 0.85 .. 0.91 from 200 MB on (1.17 .. 1.25 at 120 MB), of 6 and 10 words 0.98 .. 1.00; of 8,
-// 12 and 16 words 1.01 .. 1.03, in turns 0.93 .. 1.07.
+// CACHED: v_e stored without the hint.  Thin faces that fill no whole 128-byte lines (below 192 bytes): the stores of two indices along axis 0
+// share most lines, and past the last-level cache the hint writes a line out before its second part comes.  But stores without it take the
+// cache from what the next call on the same fields finds there: all three fields up to 256 MiB of them, u_e and D_e up to 384, D_e alone up to
+// 768 where u_e is streamed.  Cached over non-temporal, the same fields / three sets in turn, 14 sizes from 200 MB to 2.4 GB.
+// fp64 in turns (35 shapes), u_e streamed: 340 and 400 MB 0.85 .. 1.01 / 0.86 .. 1.02, from 850 MB on 0.79 .. 1.02 / 0.80 .. 1.02; 430 .. 700 MB faces
+// of 9 and 15 words 0.90 .. 1.04 / 0.88 .. 0.93, 8, 10 and 12 .. 14 0.91 .. 1.10 / 0.86 .. 0.99, 18 .. 22 0.97 .. 1.14 / 0.92 .. 1.02; not
+// streamed: 340 and 400 MB 1.01 .. 1.14 / 0.85 .. 1.00 ((12,10,1), (8,1,14)), from 460 MB on 0.84 .. 1.01 / 0.83 .. 1.01.  Faces of 16 and 24
+// words 1.00 .. 1.08.
+// One turn, fp64, elements of at most eight points along every axis and of less than 128 in all (24 shapes): 250 MB 0.89 .. 1.01 / 0.95 .. 1.01, 280
+// .. 430 MB 0.99 .. 1.45 / 0.91 .. 1.01, from 460 MB on 0.92 .. 1.02 / 0.91 .. 1.01; faces of 8 and 16 words 1.00 .. 1.06, 1.02 with one or two
+// points along axis 0.  fp32, at most six points along every axis (19 shapes): 200 and 250 MB 0.88 .. 1.02 / 0.87 .. 1.00, 280 .. 400 MB 1.19 .. 1.51 /
+// 0.79 .. 1.00, from 430 MB on 0.83 .. 1.02 / 0.84 .. 1.00; faces of 8, 12 and 16 words 1.01 .. 1.03, in turns 0.93 .. 1.07.
 constexpr int aniso_hint(bool stream, bool cached) { return (stream ? 1 : 0) | (cached ? 0 : 2); }
 constexpr bool aniso_xcd(bool stream) { return !stream; }
-template <typename T>
-bool aniso_cached_stores(const AnisoArgs &a, bool turns)
-{
-    const int face = a.ny * a.nz, points = a.nx * face;
-    const long long mib = 3LL * a.num_elems * points * (long long)sizeof(T) >> 20;
-    const auto all_up_to = [&](int n) { return a.nx <= n && a.ny <= n && a.nz <= n; };
-    if (sizeof(T) == 4)
-        return !turns && a.nx >= 3 && a.ny > 1 && a.nz > 1 && all_up_to(6) && face < 12 && face % 4 != 0 && mib >= 184;
-    if (turns) return face < 24 && face != 16 && mib >= 320;
-    return a.nx >= 3 && all_up_to(8) && !all_up_to(4) && points < 128 && face < 24 && face % 8 != 0 && mib >= 224;
-}
 template <typename T>
 bool aniso_stream(const AnisoArgs &a, bool turns)
 {
@@ -74,6 +70,23 @@ bool aniso_stream(const AnisoArgs &a, bool turns)
     if (sizeof(T) == 4) return false;
     if (!turns && mib >= 48 && mib < 80) return points >= 300;
     return points >= 128 && mib >= 144 && mib < 1536;
+}
+template <typename T>
+bool aniso_cached_stores(const AnisoArgs &a, bool turns)
+{
+    const int face = a.ny * a.nz, points = a.nx * face;
+    const long long mib = 3LL * a.num_elems * points * (long long)sizeof(T) >> 20;
+    const auto all_up_to = [&](int n) { return a.nx <= n && a.ny <= n && a.nz <= n; };
+    if (sizeof(T) == 4)
+        return !turns && a.nx >= 3 && a.ny > 1 && a.nz > 1 && all_up_to(6) && face < 12 && face % 4 != 0
+               && ((mib >= 184 && mib < 244) || mib >= 408);
+    if (turns) {
+        if (face >= 24 || face == 16 || mib < 320) return false;
+        if (!aniso_stream<T>(a, true)) return mib >= 440;
+        return mib < 384 || mib >= 784 || face == 9 || face == 15;
+    }
+    return a.nx >= 3 && all_up_to(8) && !all_up_to(4) && points < 128 && face < 24 && face % 8 != 0
+           && ((mib >= 224 && mib < 244) || mib >= 440);
 }
 
 // f(integral_constant<int, n>) for the runtime n in 1 .. MAXN (uniform over the workgroup).

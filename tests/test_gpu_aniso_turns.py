@@ -84,12 +84,12 @@ def test_streaming(dims, mib):
 
 
 def cached_shapes(regs, streams):
-    """fp64 calls in turns on 320 MiB that store v_e without the non-temporal hint: fewest and most elements per workgroup."""
+    """fp64 calls in turns on 320 or 440 MiB that store v_e without the non-temporal hint: fewest and most elements per workgroup."""
     found = []
     for dims in itertools.product(range(1, regs + 1), repeat=3):
         if max(8, (max(dims) + 1) // 2 * 2) != regs:
             continue
-        e = -(-(320 << 20) // (24 * dims[0] * dims[1] * dims[2]))
+        e = -(-((320 if streams else 440) << 20) // (24 * dims[0] * dims[1] * dims[2]))
         g = turns(dims, "f64", e)[0]
         if g and hints(dims, e) == (streams, 1):
             found.append((g, dims, e))
@@ -116,10 +116,9 @@ def test_cached_stores_in_turns(regs, streams):
         check(dims, "f64", e)
 
 
-@pytest.mark.parametrize("dims,dtype", [((3, 3, 5), "f64"), ((5, 2, 2), "f64"), ((8, 3, 5), "f64"), ((6, 7, 3), "f64"),
-                                        ((4, 3, 3), "f32"), ((6, 3, 3), "f32"), ((3, 2, 5), "f32")])
-def test_cached_stores_in_one_turn(dims, dtype):
-    mib = 224 if dtype == "f64" else 184
+@pytest.mark.parametrize("dims,dtype,mib", [((3, 3, 5), "f64", 224), ((5, 2, 2), "f64", 440), ((8, 3, 5), "f64", 224), ((6, 7, 3), "f64", 440),
+                                            ((4, 3, 3), "f32", 184), ((6, 3, 3), "f32", 408), ((3, 2, 5), "f32", 184)])
+def test_cached_stores_in_one_turn(dims, dtype, mib):
     e = -(-(mib << 20) // (3 * dims[0] * dims[1] * dims[2] * DTYPES[dtype][2])) + 1
     assert hints(dims, e, dtype) == (0, 1) and turns(dims, dtype, e)[0] == 0
     print(f"case cached {dtype} dims={dims} E={e}", flush=True)

@@ -50,8 +50,15 @@ F64, F32 = tpo.TPO_F64, tpo.TPO_F32
 
 
 @pytest.mark.parametrize("dims,dtype,mb,taken", [
-    ((13, 3, 3), F64, 400, True),        # 0.81, in turns
-    ((13, 3, 3), F64, 300, False),       # 0.84 there, 1.02 .. 1.07 on (11,4,3), (16,12,1), (15,9,2)
+    ((13, 3, 3), F64, 480, True),        # 0.83, in turns, u_e not streamed
+    ((13, 3, 3), F64, 400, False),       # 0.95 there on the same fields, 1.11 on (13,1,9), 1.14 on (8,1,14)
+    ((16, 3, 3), F64, 350, True),        # 0.90, u_e streamed
+    ((16, 3, 3), F64, 600, True),        # 1.02 on the same fields, 0.91 on three sets in turn
+    ((16, 3, 3), F64, 300, False),       # 1.02 .. 1.07 on (11,4,3), (16,12,1), (15,9,2)
+    ((12, 12, 1), F64, 400, True),       # 0.96
+    ((12, 12, 1), F64, 600, False),      # 1.08 on the same fields, 0.96 on three sets in turn
+    ((9, 10, 2), F64, 700, False),       # 1.11 on the same fields
+    ((10, 7, 2), F64, 700, False),       # 1.08 on the same fields
     ((10, 7, 2), F64, 1000, True),       # 0.92
     ((13, 1, 15), F64, 2400, True),      # 0.81
     ((16, 5, 3), F64, 700, True),        # 0.98
@@ -59,12 +66,17 @@ F64, F32 = tpo.TPO_F64, tpo.TPO_F32
     ((9, 12, 2), F64, 700, False),       # 1.03
     ((3, 3, 5), F64, 250, True),         # 0.95, one turn per pass
     ((3, 3, 5), F64, 200, False),
+    ((5, 2, 2), F64, 300, False),        # 1.25 on the same fields
+    ((6, 3, 5), F64, 400, False),        # 1.24 on the same fields
+    ((6, 3, 5), F64, 500, True),         # 0.96
     ((3, 4, 4), F64, 400, False),        # 1.03: lines shared by whole faces
     ((2, 7, 2), F64, 400, False),        # 1.02
     ((11, 4, 2), F64, 700, False),      # 1.01
     ((6, 3, 3), F32, 700, True),        # 0.88
     ((6, 3, 3), F32, 200, True),        # 0.85
     ((6, 3, 3), F32, 120, False),       # 1.25
+    ((6, 3, 3), F32, 300, False),       # 1.38 on the same fields
+    ((6, 3, 3), F32, 440, True),        # 0.89
     ((4, 3, 3), F32, 1500, True),       # 0.87
     ((4, 6, 2), F32, 400, False),       # 1.02
     ((13, 3, 3), F32, 700, False)])
