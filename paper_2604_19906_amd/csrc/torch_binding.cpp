@@ -4,8 +4,9 @@
 // shorter than the call 1.4 to 1.8 times as fast; a call that is waited for alone 18 against 22 us).
 //
 // Only the plain case is done here: exact torch.Tensor objects on a device, dense, without any wrapper or mode in their
-// dispatch keys, outside of torch function modes (which see the Python form's calls, the new output's among them), arguments as documented.  For everything else a function returns None without having done anything, and the
-// Python form takes the call with its own checks and errors.  A status other than TPO_OK comes back as a number.
+// dispatch keys, outside of torch function modes (which see the Python form's calls, the new output's among them), arguments as
+// documented.  For everything else a function returns None without having done anything, and the Python form takes the call with
+// its own checks and errors.  A status other than TPO_OK comes back as a number.
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>

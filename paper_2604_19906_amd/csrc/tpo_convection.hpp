@@ -284,7 +284,7 @@ convection_mm_kernel(const float *__restrict__ Pq, const float *__restrict__ Mq,
     };
     // LOADS_FIRST: all four long loads go out before the tables, and the tables before anything waits for one of them.  (Without the
     // second fence the products with M_e move up between the loads of the tables, whose last words then are a round trip of their own:
-    // n = 10, 14 and 15 1.03 .. 1.09 of the time at 30 MB .. 1 GB.)  From n = 13
+    // n = 10, 14 and 15 1.03 .. 1.09 of the time at 30 MB .. 1 GB; up to 16 MB n = 11 and 13 .. 16 0.98 .. 1.00.)  From n = 13
     // on on large batches; below, the registers they hold cost more than the wait there, but less with the few units per workgroup of
     // the rows for small batches (n = 9 .. 12) and at n = 10.  At 3 GB, first against last:
     // n = 13 617 / 651 us, 14 726 / 768, 16 606 / 633; n = 12 614 / 588, 11 636 / 565, 9 605 / 542.  On smaller

@@ -475,8 +475,9 @@ struct PencilTune {
 // (DDIRECT 2), and an LDS request of 36 KB (20.8 KB are used), which holds the CU at 4 workgroups = 8
 // elements instead of 14.  Bound by memory in one-shot bursts: a kernel of the same loads and stores alone
 // runs at 6.28 TB/s with 85 KB asked for per CU and at 5.7 TB/s with 213 KB.  Against D_e at once with 28 KB
-// (5 workgroups) 0.98 of the time at 2.4 GB, 0.977 .. 0.986 at 3, 5.5 and 8.3 GB, one matrix and three; the named
-// workload 1440 -> 1429 us with three sets of fields in turn, 1.429 and 1.430 ms on one set again and again
+// (5 workgroups) 0.98 .. 0.99 of the time at 1.8 .. 8.4 GB and 0.975 .. 0.99 up to 29 GB, one matrix and three, the same
+// fields and three sets in turn (50 calls of 15 alternating rounds, all below 1); the named workload 1437 -> 1420 us (1431 ->
+// 1418 and 1436 -> 1420 on another box), less than what two boxes differ by
 // (32 and 40 KB the same within 1 %; late D_e at 24 and 28 KB 0.99 .. 1.00; D_e at once with 32 .. 40 KB
 // 1.02 .. 1.05; D_e after the product along axis 0 instead, 32 .. 40 KB, 1.01 .. 1.03).  Requests of
 // 32 / 32 / 40 KB at n = 9, 15, 16 give 0.97 .. 1.03: not taken.  The first choice was made on the named workload
